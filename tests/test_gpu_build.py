@@ -149,6 +149,27 @@ def test_build_random_soups_ragged_tiles(ctx, n):
     check_scene(ctx, v, t)
 
 
+@pytest.mark.parametrize("n,spread", [(511, 3.0), (512, 3.0), (513, 3.0), (1025, 3.0), (1700, 0.0),
+                                      (131072, 30.0), (131073, 30.0)])
+def test_build_chunk_and_sort_shape_edges(ctx, n, spread):
+    """Sizes around one and two 512-leaf chunks; equal codes across chunks
+    (spread 0: every triangle has the same box centre, so only leaf indices
+    tell the nodes apart); the largest input of the three-pass sort and of
+    one-by-one chunk boxes, and the next one (four passes, pyramid)."""
+    rng = np.random.default_rng(n)
+    if spread:
+        v, t = synth.random_soup(rng, n, spread)
+    else:
+        half = rng.integers(1, 64, (n, 3, 3)).astype(np.float32) / 64
+        half[:, 1] = -half[:, 0]                # box centre exactly 0
+        half[:, 2] = 0
+        v, t = half.reshape(-1, 3), np.arange(3 * n, dtype=np.int32).reshape(-1, 3)
+    log(f"build edge n={n} spread={spread}")
+    check_scene(ctx, v, t)
+    if n < 2000:
+        check_q8(ctx, v, t)
+
+
 def test_build_duplicate_codes(ctx):
     # many triangles with the same box centre -> equal Morton codes
     v, t = synth.box_room()
