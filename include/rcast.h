@@ -230,7 +230,10 @@ uint64_t rc_device_bytes(rc_ctx *ctx);
  * culling is conservative); they only change speed.
  *   persistent    1: persistent waves that take rays from per-XCD work
  *                 queues and refill idle lanes by wavefront ballot;
- *                 0: one ray per thread, one launch-wide grid (default)
+ *                 0: one ray per thread, one launch-wide grid (default).
+ *                 In the default shape (every field at its default but the
+ *                 tile) a launch too small to fill the chip shares each ray
+ *                 between four or two lanes instead
  *   stack_lds     the top entries of each lane's traversal stack kept in
  *                 LDS, as a ring (deeper entries in scratch): 8, 16 or 24
  *                 for the persistent kernel; 0 (default), 8 or 16 otherwise

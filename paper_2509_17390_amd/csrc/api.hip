@@ -341,8 +341,11 @@ TraceConfig config_of(const rc_tuning &t, const DevJob *jobs, int n_jobs)
 {
     TraceConfig cfg;
     cfg.leaf_batch = t.leaf_batch;
-    for (int k = 0; k < n_jobs; ++k)
+    cfg.pack_ok = true;
+    for (int k = 0; k < n_jobs; ++k) {
         if ((int64_t)jobs[k].n_tris > kLeafBatchMaxTris) cfg.leaf_batch = 0;
+        if ((int64_t)jobs[k].n_tris > kPackMaxTris) cfg.pack_ok = false;
+    }
     cfg.persistent = t.persistent;
     cfg.stack_lds = t.stack_lds;
     cfg.refill_min = t.refill_min;

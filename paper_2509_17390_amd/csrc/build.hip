@@ -410,7 +410,7 @@ __global__ __launch_bounds__(B) void k_scatter(const uint32_t *__restrict__ keys
 // depth 12, parity 8), where separate topology, bottom-up and depth walks
 // took 249; of 54k triangles 35 us against 114.
 constexpr int kChunk = 512;
-constexpr int kTreeBlock = 512;
+constexpr int kTreeBlock = kChunk;
 constexpr int kGroup = 8;                       // leaves under the lowest stored heap level
 constexpr int kHeap = 2 * kChunk / kGroup;      // heap boxes stored per chunk (1..kHeap-1 used)
 constexpr int kPyramid = 8;                     // fan-in of the pyramid over chunk boxes
@@ -450,13 +450,14 @@ __device__ __forceinline__ void store_box(float *__restrict__ p, int64_t i, cons
     q[2] = make_float2(b.hi[1], b.hi[2]);
 }
 
-__device__ __forceinline__ NodeRec node_record(const Box &l, const Box &r, int32_t left, int32_t right)
+__device__ __forceinline__ NodeRec node_record(const Box &l, const Box &r, int32_t left, int32_t right,
+                                               uint32_t pack_l, uint32_t pack_r)
 {
     NodeRec nd;
     nd.q0 = make_float4(l.lo[0], l.hi[0], r.lo[0], r.hi[0]);
     nd.q1 = make_float4(l.lo[1], l.hi[1], r.lo[1], r.hi[1]);
     nd.q2 = make_float4(l.lo[2], l.hi[2], r.lo[2], r.hi[2]);
-    nd.q3 = make_int4(left, right, 0, 0);
+    nd.q3 = make_int4(left, right, (int32_t)pack_l, (int32_t)pack_r);
     return nd;
 }
 
@@ -496,6 +497,7 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const f
     __shared__ int32_t par[kChunk];
     __shared__ int32_t deep[kChunk];
     __shared__ int32_t slist[kChunk];
+    __shared__ uint32_t pack[kChunk];
     __shared__ uint32_t scount, sbase;
     const int tid = threadIdx.x;
     const int32_t n = A.n, c0 = (int32_t)blockIdx.x * kChunk;
@@ -566,9 +568,13 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const f
         }
         return b;
     };
-    for (int j = tid; j < cn; j += kTreeBlock) {
-        const int32_t i = c0 + j;
-        if (i >= n - 1) continue;
+    const int j = tid;
+    const int32_t i = c0 + j;
+    const bool node = j < cn && i < n - 1;
+    bool inside = false;              // this thread's node lies in the chunk
+    int32_t left = 0, right = 0;
+    Box lb, rb;
+    if (node) {
         const uint32_t ki = sk[1 + j];
         // prefix with local leaf q in -1..cn (halo included), -1 outside the input
         auto pre = [&](int q) {
@@ -578,41 +584,46 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const f
         const int pn = pre(j + 1), pp = pre(j - 1);
         const int d = pn >= pp ? 1 : -1;
         const int dmin = d > 0 ? pp : pn;
-        if (pre(d > 0 ? cn : -1) > dmin) {
+        inside = pre(d > 0 ? cn : -1) <= dmin;
+        if (!inside) {
             slist[atomicAdd(&scount, 1u)] = i;
-            continue;
+        } else {
+            // largest l <= len with pre(j + l d) > thr
+            auto farthest = [&](int len, int thr) {
+                int step = 1;
+                while (step <= len && pre(j + step * d) > thr) step <<= 1;
+                int l = step >> 1;                    // pre(j + l d) > thr, or l = 0
+                int hi = step - 1 < len ? step - 1 : len;
+                while (l < hi) {
+                    const int mid = (l + hi + 1) >> 1;
+                    if (pre(j + mid * d) > thr) l = mid; else hi = mid - 1;
+                }
+                return l;
+            };
+            // far end of the range: the last leaf with a prefix above dmin
+            const int l = farthest(d > 0 ? cn - 1 - j : j, dmin);
+            const int e = j + l * d;
+            const int s = farthest(l - 1, pre(e));
+            const int gamma = j + s * d + (d < 0 ? -1 : 0);
+            const int lo = j < e ? j : e, hi = j < e ? e : j;
+            left = lo == gamma ? ~(c0 + gamma) : c0 + gamma;
+            right = hi == gamma + 1 ? ~(c0 + gamma + 1) : c0 + gamma + 1;
+            if (left >= 0) par[gamma] = i;
+            if (right >= 0) par[gamma + 1] = i;
+            pack[j] = pack_children(left, right);
+            lb = query(lo, gamma);
+            rb = query(gamma + 1, hi);
         }
-        // far end of the range: the last leaf with a prefix above dmin
-        const int room = d > 0 ? cn - 1 - j : j;
-        auto farthest = [&](int len, int thr) {   // largest l <= len with pre(j + l d) > thr
-            int step = 1;
-            while (step <= len && pre(j + step * d) > thr) step <<= 1;
-            int l = step >> 1;                    // pre(j + l d) > thr, or l = 0
-            int hi = step - 1 < len ? step - 1 : len;
-            while (l < hi) {
-                const int mid = (l + hi + 1) >> 1;
-                if (pre(j + mid * d) > thr) l = mid; else hi = mid - 1;
-            }
-            return l;
-        };
-        const int l = farthest(room, dmin);
-        const int e = j + l * d;
-        const int s = farthest(l - 1, pre(e));
-        const int gamma = j + s * d + (d < 0 ? -1 : 0);
-        const int lo = j < e ? j : e, hi = j < e ? e : j;
-        const int32_t left = lo == gamma ? ~(c0 + gamma) : c0 + gamma;
-        const int32_t right = hi == gamma + 1 ? ~(c0 + gamma + 1) : c0 + gamma + 1;
-        if (left >= 0) par[gamma] = i;
-        if (right >= 0) par[gamma + 1] = i;
-        A.topo[3 * (int64_t)i + 0] = left;
-        A.topo[3 * (int64_t)i + 1] = right;
-        A.nodes[i] = node_record(query(lo, gamma), query(gamma + 1, hi), left, right);
     }
     __syncthreads();
     if (tid == 0) sbase = scount ? atomicAdd(A.span_count, scount) : 0u;
-    for (int j = tid; j < cn; j += kTreeBlock) {
-        const int32_t i = c0 + j;
-        if (i >= n - 1) continue;
+    if (node) {
+        if (inside) {
+            A.topo[3 * (int64_t)i + 0] = left;
+            A.topo[3 * (int64_t)i + 1] = right;
+            A.nodes[i] = node_record(lb, rb, left, right, left >= 0 ? pack[left - c0] : 0u,
+                                     right >= 0 ? pack[right - c0] : 0u);
+        }
         if (par[j] >= 0) A.topo[3 * (int64_t)i + 2] = par[j];
         int d = 0, r = j;
         for (int32_t p = par[r]; p >= 0; p = par[r]) {
@@ -624,8 +635,7 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const f
         if (d) atomicMax(&deep[r], d);
     }
     __syncthreads();
-    for (int j = tid; j < cn; j += kTreeBlock)
-        if (c0 + j < n - 1 && par[j] < 0) A.sub_height[c0 + j] = (uint8_t)deep[j];
+    if (node && par[j] < 0) A.sub_height[i] = (uint8_t)deep[j];
     for (uint32_t q = tid; q < scount; q += kTreeBlock) A.span[sbase + q] = slist[q];
     if (blockIdx.x == 0 && tid == 0) {
         if (n > 1 && n <= kChunk) {   // the whole tree
@@ -772,7 +782,7 @@ __device__ void span_node(const TreeArrays &A, int m, int32_t i)
         if (left >= 0) A.topo[3 * (int64_t)left + 2] = i;
         if (right >= 0) A.topo[3 * (int64_t)right + 2] = i;
         if (i == 0) A.topo[2] = -1;
-        A.nodes[i] = node_record(b[0], b[1], left, right);
+        A.nodes[i] = node_record(b[0], b[1], left, right, 0u, 0u);   // packs: span_depth
         A.rel[i] = 0;
         A.sroot[i] = i;
         A.sub_height[i] = kCrosses;
@@ -780,15 +790,18 @@ __device__ void span_node(const TreeArrays &A, int m, int32_t i)
 }
 
 // Depth of a crossing node by its ancestors (all of them cross chunks), and
-// of the chunk subtrees and leaves below it.
+// of the chunk subtrees and leaves below it; its record's names of its
+// children's children.
 __device__ void span_depth(const TreeArrays &A, int32_t i)
 {
     int d = 0;
     for (int32_t p = A.topo[3 * (int64_t)i + 2]; p >= 0 && d <= 64; p = A.topo[3 * (int64_t)p + 2]) ++d;
     A.base[i] = (uint8_t)d;
     int deepest = 0;
+    uint32_t pack[2];
     for (int k = 0; k < 2; ++k) {
         const int32_t c = A.topo[3 * (int64_t)i + k];
+        pack[k] = c < 0 ? 0u : pack_children(A.topo[3 * (int64_t)c], A.topo[3 * (int64_t)c + 1]);
         if (c < 0) {
             deepest = deepest > d + 1 ? deepest : d + 1;
         } else if (A.sub_height[c] != kCrosses) {
@@ -797,6 +810,8 @@ __device__ void span_depth(const TreeArrays &A, int32_t i)
             deepest = deepest > t ? deepest : t;
         }
     }
+    int2 *q3 = reinterpret_cast<int2 *>(&A.nodes[i].q3);
+    q3[1] = make_int2((int32_t)pack[0], (int32_t)pack[1]);
     atomicMax(A.depth_out, deepest);
 }
 

@@ -12,9 +12,11 @@
 //   q0 = (L.lo.x, L.hi.x, R.lo.x, R.hi.x)
 //   q1 = (L.lo.y, L.hi.y, R.lo.y, R.hi.y)
 //   q2 = (L.lo.z, L.hi.z, R.lo.z, R.hi.z)
-//   q3 = (ref L, ref R, -, -)   as int bits
+//   q3 = (ref L, ref R, children of L, children of R)   as int bits
 // A child reference c >= 0 is an internal node index; c < 0 is the leaf
-// holding triangle record ~c (leaf order).  Node 0 is the root.
+// holding triangle record ~c (leaf order).  Node 0 is the root.  The two
+// children of a node are adjacent (g and g + 1, as node or leaf), so one
+// word names them both: pack_children; it is 0 for a leaf.
 //
 // Triangle record, 48 bytes = 3 x float4, in leaf order:
 //   (v0.x v0.y v0.z v1.x) (v1.y v1.z v2.x v2.y) (v2.z id - -)
@@ -24,6 +26,14 @@ struct NodeRec {
     int4 q3;
 };
 static_assert(sizeof(NodeRec) == 64, "node record is 64 bytes");
+
+// g << 2 | (g is a leaf) | (g + 1 is a leaf) << 1; holds trees of up to 2^30
+// primitives (larger ones: unspecified, and not read)
+__host__ __device__ inline uint32_t pack_children(int32_t left, int32_t right)
+{
+    return ((uint32_t)(left < 0 ? ~left : left) << 2) | (left < 0 ? 1u : 0u) | (right < 0 ? 2u : 0u);
+}
+constexpr int64_t kPackMaxTris = (int64_t)1 << 30;
 
 struct TriRec {
     float4 a, b, c;
@@ -106,6 +116,7 @@ struct TraceConfig {
     int group_waves;    // waves per workgroup of the one-ray-per-thread grid (1 or 4)
     int leaf_batch;     // Q8 grid: 0 tests leaves on the spot; 1..64 queues them per wave
                         // and tests them once this many are queued (scenes < 2^26 tris)
+    bool pack_ok;       // every scene's nodes can be named by pack_children
 };
 
 // Largest scene (triangles) the queued-leaf traversal takes: a queued pair
@@ -146,7 +157,8 @@ hipError_t validate_mesh_launch(const float *verts, int64_t nv, const int32_t *t
 
 enum TraceMode { TRACE_BVH = 0, TRACE_BRUTE = 1, TRACE_STATS = 2 };
 
-enum NodeFormat { FMT_BINARY = 0, FMT_Q8 = 1 };
+// FMT_WIDE: the plain records, two levels a visit (a traversal, not a layout)
+enum NodeFormat { FMT_BINARY = 0, FMT_Q8 = 1, FMT_WIDE = 2 };
 
 hipError_t trace_launch(int mode, int fmt, const TraceConfig &cfg, const DevJob *jobs, int n_jobs,
                         WorkQueues *queues, int64_t total_rays, float *out_range,

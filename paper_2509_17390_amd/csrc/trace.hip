@@ -17,6 +17,8 @@
 //    instead of waiting for the slowest wave of a larger workgroup (10%
 //    faster than four-wave workgroups on the headline batch); four-wave
 //    workgroups spread a small launch over more CUs.
+//    Launches that leave the chip idle share a ray between four or two lanes
+//    instead (k_trace_group).
 //  * Persistent waves.  The launch's rays are split into one contiguous
 //    range per XCD (workgroups are dispatched round-robin over the 8 XCDs,
 //    so block b runs on XCD b % 8 and takes rays from range b % 8 first,
@@ -29,10 +31,11 @@
 //    stack live in LDS (slot-major, so the 64 lanes of a wave touch 64
 //    consecutive words); deeper entries are in scratch.  A Karras tree over
 //    3b-bit codes plus index tie-breaks is at most 62 levels deep, so 64
-//    entries always suffice (96 for 4-wide nodes: at most three pushes per
-//    level).
-//  * Node formats: the binary tree with FP32 child boxes, or 4-wide nodes
-//    with 8-bit child boxes in the node's frame (see node_step_q8).
+//    entries always suffice (96 for four candidates a visit: at most three
+//    pushes per two levels).
+//  * Node formats: the binary tree with FP32 child boxes, walked two levels a
+//    visit (node_step_wide), or 4-wide nodes with 8-bit child boxes in the
+//    node's frame (node_step_q8).
 //
 // Numerics (compiled with -ffp-contract=off so every variant rounds alike):
 //  * Ray: direction R_s d_j is formed and normalised in FP64, then rounded to
@@ -394,6 +397,7 @@ __device__ __forceinline__ void test_leaf(LaneRay &L, int leaf)
 
 // Set up the ray with flattened launch index g; returns true if it still
 // needs traversal (false: already finished, e.g. empty scene).
+template <int FMT>
 __device__ __forceinline__ bool setup_ray(const DevJob *__restrict__ jobs, int n_jobs, int64_t g,
                                           LaneRay &L)
 {
@@ -427,6 +431,10 @@ __device__ __forceinline__ bool setup_ray(const DevJob *__restrict__ jobs, int n
     if (jb.root_leaf) {
         test_leaf(L, 0);
         return false;
+    }
+    if (FMT == FMT_WIDE) {
+        const float4 w = ldg4(L.nodes, 3);
+        L.node = (int)pack_children(__float_as_int(w.x), __float_as_int(w.y));
     }
     return true;
 }
@@ -595,10 +603,127 @@ __device__ __forceinline__ bool node_step_q8(LaneRay &L, LaneStack<SS, STK, BLK>
     return !more | full;
 }
 
+// Sort key of a candidate at distance t >= 0: the bits of t order like t, and
+// the candidate's number in the two lowest makes keys distinct, so an integer
+// minimum and maximum sort them.  The number raises t by at most three units
+// in the last place, far inside t_hi's margin.  kNoKey (+inf) and above: none.
+constexpr uint32_t kNoKey = 0x7f800000u;
+
+__device__ __forceinline__ uint32_t sort_key(bool in, float t, int k)
+{
+    return ((in ? __float_as_uint(t + 0.0f) : kNoKey) & ~3u) | (uint32_t)k;
+}
+
+// Plain nodes, two levels a visit.  A node is named by its children
+// (pack_children): they are adjacent records, so both are fetched at once and
+// their four boxes are the candidates.  A child that is a leaf itself has no
+// box here and goes to its triangle test.  Against one binary node a visit
+// this halves the dependent fetches (the chain that bounds a wave) and three
+// quarters of the loop's bookkeeping.  8.4M rays on 18k / 1.03M / 3M / 52k
+// triangles: 972 / 1,526 / 2,015 / 1,189 us against 1,031 / 1,705 / 2,406 /
+// 1,360 with one node a visit.
+template <int SS, int STK, int BLK>
+__device__ __forceinline__ bool node_step_wide(LaneRay &L, LaneStack<SS, STK, BLK> &S)
+{
+    const uint32_t e = (uint32_t)L.node;
+    const bool leaf0 = e & 1u, leaf1 = e & 2u;
+    const int32_t g = (int32_t)(e >> 2);
+    // (the record of a leaf child is replaced by the root's, and not used)
+    const uint32_t e0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)e);
+    const uint64_t p = (uint64_t)(uintptr_t)L.nodes;
+    const uint32_t plo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+    const uint32_t phi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+    const uint64_t p0 = ((uint64_t)phi << 32) | plo;
+    float4 a[4], b[4];
+    if (__ballot(e != e0 || p != p0) == 0ull) {   // as in load_node
+        const int64_t i0 = e0 & 1u ? 0 : (int64_t)(e0 >> 2);
+        const int64_t i1 = e0 & 2u ? 0 : (int64_t)(e0 >> 2) + 1;
+        const gvec4_c *q = (const gvec4_c *)(uintptr_t)p0;
+        for (int k = 0; k < 4; ++k) {
+            const gvec4 x = q[4 * i0 + k], y = q[4 * i1 + k];
+            a[k] = make_float4(x.x, x.y, x.z, x.w);
+            b[k] = make_float4(y.x, y.y, y.z, y.w);
+        }
+    } else {
+        const int64_t i0 = leaf0 ? 0 : (int64_t)g, i1 = leaf1 ? 0 : (int64_t)g + 1;
+        for (int k = 0; k < 4; ++k) {
+            a[k] = ldg4(L.nodes, 4 * i0 + k);
+            b[k] = ldg4(L.nodes, 4 * i1 + k);
+        }
+    }
+    ++L.n_nodes;
+    float t[4];
+    t[0] = slab(L.r, a[0].x, a[0].y, a[1].x, a[1].y, a[2].x, a[2].y, L.t_lo, L.t_hi);
+    t[1] = slab(L.r, a[0].z, a[0].w, a[1].z, a[1].w, a[2].z, a[2].w, L.t_lo, L.t_hi);
+    t[2] = slab(L.r, b[0].x, b[0].y, b[1].x, b[1].y, b[2].x, b[2].y, L.t_lo, L.t_hi);
+    t[3] = slab(L.r, b[0].z, b[0].w, b[1].z, b[1].w, b[2].z, b[2].w, L.t_lo, L.t_hi);
+    t[0] = leaf0 ? L.t_lo : t[0];
+    t[1] = leaf0 ? INFINITY : t[1];
+    t[2] = leaf1 ? L.t_lo : t[2];
+    t[3] = leaf1 ? INFINITY : t[3];
+    // a leaf's triangle, or what names an internal node
+    const int32_t ref[4] = {leaf0 ? ~g : __float_as_int(a[3].x), __float_as_int(a[3].y),
+                            leaf1 ? ~(g + 1) : __float_as_int(b[3].x), __float_as_int(b[3].y)};
+    const uint32_t name[4] = {__float_as_uint(a[3].z), __float_as_uint(a[3].w),
+                              __float_as_uint(b[3].z), __float_as_uint(b[3].w)};
+    uint32_t lm = 0;
+    uint32_t key[4];
+    for (int k = 0; k < 4; ++k) {
+        const bool hit = t[k] < INFINITY;
+        lm |= ref[k] < 0 && hit ? 1u << k : 0u;
+        key[k] = sort_key(ref[k] >= 0 && hit, t[k], k);
+    }
+#pragma unroll 1
+    while (lm != 0u) {
+        const int k = __builtin_ctz(lm);
+        lm &= lm - 1u;
+        const float tk = k == 0 ? t[0] : (k == 1 ? t[1] : (k == 2 ? t[2] : t[3]));
+        const int32_t rk = k == 0 ? ref[0] : (k == 1 ? ref[1] : (k == 2 ? ref[2] : ref[3]));
+        if (tk <= L.t_hi) test_leaf(L, ~rk);
+    }
+    // internal candidates: continue with the nearest, push the others
+    // farthest first
+#define RC_KSWAP(i, j)                                                  \
+    {                                                                   \
+        const uint32_t lo = key[i] < key[j] ? key[i] : key[j];          \
+        key[j] = key[i] < key[j] ? key[j] : key[i];                     \
+        key[i] = lo;                                                    \
+    }
+    RC_KSWAP(0, 1) RC_KSWAP(2, 3) RC_KSWAP(0, 2) RC_KSWAP(1, 3) RC_KSWAP(1, 2)
+#undef RC_KSWAP
+    const uint32_t lim = __float_as_uint(fminf(L.t_hi, FLT_MAX)) | 3u;
+    auto name_of = [&](uint32_t w) {
+        const uint32_t n01 = w & 1u ? name[1] : name[0], n23 = w & 1u ? name[3] : name[2];
+        return (int)(w & 2u ? n23 : n01);
+    };
+    const bool full = L.sp > STK - 3;
+    L.corrupt = L.corrupt | full;
+    if (key[1] <= lim && !full) {
+        if (key[3] <= lim) S.put(L.sp++, name_of(key[3]), __uint_as_float(key[3]));
+        if (key[2] <= lim) S.put(L.sp++, name_of(key[2]), __uint_as_float(key[2]));
+        S.put(L.sp++, name_of(key[1]), __uint_as_float(key[1]));
+    }
+    bool more = key[0] <= lim;
+    L.node = more ? name_of(key[0]) : L.node;
+    bool pop = !more;
+    while (pop & (L.sp > 0)) {
+        --L.sp;
+        int n;
+        float tt;
+        S.get(L.sp, n, tt);
+        const bool ok = tt <= L.t_hi;
+        L.node = ok ? n : L.node;
+        more = ok;
+        pop = !ok;
+    }
+    return !more | full;
+}
+
 template <int FMT, int SS, int STK, int BLK>
 __device__ __forceinline__ bool visit(LaneRay &L, LaneStack<SS, STK, BLK> &S)
 {
     if (FMT == FMT_Q8) return node_step_q8<SS, STK, BLK>(L, S);
+    if (FMT == FMT_WIDE) return node_step_wide<SS, STK, BLK>(L, S);
     return node_step<SS, STK, BLK>(L, S);
 }
 
@@ -652,9 +777,9 @@ __global__ __launch_bounds__(BLK, WAVES) void k_trace(const DevJob *__restrict__
     const int64_t g = g0 + (int64_t)blockIdx.x * BLK + threadIdx.x;
     if (g >= total) return;
     LaneRay L;
-    LaneStack<SS, FMT == FMT_Q8 ? kStackQ8 : kStack, BLK> S;
+    LaneStack<SS, FMT == FMT_BINARY ? kStack : kStackQ8, BLK> S;
     S.lw = s_stk + threadIdx.x;
-    bool go = setup_ray(jobs, n_jobs, g, L);
+    bool go = setup_ray<FMT>(jobs, n_jobs, g, L);
     if (MODE == TRACE_BRUTE) {
         for (int k = 0; go && k < L.n_tris_scene; ++k) test_leaf(L, k);
     } else {
@@ -829,7 +954,7 @@ __global__ __launch_bounds__(BLK, WAVES) void k_trace_defer(const DevJob *__rest
     L.n_tris = 0;
     L.n_nodes = 0;
     if (valid) {
-        trav = setup_ray(jobs, n_jobs, g, L);
+        trav = setup_ray<FMT_Q8>(jobs, n_jobs, g, L);
         W.o[0][lane] = L.r.o[0];
         W.o[1][lane] = L.r.o[1];
         W.o[2][lane] = L.r.o[2];
@@ -942,6 +1067,215 @@ __global__ __launch_bounds__(BLK, WAVES) void k_trace_defer(const DevJob *__rest
     finish_ray<MODE>(L, out_range, out_hit, out_nodes, out_tris);
 }
 
+// ---------------------------------------------------------------------------
+// Several lanes per ray, for launches that leave the chip idle.
+//
+// A launch of a few thousand waves ends with its longest ray: the time is the
+// number of node visits of that ray times the length of one visit, and with
+// one ray per lane a visit is some 250 vector instructions behind a dependent
+// fetch (about 1.6 us with one to four waves on a SIMD).  Here G = 4 or 2
+// lanes share a ray and its four candidates of a visit: each lane tests 4 / G
+// boxes and, where they are leaves, their triangles, so a visit is shorter,
+// leaves are tested side by side, and a wave ends with the longest of 64 / G
+// rays.  More lanes per ray issue more instructions in all, so they pay only
+// while the launch is short of waves (see group_lanes).
+//  * Quantised nodes: the candidates are the four children.
+//  * Plain nodes: two levels a visit, as in node_step_wide.
+// Candidates are ranked by entry distance with lane permutes; the nearest is
+// taken next and the others go to the ray's stack in LDS, all in one step.
+// Entries beyond kGroupLds (deeper than nearly every ray gets) are kept by
+// every lane of the group in scratch.  Results are the same (t, triangle id)
+// minima.
+constexpr int kGroupLds = 24;
+constexpr int kXor1 = 0xb1, kXor2 = 0x4e, kXor3 = 0x1b;   // quad_perm controls
+template <int CTRL>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
+}
+
+template <int CTRL>
+__device__ __forceinline__ void merge_best(LaneRay &L)
+{
+    const float t = __uint_as_float(quad_perm<CTRL>(__float_as_uint(L.best_t)));
+    const int id = (int)quad_perm<CTRL>((uint32_t)L.best_id);
+    const int leaf = (int)quad_perm<CTRL>((uint32_t)L.best_leaf);
+    const bool b = better(t, id, L.best_t, L.best_id);
+    L.best_t = b ? t : L.best_t;
+    L.best_id = b ? id : L.best_id;
+    L.best_leaf = b ? leaf : L.best_leaf;
+}
+
+// One lane's candidates of a visit: entry distance (+inf: none), leaf ~ref
+// or internal node, and what a visit of that node starts from.
+template <int C>
+struct Candidates {
+    float t[C];
+    int32_t ref[C];
+    uint32_t entry[C];
+};
+
+// lane j of the group's candidates j * C .. j * C + C - 1 of `entry`
+template <int FMT, int C>
+__device__ __forceinline__ Candidates<C> fetch_candidates(const LaneRay &L, uint32_t entry, int j)
+{
+    Candidates<C> h;
+    if constexpr (FMT == FMT_Q8) {
+        const float4 q0 = ldg4(L.nodes, 4 * (int64_t)entry), q1 = ldg4(L.nodes, 4 * (int64_t)entry + 1),
+                     q2 = ldg4(L.nodes, 4 * (int64_t)entry + 2);
+        typedef __attribute__((address_space(1))) const int32_t gint_g;
+        for (int c = 0; c < C; ++c)
+            h.ref[c] = ((gint_g *)L.nodes)[16 * (int64_t)entry + 12 + j * C + c];
+        const float org[3] = {q0.x, q0.y, q0.z}, scl[3] = {q0.w, q1.x, q1.y};
+        const uint32_t lo[3] = {__float_as_uint(q1.z), __float_as_uint(q2.x), __float_as_uint(q2.z)};
+        const uint32_t hi[3] = {__float_as_uint(q1.w), __float_as_uint(q2.y), __float_as_uint(q2.w)};
+        float en[C], ex[C];
+        for (int c = 0; c < C; ++c) { en[c] = L.t_lo; ex[c] = L.t_hi; }
+        for (int a = 0; a < 3; ++a) {
+            // node_step_q8's bounds
+            const float inv = L.r.inv[a];
+            const float aa = (org[a] - L.r.org[a]) * inv;
+            const float b = scl[a] * inv;
+            const float E = kQErr * fmaf(255.0f, fabsf(b), fabsf(aa));
+            const bool neg = inv < 0.0f;
+            const uint32_t qn = (neg ? hi[a] : lo[a]) >> (8 * C * j);
+            const uint32_t qf = (neg ? lo[a] : hi[a]) >> (8 * C * j);
+            for (int c = 0; c < C; ++c) {
+                en[c] = fmaxf(en[c], fmaf(qbyte(qn, c), b, aa - E));
+                ex[c] = fminf(ex[c], fmaf(qbyte(qf, c), b, aa + E));
+            }
+        }
+        for (int c = 0; c < C; ++c) {
+            h.entry[c] = (uint32_t)h.ref[c];
+            h.t[c] = h.ref[c] != kEmptyChild && en[c] <= ex[c] ? en[c] : INFINITY;
+        }
+    } else {
+        const int which = C == 2 ? j : j >> 1, slot = C == 2 ? 0 : j & 1;
+        const int32_t child = (int32_t)(entry >> 2) + which;
+        for (int c = 0; c < C; ++c) {
+            h.ref[c] = ~child;
+            h.entry[c] = 0;
+            h.t[c] = slot + c ? INFINITY : L.t_lo;
+        }
+        if (!((entry >> which) & 1u)) {   // not a leaf
+            typedef float gvec2 __attribute__((ext_vector_type(2)));
+            typedef __attribute__((address_space(1))) const gvec2 gvec2_g;
+            const gvec2_g *p = (gvec2_g *)L.nodes + 8 * (int64_t)child + slot;
+            const float4 w = ldg4(L.nodes, 4 * (int64_t)child + 3);
+            for (int c = 0; c < C; ++c) {
+                const gvec2 x = p[c], y = p[2 + c], z = p[4 + c];
+                h.t[c] = slab(L.r, x.x, x.y, y.x, y.y, z.x, z.y, L.t_lo, L.t_hi);
+                h.ref[c] = __float_as_int(slot + c ? w.y : w.x);
+                h.entry[c] = __float_as_uint(slot + c ? w.w : w.z);
+            }
+        }
+    }
+    return h;
+}
+
+template <int FMT, int G>
+__global__ __launch_bounds__(64, G == 4 ? 8 : 6) void k_trace_group(const DevJob *__restrict__ jobs, int n_jobs,
+                                                       int64_t total, float *__restrict__ out_range,
+                                                       int32_t *__restrict__ out_hit)
+{
+    constexpr int C = 4 / G, RAYS = 64 / G;
+    __shared__ uint64_t s_stk[kGroupLds][RAYS];
+    const int lane = threadIdx.x, j = lane & (G - 1);
+    const int64_t g = (int64_t)blockIdx.x * RAYS + lane / G;
+    if (g >= total) return;
+    uint64_t deep[kStackQ8 - kGroupLds];
+    uint64_t *stk = &s_stk[0][lane / G];
+    LaneRay L;
+    bool go = setup_ray<FMT>(jobs, n_jobs, g, L);
+    uint32_t entry = (uint32_t)L.node;
+    while (go) {
+        const Candidates<C> h = fetch_candidates<FMT, C>(L, entry, j);
+        uint32_t lm = 0;
+        for (int c = 0; c < C; ++c) lm |= h.ref[c] < 0 && h.t[c] < INFINITY ? 1u << c : 0u;
+        if (__ballot(lm != 0u)) {
+            if constexpr (C == 1) {
+                if (lm) test_leaf(L, ~h.ref[0]);
+            } else {
+#pragma unroll 1
+                while (lm != 0u) {
+                    const int c = __builtin_ctz(lm);
+                    lm &= lm - 1u;
+                    const float tc = c == 0 ? h.t[0] : h.t[C - 1];
+                    if (tc <= L.t_hi) test_leaf(L, ~(c == 0 ? h.ref[0] : h.ref[C - 1]));
+                }
+            }
+            // the group's best hit (a (t, id) minimum, so the order is free)
+            merge_best<kXor1>(L);
+            if constexpr (G == 4) merge_best<kXor2>(L);
+            L.t_hi = L.best_leaf >= 0 ? L.best_t * (1.0f + kCullRel) : L.t_hi;
+        }
+        const float lim = fminf(L.t_hi, FLT_MAX);
+        uint32_t key[C], rank[C];
+        uint32_t nh = 0;
+        for (int c = 0; c < C; ++c) {
+            const bool in = h.ref[c] >= 0 && h.t[c] <= lim;
+            key[c] = sort_key(in, h.t[c], j * C + c);
+            nh += in ? 1u : 0u;
+        }
+        for (int c = 0; c < C; ++c) {
+            rank[c] = 0;
+            if constexpr (G == 4) {
+                rank[c] += quad_perm<kXor1>(key[c]) < key[c] ? 1u : 0u;
+                rank[c] += quad_perm<kXor2>(key[c]) < key[c] ? 1u : 0u;
+                rank[c] += quad_perm<kXor3>(key[c]) < key[c] ? 1u : 0u;
+            } else {
+                for (int o = 0; o < C; ++o) rank[c] += quad_perm<kXor1>(key[o]) < key[c] ? 1u : 0u;
+                rank[c] += key[C - 1 - c] < key[c] ? 1u : 0u;
+            }
+        }
+        nh += quad_perm<kXor1>(nh);
+        if constexpr (G == 4) nh += quad_perm<kXor2>(nh);
+        const int sp = L.sp;
+        const bool full = sp > kStackQ8 - 3;   // deeper than any valid tree
+        const int top = sp + (int)nh - 1;      // the stack's size after the pushes
+        uint32_t next = 0;
+        for (int c = 0; c < C; ++c) {
+            const bool in = key[c] < kNoKey;
+            next |= in && rank[c] == 0 ? h.entry[c] : 0u;
+            const int at = top - (int)rank[c];   // farthest lowest
+            if (in && rank[c] > 0 && !full && at < kGroupLds)
+                stk[RAYS * at] = (uint64_t)h.entry[c] | ((uint64_t)key[c] << 32);
+        }
+        if (top > kGroupLds && !full) {
+            for (int q = 0; q < 4; ++q) {   // every lane keeps candidate q
+                const int c = q % C, src = lane - j + q / C;
+                const uint32_t k = (uint32_t)__shfl((int)(c == 0 ? key[0] : key[C - 1]), src, 64);
+                const uint32_t e = (uint32_t)__shfl((int)(c == 0 ? h.entry[0] : h.entry[C - 1]), src, 64);
+                const int r = __shfl((int)(c == 0 ? rank[0] : rank[C - 1]), src, 64);
+                if (k < kNoKey && r > 0 && top - r >= kGroupLds)
+                    deep[top - r - kGroupLds] = (uint64_t)e | ((uint64_t)k << 32);
+            }
+        }
+        wave_sync_lds();   // a lane's entries are read by the group's others
+        next |= quad_perm<kXor1>(next);
+        if constexpr (G == 4) next |= quad_perm<kXor2>(next);
+        bool more = nh > 0;
+        entry = next;
+        L.sp = more && !full ? top : sp;
+        bool pop = !more;
+        while (pop && L.sp > 0) {
+            --L.sp;
+            uint64_t w;
+            if (L.sp < kGroupLds) w = stk[RAYS * L.sp];
+            else w = deep[L.sp - kGroupLds];
+            more = __uint_as_float((uint32_t)(w >> 32)) <= L.t_hi;
+            entry = (uint32_t)w;
+            pop = !more;
+        }
+        // a correct traversal visits each record at most once
+        const bool over = ++L.fetched > L.n_tris_scene + 64;
+        L.corrupt = L.corrupt | full | (more & over);
+        go = more & !full & !over;
+        wave_sync_lds();
+    }
+    if (j == 0) finish_ray<TRACE_BVH>(L, out_range, out_hit, nullptr, nullptr);
+}
+
 // Persistent waves with per-XCD queues, stealing and ballot refill.  Each
 // wave keeps a private pool of consecutive ray indices [pool_next, pool_end)
 // in scalar registers and refills idle lanes from it; the pool itself is
@@ -959,7 +1293,7 @@ __global__ __launch_bounds__(kBlock) void k_trace_persistent(
     const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const unsigned long long n_waves = (unsigned long long)gridDim.x * (kBlock / 64);
     LaneRay L;
-    LaneStack<SS, FMT == FMT_Q8 ? kStackQ8 : kStack, kBlock> S;
+    LaneStack<SS, FMT == FMT_BINARY ? kStack : kStackQ8, kBlock> S;
     S.lw = s_stk + threadIdx.x;
     int xq = blockIdx.x % kQueues;
     bool exhausted = false;   // wave-uniform
@@ -1007,7 +1341,7 @@ __global__ __launch_bounds__(kBlock) void k_trace_persistent(
                 const unsigned long long rank = __popcll(idle & lt_mask);
                 const bool mine = ((idle >> lane) & 1ull) && rank < take;
                 if (mine) {
-                    active = setup_ray(jobs, n_jobs, (int64_t)(pool_next + rank), L);
+                    active = setup_ray<FMT>(jobs, n_jobs, (int64_t)(pool_next + rank), L);
                     if (!active) finish_ray<MODE>(L, out_range, out_hit, out_nodes, out_tris);
                 }
                 pool_next += take;
@@ -1061,12 +1395,42 @@ hipError_t launch_persistent(const TraceConfig &cfg, const DevJob *jobs, int n_j
     return hipGetLastError();
 }
 
+// Lanes per ray of a launch in the default shape (a caller who asks for an
+// LDS stack, larger workgroups, persistent waves or queued leaf tests gets
+// them).  Four lanes win while the launch has fewer waves than the chip holds,
+// two a little longer on plain nodes, whose one-lane visit is dearer; beyond,
+// the extra instructions of shared rays cost more than the short waves save.
+// us per call for indoor 18k / indoor 1.03M / terrain 3M / terrain 52k
+// triangles, rays in rows:
+//                quantised: 1 lane       4 lanes            plain: 1 lane          2 lanes             4 lanes
+//      5,760   110 152 137 116     85 102  95  81     113 157 145 121     91 118 115  96     81  98  92  80
+//    131,072   140 217 249 146    105 146 177 120     149 230 288 164    115 162 210 129    110 151 175 122
+//    262,144   127 260 247 128    131 210 177 129     147 298 259 142    125 214 204 122    129 208 176 131
+//    524,288   178 267 321 212    190 271 272 210     195 297 353 233    170 254 266 194    191 269 266 214
+//  1,048,576   232 355 394 262    296 408 455 343     249 390 440 289    239 355 409 280    297 392 461 337
+//  2,097,152   314 480 581 397    505 678 740 560     352 550 686 446    394 557 645 448    501 673 739 569
+// (262,144 is one dense frame, the others 1,024 azimuths an environment; the
+// calls' host side is some 45 us of each.)
+constexpr int64_t kFourLaneRays = 3 << 17;
+constexpr int64_t kTwoLaneRays = 3 << 19;   // plain nodes
+
+int group_lanes(const TraceConfig &cfg, int fmt, int64_t total)
+{
+    if (cfg.persistent || cfg.stack_lds != 0 || !cfg.waves_cap || cfg.group_waves != 1 ||
+        cfg.leaf_batch != 0)
+        return 1;
+    if (total <= kFourLaneRays) return 4;
+    return fmt == FMT_WIDE && total <= kTwoLaneRays ? 2 : 1;
+}
+
 template <int MODE, int FMT>
 hipError_t launch_mode(const TraceConfig &cfg, const DevJob *jobs, int n_jobs, WorkQueues *queues,
                        int64_t total, float *out_range, int32_t *out_hit, int32_t *out_nodes,
                        int32_t *out_tris, hipStream_t s)
 {
-    if (cfg.persistent && MODE != TRACE_BRUTE) {
+    // cross-checks and scenes beyond pack_children have the default shape only
+    constexpr bool one_shape = MODE == TRACE_BRUTE || (MODE == TRACE_BVH && FMT == FMT_BINARY);
+    if (cfg.persistent && !one_shape) {
         switch (cfg.stack_lds) {
         case 8:
             return launch_persistent<MODE, FMT, 8>(cfg, jobs, n_jobs, queues, out_range, out_hit,
@@ -1079,9 +1443,25 @@ hipError_t launch_mode(const TraceConfig &cfg, const DevJob *jobs, int n_jobs, W
                                                     out_nodes, out_tris, s);
         }
     }
+    if constexpr (MODE == TRACE_BVH && FMT != FMT_BINARY) {
+        const int lanes = group_lanes(cfg, FMT, total);
+        const dim3 grid((unsigned)((total * lanes + 63) / 64));
+        if (lanes == 4) {
+            hipLaunchKernelGGL((k_trace_group<FMT, 4>), grid, dim3(64), 0, s, jobs, n_jobs, total,
+                               out_range, out_hit);
+            return hipGetLastError();
+        }
+        if constexpr (FMT == FMT_WIDE) {
+            if (lanes == 2) {
+                hipLaunchKernelGGL((k_trace_group<FMT, 2>), grid, dim3(64), 0, s, jobs, n_jobs,
+                                   total, out_range, out_hit);
+                return hipGetLastError();
+            }
+        }
+    }
     // one thread per ray; a dispatch holds at most 2^32 work-items, so large
     // batches go out as several dispatches of kMaxRaysPerDispatch rays
-    const int blk = cfg.group_waves == 4 ? 256 : 64;
+    const int blk = cfg.group_waves == 4 && !one_shape ? 256 : 64;
     for (int64_t g0 = 0; g0 < total; g0 += kMaxRaysPerDispatch) {
         const int64_t n = total - g0 < kMaxRaysPerDispatch ? total - g0 : kMaxRaysPerDispatch;
         const dim3 grid((unsigned)((n + blk - 1) / blk));
@@ -1093,11 +1473,14 @@ hipError_t launch_mode(const TraceConfig &cfg, const DevJob *jobs, int n_jobs, W
 #define RC_DEFER(W_, B_)                                                                     \
         hipLaunchKernelGGL((k_trace_defer<MODE, W_, B_>), grid, dim3(B_), 0, s, jobs, n_jobs,  \
                            g0, total, cfg.leaf_batch, out_range, out_hit, out_nodes, out_tris)
+        // (plain nodes one level a visit: stats, which count them, and scenes
+        // beyond pack_children)
         if (MODE == TRACE_BRUTE) RC_GRID2(0, 1, 64);
         else if (FMT == FMT_Q8 && cfg.leaf_batch > 0) {
             if (blk == 256) { if (cfg.waves_cap) RC_DEFER(8, 256); else RC_DEFER(1, 256); }
             else { if (cfg.waves_cap) RC_DEFER(8, 64); else RC_DEFER(1, 64); }
         }
+        else if (MODE == TRACE_BVH && FMT == FMT_BINARY) RC_GRID2(0, 8, 64);
         else if (cfg.stack_lds == 0 && cfg.waves_cap) RC_GRID(0, 8);
         else if (cfg.stack_lds == 0) RC_GRID(0, 1);
         else if (cfg.stack_lds == 8 && cfg.waves_cap) RC_GRID(8, 8);
@@ -1154,6 +1537,9 @@ hipError_t trace_launch(int mode, int fmt, const TraceConfig &cfg, const DevJob 
         return launch_mode<TRACE_STATS, FMT_Q8>(cfg, jobs, n_jobs, queues, total_rays, out_range,
                                                 out_hit, out_nodes, out_tris, s);
     }
+    if (mode == TRACE_BVH && cfg.pack_ok)
+        return launch_mode<TRACE_BVH, FMT_WIDE>(cfg, jobs, n_jobs, queues, total_rays, out_range,
+                                                out_hit, out_nodes, out_tris, s);
     if (mode == TRACE_BVH)
         return launch_mode<TRACE_BVH, FMT_BINARY>(cfg, jobs, n_jobs, queues, total_rays,
                                                   out_range, out_hit, out_nodes, out_tris, s);

@@ -11,7 +11,7 @@ import pytest
 
 import synth
 from gpu_util import cast_scene, compare_with_oracle, cuda, log, oracle_checked
-from paper_2509_17390_amd import Context, Job, RcastError
+from paper_2509_17390_amd import RC_NODE_FP32, RC_NODE_Q8, Context, Job, RcastError
 
 pytestmark = pytest.mark.gpu
 
@@ -711,3 +711,73 @@ def test_graph_keeps_its_scene_after_release(ctx):
         assert torch.equal(h, ref_h) and torch.equal(r.view(torch.int32), ref_r.view(torch.int32))
     g.close()
     assert ctx.device_bytes() < held           # freed with the graph
+
+
+def _deep_stack_mesh(rng):
+    """Triangles whose boxes all hold the origin while their centres refine
+    geometrically toward it in every axis (the origin is a corner of Morton
+    cell 256 of 1024): a tree with an internal sibling at each level of a long
+    path, so a ray keeps more entries than a group's LDS stack holds."""
+    tri, cell = [], 2.5
+    for octave in range(8):
+        for corner in range(1, 8):
+            for _ in range(6):
+                bits = np.array([corner >> a & 1 for a in range(3)])
+                c = (bits + rng.uniform(0.05, 0.95, 3)) * 2.0 ** octave * cell
+                e = np.stack([-np.ones(3), np.ones(3), rng.uniform(-1, 1, 3)])
+                tri.append(c + e * rng.uniform(450, 600))
+    far = [[1920.0, 1920, 1920], [1900, 1920, 1900], [1920, 1900, 1900]]
+    low = [[-640.0, -640, -640], [-620, -640, -620], [-640, -620, -620]]
+    v = np.concatenate(tri + [far, low]).astype(np.float32)
+    return v, np.arange(len(v), dtype=np.int32).reshape(-1, 3)
+
+
+@pytest.mark.parametrize("nodes", ["fp32", "q8"])
+@pytest.mark.parametrize("deep", [False, True])
+def test_lanes_per_ray_match_one_lane(ctx, nodes, deep):
+    """Rays shared by four and two lanes (small launches) against one lane a
+    ray and every triangle: sizes that leave a wave partly filled, the last
+    size of each shape and the next one, stacks that outgrow their LDS part,
+    a one-triangle and an empty scene in the same launch."""
+    import torch
+    rng = np.random.default_rng(77)
+    fmt = RC_NODE_Q8 if nodes == "q8" else RC_NODE_FP32
+    v, t = _deep_stack_mesh(rng) if deep else synth.random_soup(rng, 700, 6.0)
+    scenes = []
+    for vv, tt in ((v, t), (v[:3], np.array([[0, 1, 2]], np.int32)), (v[:3], np.zeros((0, 3), np.int32))):
+        scenes.append(ctx.upload_scene(vv, tt))
+        ctx.build(scenes[-1], node_format=fmt)
+    d = rng.normal(size=(3, 3)).astype(np.float32)
+    pat3 = ctx.upload_pattern(d, 3)
+    pat1 = ctx.upload_pattern(d[:1], 1)
+    four, two = 3 << 17, 3 << 19
+    sizes = [(11, 0), (5, 1), (21, 0), (four // 3, 0), (four // 3, 1), (two // 3, 0), (two // 3, 1)]
+    for envs, extra in sizes:
+        log(f"lanes per ray nodes={nodes} deep={deep} rays={3 * envs + extra}")
+        poses = np.zeros((envs, 12), np.float32)
+        poses[:, [0, 5, 10]] = 1
+        poses[:, [3, 7, 11]] = rng.uniform(-3, 3, (envs, 3))
+        p = cuda(poses)
+        jobs, at = [], 0
+        if envs > 9:   # a few rays of the other scenes first, so waves straddle jobs
+            for s, n in ((1, 2), (2, 1)):
+                jobs.append(Job(scenes[s], pat3, p[:n], 0.0, float("inf"), at))
+                at += 3 * n
+        jobs.append(Job(scenes[0], pat3, p[len(jobs) and 3:], 0.0, float("inf"), at))
+        at += 3 * (envs - (3 if len(jobs) > 1 else 0))
+        if extra:
+            jobs.append(Job(scenes[0], pat1, p[:1], 0.1, 40.0, at))
+        r0, h0 = ctx.cast(jobs)
+        assert r0.numel() == 3 * envs + extra
+        ctx.set_tuning(group_waves=4)
+        try:
+            r1, h1 = ctx.cast(jobs)
+        finally:
+            ctx.reset_tuning()
+        assert torch.equal(h0, h1)
+        assert torch.equal(r0.view(torch.int32), r1.view(torch.int32))
+        if envs < 1000:
+            rb, hb = ctx.cast(jobs, mode="brute")
+            assert torch.equal(h0, hb) and torch.equal(r0.view(torch.int32), rb.view(torch.int32))
+    for s in scenes:
+        ctx.release_scene(s)
