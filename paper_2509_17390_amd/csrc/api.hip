@@ -2,8 +2,9 @@
 //
 // Host-side runtime: a context per device owns scene and pattern tables, the
 // LBVH build workspace and a ring of job-table slots (pinned staging buffer
-// + device buffer + completion event), so a batch call only enqueues one
-// small host-to-device copy and one traversal launch on the caller's stream.
+// + device buffer + completion event).  A batch call of a few jobs enqueues
+// one traversal launch on the caller's stream, with the job table in the
+// kernel's arguments; a larger table goes there by one small copy.
 #include "ctx.h"
 
 #include <errno.h>
@@ -120,8 +121,33 @@ void drop_holds(rc_ctx *c, Scene *const *s, size_t n)
         if (--s[i]->refs == 0 && s[i]->dead) c->reap.push_back(s[i]);
 }
 
+namespace {
+
+// Drop the references of the flights that have finished: those at the front
+// (oldest first), or with `all` wherever they are.
+void land_flights(rc_ctx *c, bool all)
+{
+    std::lock_guard<std::mutex> lk(c->ref_mu);
+    for (size_t i = 0; i < c->flights.size();) {
+        Flight &f = c->flights[i];
+        if (hipEventQuery(f.done) != hipSuccess) {
+            (void)hipGetLastError();   // "not ready" is no error of the next launch
+            if (!all) return;
+            ++i;
+            continue;
+        }
+        for (Scene *s : f.held)
+            if (--s->refs == 0 && s->dead) c->reap.push_back(s);
+        c->flight_events.push_back(f.done);
+        c->flights.erase(c->flights.begin() + (ptrdiff_t)i);
+    }
+}
+
+}  // namespace
+
 void reap_locked(rc_ctx *c)
 {
+    if (!c->mock) land_flights(c, true);
     std::vector<Scene *> r;
     {
         std::lock_guard<std::mutex> lk(c->ref_mu);
@@ -133,20 +159,16 @@ void reap_locked(rc_ctx *c)
 
 namespace {
 
-// Host function behind a launch or build: no HIP call, no c->mu.  A pooled
-// record goes back to the pool (clear() keeps its capacity).
+// Host function behind a launch: no HIP call, no c->mu.  The record goes
+// back to the pool (clear() keeps its capacity).
 void drop_host_fn(void *arg)
 {
     DropRec *d = static_cast<DropRec *>(arg);
     rc_ctx *c = d->c;
     drop_holds(c, d->held.data(), d->held.size());
-    const int slot = d->slot;
-    if (slot < 0) delete d;
     std::lock_guard<std::mutex> lk(c->ref_mu);
-    if (slot >= 0) {
-        d->held.clear();
-        c->drop_free.push_back(slot);
-    }
+    d->held.clear();
+    c->drop_free.push_back(d->slot);
     --c->pending_drops;
     c->ref_cv.notify_all();
 }
@@ -184,10 +206,51 @@ rc_status enqueue_drop(rc_ctx *c, hipStream_t s, DropRec *d)
 rc_status drop_after(rc_ctx *c, hipStream_t s, std::vector<Scene *> &held)
 {
     if (held.empty()) return RC_OK;
-    DropRec *d = new DropRec();
-    d->c = c;
-    d->held.swap(held);
-    return enqueue_drop(c, s, d);
+    auto drop_now = [&] {
+        drop_holds(c, held.data(), held.size());
+        held.clear();
+    };
+    if (stream_capturing(s)) {
+        drop_now();
+        return RC_OK;
+    }
+    land_flights(c, false);
+    Flight f;
+    Flight oldest;
+    {
+        std::lock_guard<std::mutex> lk(c->ref_mu);
+        if (!c->flight_events.empty()) {
+            f.done = c->flight_events.back();
+            c->flight_events.pop_back();
+        }
+        if (c->flights.size() >= kMaxFlights) {
+            oldest = std::move(c->flights.front());
+            c->flights.pop_front();
+        }
+    }
+    if (oldest.done) {   // too many to keep track of: wait for one
+        (void)hipEventSynchronize(oldest.done);
+        drop_holds(c, oldest.held.data(), oldest.held.size());
+        std::lock_guard<std::mutex> lk(c->ref_mu);
+        c->flight_events.push_back(oldest.done);
+    }
+    hipError_t e = hipSuccess;
+    if (!f.done) e = hipEventCreateWithFlags(&f.done, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(f.done, s);
+    if (e != hipSuccess) {
+        // no event: wait for the stream, then drop here
+        (void)hipStreamSynchronize(s);
+        drop_now();
+        if (f.done) {
+            std::lock_guard<std::mutex> lk(c->ref_mu);
+            c->flight_events.push_back(f.done);
+        }
+        return fail(RC_E_DEVICE, "hipEventRecord failed: %s", hipGetErrorString(e));
+    }
+    f.held.swap(held);
+    std::lock_guard<std::mutex> lk(c->ref_mu);
+    c->flights.push_back(std::move(f));
+    return RC_OK;
 }
 
 Pattern *get_pattern(rc_ctx *c, int32_t id)
@@ -297,9 +360,10 @@ rc_status prepare_jobs(rc_ctx *c, const rc_tuning &tuning, const rc_job *jobs, i
     return RC_OK;
 }
 
-// Copy a job table into the next ring slot; returns the device pointer.
-size_t slot_bytes(int cap) { return sizeof(DevJob) * cap + sizeof(WorkQueues); }
+// Device and host layout of a staged table: work queues, then the jobs.
+size_t stage_bytes(int cap) { return sizeof(WorkQueues) + sizeof(DevJob) * (size_t)cap; }
 
+// Copy a job table into the next ring slot; returns the device pointers.
 rc_status stage_jobs(rc_ctx *c, const std::vector<DevJob> &dj, int64_t total, hipStream_t stream,
                      DevJob **dev, WorkQueues **queues, JobSlot **slot_out)
 {
@@ -313,24 +377,21 @@ rc_status stage_jobs(rc_ctx *c, const std::vector<DevJob> &dj, int64_t total, hi
         if (sl.host) (void)hipHostFree(sl.host);
         // c->used is guarded by c->mu (taken inside job_mu, never the other way)
         std::lock_guard<std::mutex> lk(c->mu);
-        if (sl.dev) dev_free(c, sl.dev, slot_bytes(sl.cap));
+        if (sl.dev) dev_free(c, sl.dev, stage_bytes(sl.cap));
         sl.host = nullptr;
         sl.dev = nullptr;
         sl.cap = 0;
-        HIP_TRY(hipHostMalloc((void **)&sl.host, slot_bytes(cap), hipHostMallocDefault));
-        rc_status st = dev_alloc(c, (void **)&sl.dev, slot_bytes(cap));
+        HIP_TRY(hipHostMalloc((void **)&sl.host, stage_bytes(cap), hipHostMallocDefault));
+        rc_status st = dev_alloc(c, (void **)&sl.dev, stage_bytes(cap));
         if (st != RC_OK) return st;
         sl.cap = cap;
     }
-    memcpy(sl.host, dj.data(), sizeof(DevJob) * dj.size());
-    WorkQueues *hq = reinterpret_cast<WorkQueues *>(sl.host + sl.cap);
-    init_queues(*hq, total);
-    HIP_TRY(hipMemcpyAsync(sl.dev, sl.host, sizeof(DevJob) * dj.size(), hipMemcpyHostToDevice,
+    init_queues(*reinterpret_cast<WorkQueues *>(sl.host), total);
+    memcpy(sl.host + sizeof(WorkQueues), dj.data(), sizeof(DevJob) * dj.size());
+    HIP_TRY(hipMemcpyAsync(sl.dev, sl.host, stage_bytes((int)dj.size()), hipMemcpyHostToDevice,
                            stream));
-    WorkQueues *dq = reinterpret_cast<WorkQueues *>(sl.dev + sl.cap);
-    HIP_TRY(hipMemcpyAsync(dq, hq, sizeof(WorkQueues), hipMemcpyHostToDevice, stream));
-    *dev = sl.dev;
-    *queues = dq;
+    *queues = reinterpret_cast<WorkQueues *>(sl.dev);
+    *dev = reinterpret_cast<DevJob *>(sl.dev + sizeof(WorkQueues));
     *slot_out = &sl;
     return RC_OK;
 }
@@ -355,8 +416,6 @@ TraceConfig config_of(const rc_tuning &t, const DevJob *jobs, int n_jobs)
     cfg.group_waves = t.group_waves;
     return cfg;
 }
-
-size_t stage_bytes(int cap) { return sizeof(WorkQueues) + sizeof(DevJob) * (size_t)cap; }
 
 void stage_free(rc_ctx *c, StageBuf &b)
 {
@@ -431,18 +490,22 @@ rc_status trace_common(rc_ctx *c, int mode, const rc_job *jobs, int32_t n_jobs, 
     DevJob *djd = nullptr;
     WorkQueues *dq = nullptr;
     hipError_t e = hipSuccess;
-    if (own) {
+    const TraceConfig cfg = config_of(tuning, dj.data(), n_run);
+    if (trace_takes_inline(mode, fmt, cfg, n_run)) {
+        e = trace_launch(mode, fmt, cfg, nullptr, n_run, nullptr, total, out_range, out_hit,
+                         out_nodes, out_tris, s, dj.data());
+    } else if (own) {
         st = stage_own(c, *own, dj, total, s, &djd, &dq);
         if (st != RC_OK) return st;
-        e = trace_launch(mode, fmt, config_of(tuning, dj.data(), n_run), djd, n_run, dq, total,
-                         out_range, out_hit, out_nodes, out_tris, s);
+        e = trace_launch(mode, fmt, cfg, djd, n_run, dq, total, out_range, out_hit, out_nodes,
+                         out_tris, s);
     } else {
         std::lock_guard<std::mutex> lk(c->job_mu);
         JobSlot *slot = nullptr;
         st = stage_jobs(c, dj, total, s, &djd, &dq, &slot);
         if (st != RC_OK) return st;
-        e = trace_launch(mode, fmt, config_of(tuning, dj.data(), n_run), djd, n_run, dq, total,
-                         out_range, out_hit, out_nodes, out_tris, s);
+        e = trace_launch(mode, fmt, cfg, djd, n_run, dq, total, out_range, out_hit, out_nodes,
+                         out_tris, s);
         if (e == hipSuccess) e = hipEventRecord(slot->done, s);
         if (e == hipSuccess) slot->used = true;
     }
@@ -598,10 +661,13 @@ void rc_destroy(rc_ctx *c)
     (void)hipSetDevice(c->device);
     (void)hipDeviceSynchronize();
     {
-        // every drop host function has run before the scenes go
+        // every drop host function has run before the scenes go (and the
+        // device is idle, so no flight is left in the air)
         std::unique_lock<std::mutex> lk(c->ref_mu);
         c->ref_cv.wait(lk, [&] { return c->pending_drops == 0; });
     }
+    for (Flight &f : c->flights) (void)hipEventDestroy(f.done);   // all have landed
+    for (hipEvent_t ev : c->flight_events) (void)hipEventDestroy(ev);
     for (auto &s : c->scenes)
         if (s.alive) free_scene(c, s);
     for (auto &p : c->patterns)
@@ -612,7 +678,7 @@ void rc_destroy(rc_ctx *c)
     if (c->mesh_ws) dev_free(c, c->mesh_ws, c->mesh_ws_bytes);
     for (auto &sl : c->slots) {
         if (sl.host) (void)hipHostFree(sl.host);
-        if (sl.dev) dev_free(c, sl.dev, slot_bytes(sl.cap));
+        if (sl.dev) dev_free(c, sl.dev, stage_bytes(sl.cap));
         if (sl.done) (void)hipEventDestroy(sl.done);
     }
     if (c->ws) dev_free(c, c->ws, c->ws_bytes);

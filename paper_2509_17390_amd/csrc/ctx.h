@@ -90,10 +90,10 @@ struct GaussSet {
 
 constexpr int kSlots = 8;
 
-// A slot holds one launch's job table followed by its work queues.
+// A slot holds one launch's work queues followed by its job table.
 struct JobSlot {
-    DevJob *host = nullptr;  // pinned: DevJob[cap] then WorkQueues
-    DevJob *dev = nullptr;
+    char *host = nullptr;    // pinned: WorkQueues then DevJob[cap]
+    char *dev = nullptr;
     int cap = 0;
     hipEvent_t done = nullptr;
     bool used = false;
@@ -101,9 +101,19 @@ struct JobSlot {
 
 struct ServeState;  // serve.hip
 
+// References of one launch or build, dropped once `done` (recorded on its
+// stream behind its work) has passed.  Polled, never waited for: a host
+// function on the stream would drop them at once, but stalls the stream until
+// the host has run it (about 30 us a call).
+struct Flight {
+    hipEvent_t done = nullptr;
+    std::vector<Scene *> held;
+};
+constexpr size_t kMaxFlights = 1024;
+
 // References dropped by a host function once the work enqueued before it on
-// a stream has finished.  Records with slot >= 0 belong to the context's
-// pool, preallocated for the launch entry point that allocates nothing.
+// a stream has finished: the launch entry point that allocates nothing, whose
+// records are preallocated.
 struct DropRec {
     rc_ctx *c = nullptr;
     std::vector<Scene *> held;
@@ -143,6 +153,8 @@ struct rc_ctx {
     std::mutex ref_mu;
     std::condition_variable ref_cv;
     std::vector<rc::Scene *> reap;       // dead scenes without references, freed under mu
+    std::deque<rc::Flight> flights;      // launches and builds not known to have finished
+    std::vector<hipEvent_t> flight_events;   // events of past ones, for the next
     int pending_drops = 0;               // drop host functions enqueued and not yet run
     std::vector<rc::DropRec> drop_pool;  // kDropPool records, each with room for
     std::vector<int> drop_free;          //   kNoAllocJobs scenes; indices of free ones

@@ -160,9 +160,14 @@ enum TraceMode { TRACE_BVH = 0, TRACE_BRUTE = 1, TRACE_STATS = 2 };
 // FMT_WIDE: the plain records, two levels a visit (a traversal, not a layout)
 enum NodeFormat { FMT_BINARY = 0, FMT_Q8 = 1, FMT_WIDE = 2 };
 
+// The job table is `jobs` (device memory, with `queues`), or with `inl` (host
+// memory; only where trace_takes_inline) travels in the launch's arguments.
+constexpr int kInlineJobs = 4;
+bool trace_takes_inline(int mode, int fmt, const TraceConfig &cfg, int n_jobs);
 hipError_t trace_launch(int mode, int fmt, const TraceConfig &cfg, const DevJob *jobs, int n_jobs,
                         WorkQueues *queues, int64_t total_rays, float *out_range,
-                        int32_t *out_hit, int32_t *out_nodes, int32_t *out_tris, hipStream_t s);
+                        int32_t *out_hit, int32_t *out_nodes, int32_t *out_tris, hipStream_t s,
+                        const DevJob *inl = nullptr);
 
 // Fill queue ranges for a launch of total_rays rays (host side).
 void init_queues(WorkQueues &q, int64_t total_rays);

@@ -62,6 +62,7 @@
 
 #include <float.h>
 #include <math.h>
+#include <string.h>
 
 namespace {
 
@@ -764,9 +765,25 @@ __device__ __forceinline__ void finish_ray(const LaneRay &L, float *__restrict__
 }
 
 // ---------------------------------------------------------------------------
+// The job table of a grid launch: in device memory, or (small tables) in the
+// kernel's arguments, as the first of them.  A copy to device memory in front
+// of the launch costs the stream 4 us and the host about twice that.
+struct InlineJobs {
+    DevJob j[kInlineJobs];
+};
+
+__device__ __forceinline__ const DevJob *job_table(const DevJob *table)
+{
+    // both as global addresses, so that neither is read by flat loads
+    typedef __attribute__((address_space(1))) const DevJob job_g;
+    const uint64_t args = (uint64_t)(uintptr_t)__builtin_amdgcn_kernarg_segment_ptr();
+    return (const DevJob *)(job_g *)(table ? (uint64_t)(uintptr_t)table : args);
+}
+
+// ---------------------------------------------------------------------------
 // One ray per thread (also the brute-force cross-check).
 template <int MODE, int FMT, int SS, int WAVES, int BLK>
-__global__ __launch_bounds__(BLK, WAVES) void k_trace(const DevJob *__restrict__ jobs, int n_jobs,
+__global__ __launch_bounds__(BLK, WAVES) void k_trace(InlineJobs, const DevJob *table, int n_jobs,
                                                   int64_t g0, int64_t total,
                                                   float *__restrict__ out_range,
                                                   int32_t *__restrict__ out_hit,
@@ -774,6 +791,7 @@ __global__ __launch_bounds__(BLK, WAVES) void k_trace(const DevJob *__restrict__
                                                   int32_t *__restrict__ out_tris)
 {
     __shared__ uint64_t s_stk[SS > 0 ? SS * BLK : 1];
+    const DevJob *jobs = job_table(table);
     const int64_t g = g0 + (int64_t)blockIdx.x * BLK + threadIdx.x;
     if (g >= total) return;
     LaneRay L;
@@ -1174,12 +1192,13 @@ __device__ __forceinline__ Candidates<C> fetch_candidates(const LaneRay &L, uint
 }
 
 template <int FMT, int G>
-__global__ __launch_bounds__(64, G == 4 ? 8 : 6) void k_trace_group(const DevJob *__restrict__ jobs, int n_jobs,
+__global__ __launch_bounds__(64, G == 4 ? 8 : 6) void k_trace_group(InlineJobs, const DevJob *table, int n_jobs,
                                                        int64_t total, float *__restrict__ out_range,
                                                        int32_t *__restrict__ out_hit)
 {
     constexpr int C = 4 / G, RAYS = 64 / G;
     __shared__ uint64_t s_stk[kGroupLds][RAYS];
+    const DevJob *jobs = job_table(table);
     const int lane = threadIdx.x, j = lane & (G - 1);
     const int64_t g = (int64_t)blockIdx.x * RAYS + lane / G;
     if (g >= total) return;
@@ -1426,8 +1445,11 @@ int group_lanes(const TraceConfig &cfg, int fmt, int64_t total)
 template <int MODE, int FMT>
 hipError_t launch_mode(const TraceConfig &cfg, const DevJob *jobs, int n_jobs, WorkQueues *queues,
                        int64_t total, float *out_range, int32_t *out_hit, int32_t *out_nodes,
-                       int32_t *out_tris, hipStream_t s)
+                       int32_t *out_tris, hipStream_t s, const DevJob *host_jobs)
 {
+    InlineJobs inl;
+    if (host_jobs) memcpy(inl.j, host_jobs, sizeof(DevJob) * (size_t)n_jobs);
+
     // cross-checks and scenes beyond pack_children have the default shape only
     constexpr bool one_shape = MODE == TRACE_BRUTE || (MODE == TRACE_BVH && FMT == FMT_BINARY);
     if (cfg.persistent && !one_shape) {
@@ -1447,14 +1469,14 @@ hipError_t launch_mode(const TraceConfig &cfg, const DevJob *jobs, int n_jobs, W
         const int lanes = group_lanes(cfg, FMT, total);
         const dim3 grid((unsigned)((total * lanes + 63) / 64));
         if (lanes == 4) {
-            hipLaunchKernelGGL((k_trace_group<FMT, 4>), grid, dim3(64), 0, s, jobs, n_jobs, total,
-                               out_range, out_hit);
+            hipLaunchKernelGGL((k_trace_group<FMT, 4>), grid, dim3(64), 0, s, inl, jobs, n_jobs,
+                               total, out_range, out_hit);
             return hipGetLastError();
         }
         if constexpr (FMT == FMT_WIDE) {
             if (lanes == 2) {
-                hipLaunchKernelGGL((k_trace_group<FMT, 2>), grid, dim3(64), 0, s, jobs, n_jobs,
-                                   total, out_range, out_hit);
+                hipLaunchKernelGGL((k_trace_group<FMT, 2>), grid, dim3(64), 0, s, inl, jobs,
+                                   n_jobs, total, out_range, out_hit);
                 return hipGetLastError();
             }
         }
@@ -1466,8 +1488,8 @@ hipError_t launch_mode(const TraceConfig &cfg, const DevJob *jobs, int n_jobs, W
         const int64_t n = total - g0 < kMaxRaysPerDispatch ? total - g0 : kMaxRaysPerDispatch;
         const dim3 grid((unsigned)((n + blk - 1) / blk));
 #define RC_GRID2(SS_, W_, B_)                                                                \
-        hipLaunchKernelGGL((k_trace<MODE, FMT, SS_, W_, B_>), grid, dim3(B_), 0, s, jobs,      \
-                           n_jobs, g0, total, out_range, out_hit, out_nodes, out_tris)
+        hipLaunchKernelGGL((k_trace<MODE, FMT, SS_, W_, B_>), grid, dim3(B_), 0, s, inl,       \
+                           jobs, n_jobs, g0, total, out_range, out_hit, out_nodes, out_tris)
 #define RC_GRID(SS_, W_)                                                                     \
         if (blk == 256) RC_GRID2(SS_, W_, 256); else RC_GRID2(SS_, W_, 64)
 #define RC_DEFER(W_, B_)                                                                     \
@@ -1522,27 +1544,35 @@ void init_queues(WorkQueues &q, int64_t total_rays)
     }
 }
 
+bool trace_takes_inline(int mode, int fmt, const TraceConfig &cfg, int n_jobs)
+{
+    if (n_jobs > kInlineJobs) return false;
+    if (mode == TRACE_BRUTE) return true;
+    return !cfg.persistent && !(fmt == FMT_Q8 && cfg.leaf_batch > 0);
+}
+
 hipError_t trace_launch(int mode, int fmt, const TraceConfig &cfg, const DevJob *jobs,
                         int n_jobs, WorkQueues *queues, int64_t total_rays, float *out_range,
-                        int32_t *out_hit, int32_t *out_nodes, int32_t *out_tris, hipStream_t s)
+                        int32_t *out_hit, int32_t *out_nodes, int32_t *out_tris, hipStream_t s,
+                        const DevJob *inl)
 {
     if (total_rays <= 0) return hipSuccess;
     if (mode == TRACE_BRUTE)
         return launch_mode<TRACE_BRUTE, FMT_BINARY>(cfg, jobs, n_jobs, queues, total_rays,
-                                                    out_range, out_hit, out_nodes, out_tris, s);
+                                                    out_range, out_hit, out_nodes, out_tris, s, inl);
     if (fmt == FMT_Q8) {
         if (mode == TRACE_BVH)
             return launch_mode<TRACE_BVH, FMT_Q8>(cfg, jobs, n_jobs, queues, total_rays,
-                                                  out_range, out_hit, out_nodes, out_tris, s);
+                                                  out_range, out_hit, out_nodes, out_tris, s, inl);
         return launch_mode<TRACE_STATS, FMT_Q8>(cfg, jobs, n_jobs, queues, total_rays, out_range,
-                                                out_hit, out_nodes, out_tris, s);
+                                                out_hit, out_nodes, out_tris, s, inl);
     }
     if (mode == TRACE_BVH && cfg.pack_ok)
         return launch_mode<TRACE_BVH, FMT_WIDE>(cfg, jobs, n_jobs, queues, total_rays, out_range,
-                                                out_hit, out_nodes, out_tris, s);
+                                                out_hit, out_nodes, out_tris, s, inl);
     if (mode == TRACE_BVH)
         return launch_mode<TRACE_BVH, FMT_BINARY>(cfg, jobs, n_jobs, queues, total_rays,
-                                                  out_range, out_hit, out_nodes, out_tris, s);
+                                                  out_range, out_hit, out_nodes, out_tris, s, inl);
     return launch_mode<TRACE_STATS, FMT_BINARY>(cfg, jobs, n_jobs, queues, total_rays, out_range,
-                                                out_hit, out_nodes, out_tris, s);
+                                                out_hit, out_nodes, out_tris, s, inl);
 }

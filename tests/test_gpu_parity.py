@@ -781,3 +781,49 @@ def test_lanes_per_ray_match_one_lane(ctx, nodes, deep):
             assert torch.equal(h0, hb) and torch.equal(r0.view(torch.int32), rb.view(torch.int32))
     for s in scenes:
         ctx.release_scene(s)
+
+
+def test_many_casts_in_flight_hold_their_scenes(ctx):
+    """Job tables in the launch's arguments (up to 4 jobs) and copied ones (5)
+    give the same results; a scene cast on two streams more often than
+    launches are kept track of is freed by the first call that finds them all
+    finished, and a second scene's casts in between stay intact."""
+    import torch
+    rng = np.random.default_rng(5)
+    v, t = synth.random_soup(rng, 300, 4.0)
+    a = ctx.upload_scene(v, t)
+    ctx.build(a)
+    pat = ctx.upload_pattern(synth.lidar_pattern(4, -30, 30, 32), 32)
+    poses = np.zeros((5, 12), np.float32)
+    poses[:, [0, 5, 10]] = 1
+    poses[:, [3, 7, 11]] = rng.uniform(-3, 3, (5, 3))
+    p = cuda(poses)
+    jobs = [Job(a, pat, p[k:k + 1], 0.0, 50.0, 128 * k) for k in range(5)]
+    for _ in range(8):          # every slot of the ring of copied tables
+        r5, h5 = ctx.cast(jobs)
+    r4, h4 = ctx.cast(jobs[:4])
+    assert torch.equal(h5[:512], h4) and torch.equal(r5[:512], r4)
+    torch.cuda.synchronize()
+    base = ctx.device_bytes()
+    b = ctx.upload_scene(v, t)
+    ctx.build(b)
+    job_b = [Job(b, pat, p, 0.0, 50.0)]
+    want = ctx.cast(job_b)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    rng_out = torch.empty(640, dtype=torch.float32, device="cuda")
+    hit_out = torch.empty(640, dtype=torch.int32, device="cuda")
+    other = [torch.empty_like(rng_out), torch.empty_like(hit_out)]
+    log("1200 casts on two streams")
+    for k in range(1200):
+        ctx.raycast(job_b, rng_out, hit_out, stream=streams[0])
+        if k % 7 == 0:
+            ctx.raycast(jobs, other[0], other[1], stream=streams[1])
+    ctx.release_scene(b)
+    with pytest.raises(RcastError):
+        ctx.raycast(job_b, rng_out, hit_out)
+    torch.cuda.synchronize()
+    assert ctx.device_bytes() == base
+    assert torch.equal(rng_out, want[0]) and torch.equal(hit_out, want[1])
+    assert torch.equal(other[0], r5) and torch.equal(other[1], h5)
+    ctx.release_scene(a)
