@@ -118,6 +118,25 @@ __global__ __launch_bounds__(kBlock) void k_tri_bounds(const float *__restrict__
     block_box<kBlock>(acc, partial + 6 * blockIdx.x);
 }
 
+// Boxes of points, and partial unions as above.
+__global__ __launch_bounds__(kBlock) void k_point_bounds(const float *__restrict__ p, int64_t n,
+                                                         float *__restrict__ bounds,
+                                                         float *__restrict__ partial)
+{
+    float acc[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        for (int a = 0; a < 3; ++a) {
+            const float v = p[3 * i + a];
+            bounds[6 * i + a] = v;
+            bounds[6 * i + 3 + a] = v;
+            acc[a] = fminf(acc[a], v);
+            acc[3 + a] = fmaxf(acc[3 + a], v);
+        }
+    }
+    block_box<kBlock>(acc, partial + 6 * blockIdx.x);
+}
+
 // Partial unions of ready-made primitive boxes.
 __global__ __launch_bounds__(kBlock) void k_box_union(const float *__restrict__ bounds, int64_t n,
                                                       float *__restrict__ partial)
@@ -414,7 +433,7 @@ constexpr int kTreeBlock = kChunk;
 constexpr int kGroup = 8;                       // leaves under the lowest stored heap level
 constexpr int kHeap = 2 * kChunk / kGroup;      // heap boxes stored per chunk (1..kHeap-1 used)
 constexpr int kPyramid = 8;                     // fan-in of the pyramid over chunk boxes
-constexpr int kTopChunks = 256;                 // up to here a node looks at chunk boxes one by one
+constexpr int kTopChunks = 512;                 // up to here a node looks at chunk boxes one by one
 
 constexpr uint8_t kCrosses = 0xff;              // sub_height of a node that crosses chunks
 
@@ -486,11 +505,15 @@ struct TreeArrays {
     int32_t *depth_out;
 };
 
-// TRI: leaves are triangles and their records are written in leaf order.
-template <bool TRI>
+// Leaves are triangles or points, whose records are written in leaf order,
+// or ready-made boxes.
+enum LeafKind { LEAF_TRI, LEAF_POINT, LEAF_BOX };
+
+template <int LEAF>
 __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const float *__restrict__ verts,
-                                                       const int32_t *__restrict__ tris,
-                                                       TriRec *__restrict__ trirecs)
+                                                           const int32_t *__restrict__ tris,
+                                                           TriRec *__restrict__ trirecs,
+                                                           float4 *__restrict__ points)
 {
     __shared__ float bx[6][2 * kChunk];
     __shared__ uint32_t sk[kChunk + 2];       // codes of leaves c0 - 1 .. c0 + kChunk
@@ -515,7 +538,7 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const f
             const int32_t k = c0 + j;
             sk[1 + j] = A.keys[k];
             const int64_t t = A.sorted[k];
-            if (TRI) {
+            if (LEAF == LEAF_TRI) {
                 const float *p[3];
                 for (int v = 0; v < 3; ++v) p[v] = verts + 3 * (int64_t)tris[3 * t + v];
                 float c[3][3];
@@ -531,6 +554,9 @@ __global__ __launch_bounds__(kTreeBlock) void k_tree_chunk(TreeArrays A, const f
                 r.b = make_float4(c[1][1], c[1][2], c[2][0], c[2][1]);
                 r.c = make_float4(c[2][2], __int_as_float((int32_t)t), 0.0f, 0.0f);
                 trirecs[k] = r;
+            } else if (LEAF == LEAF_POINT) {
+                for (int a = 0; a < 3; ++a) b.lo[a] = b.hi[a] = verts[3 * t + a];
+                points[k] = make_float4(b.lo[0], b.lo[1], b.lo[2], __int_as_float((int32_t)t));
             } else {
                 b = load_box(A.bounds, t);
             }
@@ -1137,7 +1163,8 @@ hipError_t sort_pass(const SortShape &sh, bool first, bool have_hist, const uint
         first, have_hist, kin, vin, kout, vout, n, shift, hist, digit_tot, sh.tiles, s);
 }
 
-hipError_t lbvh_build_any(const BuildBuffers &b, const float *prim_boxes, hipStream_t s)
+hipError_t lbvh_build_any(const BuildBuffers &b, const float *prim_boxes, float4 *out_pts,
+                          hipStream_t s)
 {
     const int64_t n = b.nt;
     if (n <= 0) return hipSuccess;
@@ -1148,6 +1175,9 @@ hipError_t lbvh_build_any(const BuildBuffers &b, const float *prim_boxes, hipStr
     if (prim_boxes)
         hipLaunchKernelGGL(k_box_union, dim3((unsigned)bgrid), dim3(kBlock), 0, s, prim_boxes, n,
                            w.partial);
+    else if (out_pts)
+        hipLaunchKernelGGL(k_point_bounds, dim3((unsigned)bgrid), dim3(kBlock), 0, s, b.verts, n,
+                           w.bounds, w.partial);
     else
         hipLaunchKernelGGL(k_tri_bounds, dim3((unsigned)bgrid), dim3(kBlock), 0, s, b.verts, b.tris,
                            n, w.bounds, w.partial);
@@ -1191,12 +1221,15 @@ hipError_t lbvh_build_any(const BuildBuffers &b, const float *prim_boxes, hipStr
     A.span = w.span;
     A.span_count = w.span_count;
     A.depth_out = b.depth_out;
-    if (b.trirecs)
-        hipLaunchKernelGGL(k_tree_chunk<true>, dim3((unsigned)m), dim3(kTreeBlock), 0, s, A, b.verts,
-                           b.tris, b.trirecs);
+    if (out_pts)
+        hipLaunchKernelGGL(k_tree_chunk<LEAF_POINT>, dim3((unsigned)m), dim3(kTreeBlock), 0, s, A,
+                           b.verts, nullptr, nullptr, out_pts);
+    else if (b.trirecs)
+        hipLaunchKernelGGL(k_tree_chunk<LEAF_TRI>, dim3((unsigned)m), dim3(kTreeBlock), 0, s, A,
+                           b.verts, b.tris, b.trirecs, nullptr);
     else
-        hipLaunchKernelGGL(k_tree_chunk<false>, dim3((unsigned)m), dim3(kTreeBlock), 0, s, A, nullptr,
-                           nullptr, nullptr);
+        hipLaunchKernelGGL(k_tree_chunk<LEAF_BOX>, dim3((unsigned)m), dim3(kTreeBlock), 0, s, A,
+                           nullptr, nullptr, nullptr, nullptr);
     if (m > 1) {
         if (m > kTopChunks) hipLaunchKernelGGL(k_tree_pyramid, dim3(1), dim3(kTopBlock), 0, s, A, m);
         // about 10 crossing nodes a chunk
@@ -1219,13 +1252,19 @@ hipError_t lbvh_build_any(const BuildBuffers &b, const float *prim_boxes, hipStr
 
 hipError_t lbvh_build_launch(const BuildBuffers &b, hipStream_t s)
 {
-    return lbvh_build_any(b, nullptr, s);
+    return lbvh_build_any(b, nullptr, nullptr, s);
+}
+
+hipError_t lbvh_build_points_launch(const BuildBuffers &b, float4 *out_pts, hipStream_t s)
+{
+    if (b.trirecs || !out_pts) return hipErrorInvalidValue;
+    return lbvh_build_any(b, nullptr, out_pts, s);
 }
 
 hipError_t lbvh_build_boxes_launch(const BuildBuffers &b, const float *boxes, hipStream_t s)
 {
     if (b.trirecs) return hipErrorInvalidValue;
-    return lbvh_build_any(b, boxes, s);
+    return lbvh_build_any(b, boxes, nullptr, s);
 }
 
 size_t radix_sort_ws_bytes(int64_t n)

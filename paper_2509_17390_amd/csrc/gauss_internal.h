@@ -49,6 +49,10 @@ constexpr int kVoxTile = 8;   // tile edge in voxels
 // be null (build.hip).
 hipError_t lbvh_build_boxes_launch(const BuildBuffers &b, const float *boxes, hipStream_t s);
 
+// LBVH over points (b.verts, [nt][3]; b.tris is ignored, b.trirecs must be
+// null); out_pts receives the points in leaf order as (x, y, z, index).
+hipError_t lbvh_build_points_launch(const BuildBuffers &b, float4 *out_pts, hipStream_t s);
+
 // Interleave the uploaded arrays into the 48-byte layout.
 hipError_t gauss_pack_launch(const GaussArrays &a, float4 *out, hipStream_t s);
 // Validation of an uploaded set: flags[0] |= 1 non-finite value, 2 scale

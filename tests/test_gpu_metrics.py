@@ -63,6 +63,47 @@ def test_ties_go_to_the_lowest_index(ctx):
         assert i[k] == np.nonzero(dd == m)[0].min()
 
 
+@pytest.mark.parametrize("spread", ["clustered", "line", "huge", "tiny", "nonfinite"])
+@pytest.mark.parametrize("many", [False, True])
+def test_nearest_equals_every_pair_in_fp64(ctx, spread, many):
+    """Both search shapes (four lanes a query, and one lane beyond 262,144
+    queries) bit for bit against all pairs in FP64: duplicates and ties, deep
+    trees (points refining toward a corner), float32 squares that overflow or
+    vanish, infinite and NaN coordinates."""
+    rng = np.random.default_rng(len(spread))
+    n_ref, n_q = 700, 301
+    ref = rng.uniform(-1, 1, (n_ref, 3))
+    if spread == "clustered":
+        ref[::3] = ref[1]
+    elif spread == "line":
+        ref = np.abs(ref) * 2.0 ** -rng.integers(0, 10, (n_ref, 1))
+    elif spread == "huge":
+        ref *= 3e37 ** rng.uniform(0, 1, (n_ref, 1))
+    elif spread == "tiny":
+        ref *= 1e-25
+    q = ref[rng.integers(0, n_ref, n_q)] * rng.choice([1.0, 1.0, 1.01, 0.5], (n_q, 1))
+    ref, q = ref.astype(np.float32), q.astype(np.float32)
+    if spread == "nonfinite":
+        ref[5] = (np.inf, 0, 0)
+        ref[6] = (np.nan, 0, 0)
+        ref[7] = -np.inf
+        q[0] = (np.inf, 1, 1)
+        q[1] = (np.nan, 0, 0)
+        q[2] = -np.inf
+    log(f"nearest {spread} many={many}")
+    reps = 262145 // n_q + 1 if many else 1
+    d, i = gpu_nearest(ctx, ref, np.tile(q, (reps, 1)))
+    with np.errstate(invalid="ignore", over="ignore"):
+        g = ref.astype(np.float64)[None] - q.astype(np.float64)[:, None]
+        d2 = (g[..., 0] ** 2 + g[..., 1] ** 2) + g[..., 2] ** 2
+    wins = np.where(np.isnan(d2), np.inf, d2)
+    want = wins.min(axis=1)
+    first = np.where((d2 == want[:, None]).any(axis=1), np.argmax(d2 == want[:, None], axis=1),
+                     0x7fffffff)
+    assert np.array_equal(d.reshape(reps, n_q), np.tile(np.sqrt(want), (reps, 1)))
+    assert np.array_equal(i.reshape(reps, n_q), np.tile(first, (reps, 1)))
+
+
 def test_empty_reference(ctx):
     d, i = gpu_nearest(ctx, np.zeros((0, 3), np.float32),
                        np.ones((5, 3), np.float32))
