@@ -76,20 +76,30 @@ hipError_t tsdf_shells_phi_launch(const uint8_t *vt, const uint64_t *O, uint8_t 
                                   const TsdfGrid &g, int shells, float h, float r, hipStream_t s);
 
 // Marching cubes: the case table (count[256], tri[256][15] edge ids, -1
-// padded), the count pass (edge masks and cell cases, one byte each per
-// point; voff: each point's vertex offset within its scan tile (u16); vsums /
-// tsums: exclusive scans of the tiles' vertex and triangle totals, with
-// mc_scan_sums_len(n) entries, the grand total last), and the emit pass
-// (normals: float32 [nv][3] or null).
+// padded), the count pass into the buffers below, and the emit pass (normals:
+// float32 [nv][3] or null).
 void mc_table_copy(uint8_t *count, int8_t *tri);
-int64_t mc_scan_sums_len(int64_t n);
+int64_t mc_words(int64_t n);        // words of 64 points
+int64_t mc_blocks(int64_t n);       // count blocks
+size_t mc_word_bytes();
+struct McBuffers {
+    uint64_t *inside;               // [mc_words] phi < iso
+    void *words;                    // [mc_words] x mc_word_bytes: crossed edges, offsets
+    uint64_t *cells;                // [mc_words] active cells
+    uint8_t *list, *group;          // [256 mc_blocks] each block's words that have any, and
+                                    // the places in the list where its groups begin
+    uint32_t *nlist;                // [mc_blocks] listed words
+    uint32_t *vsums, *tsums, *gsums;   // [mc_blocks] scans of the blocks' vertices, triangles
+                                       // and groups
+    uint32_t *totals;               // [3] vertices, triangles, groups
+};
 hipError_t mc_count_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
-                           uint8_t *mask, uint8_t *cases, uint16_t *voff, uint32_t *vsums,
-                           uint32_t *tsums, hipStream_t s);
+                           const McBuffers &b, hipStream_t s);
 hipError_t mc_emit_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
-                          const int8_t *tris_of, const uint8_t *mask, const uint8_t *cases,
-                          const uint16_t *voff, const uint32_t *vsums, const uint32_t *tsums,
+                          const int8_t *tris_of, const McBuffers &b, uint32_t ngroups,
                           float *verts, int32_t *tris, float *normals, hipStream_t s);
+// Entries of the sums array of scan_u32_launch.
+int64_t mc_scan_sums_len(int64_t n);
 
 // ---------------------------------------------------------------------------
 // Nearest neighbours and fidelity metrics (nn.hip).

@@ -1003,71 +1003,195 @@ __global__ __launch_bounds__(kBlock) void k_phi(const uint8_t *__restrict__ p,
     }
 }
 
-// ---- marching cubes --------------------------------------------------------
-// Count pass, per lattice point: mask of crossed edges +x/+y/+z (bits 0..2)
-// and the case of the cell it anchors (bit k set when corner k = (k & 1,
-// k >> 1 & 1, k >> 2 & 1) is inside, phi < iso), one byte each; the vertex
-// and triangle counts follow from them.
-// Over 64 x 4 x 4 tiles: a block loads the inside bits of its tile plus
-// one point further along each axis into LDS (each phi read once per tile,
-// about 1.6x over the grid), then each thread takes four consecutive
-// points of a row from LDS.  Points whose +x, +y or +z
-// neighbour lies outside the grid never use it (the coordinate tests), so
-// those LDS bytes are only placeholders.
-constexpr int kMcTX = 64, kMcTY = 4, kMcTZ = 4;
-
-__global__ __launch_bounds__(kBlock) void k_mc_count_tile(const float *__restrict__ phi,
-                                                          TsdfGrid g, float iso,
-                                                          uint8_t *__restrict__ mask,
-                                                          uint8_t *__restrict__ cases)
+__device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *total)
 {
-    constexpr int LX = kMcTX + 1, LY = kMcTY + 1, LZ = kMcTZ + 1, NL = LX * LY * LZ;
-    static_assert((kMcTX / 4) * kMcTY * kMcTZ == kBlock, "four points per thread");
-    __shared__ uint8_t ins[NL];
-    const int bx = (int)blockIdx.x * kMcTX, by = (int)blockIdx.y * kMcTY;
-    const int bz = (int)blockIdx.z * kMcTZ;
-    constexpr int PER = (NL + kBlock - 1) / kBlock;
-    uint8_t v[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int q = (int)threadIdx.x + k * kBlock;
-        const int lx = q % LX, t = q / LX, ly = t % LY, lz = t / LY;
-        const int gx = bx + lx, gy = by + ly, gz = bz + lz;
-        // points outside the grid read point 0 and count as outside: no
-        // branch between the loads, so all PER are in flight at once
-        const bool ok = q < NL && gx < g.nx && gy < g.ny && gz < g.nz;
-        const float f = phi[ok ? ((int64_t)gz * g.ny + gy) * g.nx + gx : 0];
-        v[k] = ok && f < iso ? 1 : 0;
+    __shared__ uint32_t ws[kBlock / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
     }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int q = (int)threadIdx.x + k * kBlock;
-        if (q < NL) ins[q] = v[k];
+    if (lane == 63) ws[w] = x;
+    __syncthreads();
+    uint32_t off = 0, tot = 0;
+    for (int k = 0; k < kBlock / 64; ++k) {
+        if (k < w) off += ws[k];
+        tot += ws[k];
     }
     __syncthreads();
-    const int lx0 = ((int)threadIdx.x % (kMcTX / 4)) * 4;
-    const int t = (int)threadIdx.x / (kMcTX / 4), ly = t % kMcTY, lz = t / kMcTY;
-    const int gy = by + ly, gz = bz + lz;
-    if (gy >= g.ny || gz >= g.nz) return;
-    const int64_t row = ((int64_t)gz * g.ny + gy) * g.nx;
-    for (int j = 0; j < 4; ++j) {
-        const int lx = lx0 + j, gx = bx + lx;
-        if (gx >= g.nx) break;
-        const uint8_t *c = ins + (lz * LY + ly) * LX + lx;
-        const int in = c[0];
-        int m = 0;
-        if (gx < g.nx - 1 && c[1] != in) m |= 1;
-        if (gy < g.ny - 1 && c[LX] != in) m |= 2;
-        if (gz < g.nz - 1 && c[LX * LY] != in) m |= 4;
-        int cs = 0;
-        if (gx < g.nx - 1 && gy < g.ny - 1 && gz < g.nz - 1) {
-            // corner k = (k & 1, k >> 1 & 1, k >> 2 & 1)
+    *total = tot;
+    return off + x - v;
+}
+
+// ---- marching cubes --------------------------------------------------------
+// Inside bits (phi < iso) packed 64 lattice points a word, in point order:
+// word w holds points 64 w .. 64 w + 63, whatever rows they lie in.  A
+// point's neighbours are then fixed bit offsets away (1, nx, nx ny), and
+// crossed edges and active cells are word operations: the passes over the
+// grid read phi once and a bit a point afterwards.  (One mask byte, one case
+// byte and one 16-bit vertex offset a point, written, scanned and read again,
+// took 137 + 35 + 26 us and 142 us in the emission on 34.2M points with 1.7M
+// vertices; these take 26 + 21 + 8 us, the first at the rate of a copy, and
+// 104 us.)
+struct __align__(16) McWord {
+    uint64_t e[3];    // points whose +x / +y / +z edge is crossed
+    uint32_t v, t;    // vertices and triangles of the block's earlier words
+};
+constexpr int kMcWords = 256;   // words of a count block
+constexpr uint32_t kMcGroup = 64, kMcMinWeight = 8;   // a group's weight and a word's least
+
+// one wave a word: coalesced reads, a ballot packs; kMcInsideRun words a
+// wave keep as many reads in flight
+constexpr int kMcInsideRun = 8;
+
+__global__ __launch_bounds__(kBlock) void k_mc_inside(const float *__restrict__ phi, int64_t n,
+                                                      float iso, uint64_t *__restrict__ inside)
+{
+    const int lane = (int)(threadIdx.x & 63);
+    const int64_t w0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * kMcInsideRun;
+    float f[kMcInsideRun];
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                cs |= (int)c[(k & 1) + ((k >> 1) & 1) * LX + ((k >> 2) & 1) * LX * LY] << k;
+    for (int k = 0; k < kMcInsideRun; ++k) {
+        const int64_t i = 64 * (w0 + k) + lane;
+        f[k] = phi[i < n ? i : 0];
+    }
+#pragma unroll
+    for (int k = 0; k < kMcInsideRun; ++k) {
+        const int64_t i = 64 * (w0 + k) + lane;
+        const uint64_t m = __ballot(i < n && f[k] < iso);
+        if (lane == 0 && 64 * (w0 + k) < n) inside[w0 + k] = m;
+    }
+}
+
+// inside bits of the points `off` beyond word w's (u), and one further (v)
+__device__ __forceinline__ void corner_words(const uint64_t *__restrict__ inside, int64_t nw,
+                                             int64_t w, int64_t off, uint64_t &u, uint64_t &v)
+{
+    const int64_t q = w + (off >> 6);
+    const int sh = (int)(off & 63);
+    const uint64_t lo = q < nw ? inside[q] : 0ull, hi = q + 1 < nw ? inside[q + 1] : 0ull;
+    u = sh ? (lo >> sh) | (hi << (64 - sh)) : lo;
+    v = (u >> 1) | (((hi >> sh) & 1ull) << 63);
+}
+
+// Points of word w that have a +x, +y, +z neighbour in the grid.
+__device__ __forceinline__ void neighbour_masks(int64_t w, const TsdfGrid &g, uint64_t &mx,
+                                                uint64_t &my, uint64_t &mz)
+{
+    const int64_t i0 = 64 * w, sxy = (int64_t)g.nx * g.ny;
+    auto below = [&](int64_t end) -> uint64_t {   // points i < end
+        const int64_t k = end - i0;
+        return k <= 0 ? 0ull : (k >= 64 ? ~0ull : (1ull << k) - 1ull);
+    };
+    const uint64_t valid = below(g.n);
+    mz = below(g.n - sxy) & valid;
+    mx = valid;
+    my = valid;
+    int x, y, z;
+    coords(i0, g, x, y, z);
+    // row by row: the last point has no +x, the last row no +y
+    for (int64_t start = i0 - x; start < i0 + 64; start += g.nx) {
+        mx &= ~(below(start + g.nx) & ~below(start + g.nx - 1));
+        if (y == g.ny - 1) my &= ~(below(start + g.nx) & ~below(start));
+        y = y == g.ny - 1 ? 0 : y + 1;
+    }
+}
+
+// Per word: its crossed edges and active cells, its vertices and triangles,
+// and their offsets within the block of kMcWords words; the block's totals;
+// the block's list of the words that have any.  Only listed words are written.
+//
+// The list falls into groups of words for the emission's waves: about 64
+// vertices, at most 8 words.  (Surfaces that follow x have 64 vertices in a
+// word, others 1 to 3: waves of 8 words each had from 10 to 1,500 items, and
+// the last layers' waves ran long after the others, 136 us.)  A word weighs its
+// vertices, but 8 to 64, and belongs to group [weight of the words before it
+// / 64]: no group is empty.
+__global__ __launch_bounds__(kMcWords) void k_mc_count(const uint64_t *__restrict__ inside,
+                                                       TsdfGrid g, int64_t nw,
+                                                       const uint8_t *__restrict__ ntri,
+                                                       McWord *__restrict__ words,
+                                                       uint64_t *__restrict__ cells,
+                                                       uint8_t *__restrict__ list,
+                                                       uint8_t *__restrict__ group,
+                                                       uint32_t *__restrict__ nlist,
+                                                       uint32_t *__restrict__ vsums,
+                                                       uint32_t *__restrict__ tsums,
+                                                       uint32_t *__restrict__ gsums)
+{
+    static_assert(kMcWords == kBlock, "the block scan's size, and a byte names a word");
+    static_assert(kMcGroup * kMcWords < (1 << 15) && 5 * 64 * kMcWords < (1 << 17), "shared scan");
+    __shared__ uint8_t nt_lds[256];
+    nt_lds[threadIdx.x] = ntri[threadIdx.x];
+    __syncthreads();
+    const int64_t w = (int64_t)blockIdx.x * kMcWords + threadIdx.x;
+    McWord m;
+    m.e[0] = m.e[1] = m.e[2] = 0;
+    uint64_t cell = 0;
+    uint32_t nv = 0, nt = 0;
+    if (w < nw) {
+        uint64_t c[8], mx, my, mz;   // corner k = (k & 1, k >> 1 & 1, k >> 2 & 1)
+        const int64_t sxy = (int64_t)g.nx * g.ny;
+        corner_words(inside, nw, w, 0, c[0], c[1]);
+        corner_words(inside, nw, w, g.nx, c[2], c[3]);
+        corner_words(inside, nw, w, sxy, c[4], c[5]);
+        corner_words(inside, nw, w, sxy + g.nx, c[6], c[7]);
+        uint64_t any = c[0], all = c[0];
+#pragma unroll
+        for (int k = 1; k < 8; ++k) {
+            any |= c[k];
+            all &= c[k];
         }
-        mask[row + gx] = (uint8_t)m;
-        cases[row + gx] = (uint8_t)cs;
+        cell = any & ~all;
+        if (cell) {                  // most words lie inside or outside
+            neighbour_masks(w, g, mx, my, mz);
+            m.e[0] = (c[0] ^ c[1]) & mx;
+            m.e[1] = (c[0] ^ c[2]) & my;
+            m.e[2] = (c[0] ^ c[4]) & mz;
+            cell &= mx & my & mz;
+            nv = (uint32_t)(__popcll(m.e[0]) + __popcll(m.e[1]) + __popcll(m.e[2]));
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                uint32_t todo = (uint32_t)(cell >> (32 * half));
+                while (todo) {
+                    const int b = __builtin_ctz(todo);
+                    todo &= todo - 1;
+                    uint32_t cs = 0;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k)
+                        cs |= (((uint32_t)(c[k] >> (32 * half)) >> b) & 1u) << k;
+                    nt += nt_lds[cs];
+                }
+            }
+        }
+    }
+    // vertices (at most 3 x 64 x 256 = 49,152 a block) and listed words
+    // (at most 256) share a scan, triangles (81,920) and weights (16,384) one
+    const uint32_t busy = nv + nt ? 1u : 0u;
+    const uint32_t wt = !busy ? 0u : nv < kMcMinWeight ? kMcMinWeight : nv > kMcGroup ? kMcGroup : nv;
+    uint32_t tv, tt;
+    const uint32_t rv = block_scan_excl(nv | (busy << 16), &tv);
+    const uint32_t rt = block_scan_excl(nt | (wt << 17), &tt);
+    m.v = rv & 0xffffu;
+    m.t = rt & 0x1ffffu;
+    const uint32_t gi = (rt >> 17) / kMcGroup, li = rv >> 16;
+    __shared__ uint16_t group_of[kMcWords];
+    if (busy) {
+        words[w] = m;
+        cells[w] = cell;
+        list[(int64_t)blockIdx.x * kMcWords + li] = (uint8_t)threadIdx.x;
+        group_of[li] = (uint16_t)gi;
+    }
+    __syncthreads();
+    if (busy && (li == 0 || group_of[li - 1] != gi))
+        group[(int64_t)blockIdx.x * kMcWords + gi] = (uint8_t)li;      // its first word
+    if (threadIdx.x == 0) {
+        const uint32_t n = tv >> 16;
+        vsums[blockIdx.x] = tv & 0xffffu;
+        nlist[blockIdx.x] = n;
+        tsums[blockIdx.x] = tt & 0x1ffffu;
+        gsums[blockIdx.x] = n ? group_of[n - 1] + 1u : 0u;
     }
 }
 
@@ -1109,17 +1233,68 @@ __device__ __forceinline__ void mc_emit_vertex(const float *__restrict__ phi, co
     const float c2 = (float)(g.o[2] + ((double)z + 0.5) * g.h);
     const int64_t sx = g.nx, sxy = (int64_t)g.nx * g.ny;
     const int64_t step = a == 0 ? 1 : (a == 1 ? sx : sxy);
-    const float fa = phi[i], fb = phi[i + step];
+    float fa, fb;
     // gradient reads at both ends of the edge, issued before any is used
     const int xb = x + (a == 0), yb = y + (a == 1), zb = z + (a == 2);
     float r[12];
-    if (normals) {
+    if (normals && x > 0 && x + 2 < g.nx) {
+        // neighbours along x come with the same read (a lane's read costs a
+        // cache lookup of its own wherever vertices are not x neighbours):
+        // 5 or 8 reads for the 14 values
+        const int64_t q = a == 0 ? i : i + step;
+        float A[4], B[4], R[6][2];
+        __builtin_memcpy(A, phi + i - 1, sizeof A);
+        __builtin_memcpy(B, phi + q - 1, sizeof B);
+        const int64_t yp = y < g.ny - 1 ? sx : 0, ym = y > 0 ? sx : 0;
+        const int64_t zp = z < g.nz - 1 ? sxy : 0, zm = z > 0 ? sxy : 0;
+        // x: i + y, i - y, i + z, i - z, both ends at once.  y (z): i - y,
+        // then q + y, then +z and -z (y) at both ends; i + y is q
+        const bool ez = a == 2;
+        const int64_t qp = ez ? (zb < g.nz - 1 ? sxy : 0) : (yb < g.ny - 1 ? sx : 0);
+        const int64_t om = ez ? zm : ym, sp = ez ? yp : zp, sm = ez ? ym : zm;
+        __builtin_memcpy(R[0], phi + (a == 0 ? i + yp : q + qp), sizeof R[0]);
+        __builtin_memcpy(R[1], phi + (a == 0 ? i - ym : i - om), sizeof R[1]);
+        __builtin_memcpy(R[2], phi + (a == 0 ? i + zp : i + sp), sizeof R[2]);
+        __builtin_memcpy(R[3], phi + (a == 0 ? i - zm : i - sm), sizeof R[3]);
+        if (a != 0) {
+            __builtin_memcpy(R[4], phi + q + sp, sizeof R[4]);
+            __builtin_memcpy(R[5], phi + q - sm, sizeof R[5]);
+        }
+        fa = A[1];
+        fb = a == 0 ? A[2] : B[1];
+        r[0] = A[2];
+        r[1] = A[0];
+        r[6] = a == 0 ? A[3] : B[2];
+        r[7] = a == 0 ? A[1] : B[0];
+        if (a == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                r[2 + k] = R[k][0];
+                r[8 + k] = R[k][1];
+            }
+        } else {
+            const float ap = fb, am = R[1][0], bp = R[0][0], bm = fa;   // along the edge
+            r[2] = ez ? R[2][0] : ap;
+            r[3] = ez ? R[3][0] : am;
+            r[4] = ez ? ap : R[2][0];
+            r[5] = ez ? am : R[3][0];
+            r[8] = ez ? R[4][0] : bp;
+            r[9] = ez ? R[5][0] : bm;
+            r[10] = ez ? bp : R[4][0];
+            r[11] = ez ? bm : R[5][0];
+        }
+    } else if (normals) {
+        fa = phi[i];
+        fb = phi[i + step];
         lattice_reads(phi, i, x, g.nx, 1, r[0], r[1]);
         lattice_reads(phi, i, y, g.ny, sx, r[2], r[3]);
         lattice_reads(phi, i, z, g.nz, sxy, r[4], r[5]);
         lattice_reads(phi, i + step, xb, g.nx, 1, r[6], r[7]);
         lattice_reads(phi, i + step, yb, g.ny, sx, r[8], r[9]);
         lattice_reads(phi, i + step, zb, g.nz, sxy, r[10], r[11]);
+    } else {
+        fa = phi[i];
+        fb = phi[i + step];
     }
     const float t = __fdiv_rn(iso - fa, fb - fa);
     const float pa = __fadd_rn(a == 0 ? c0 : (a == 1 ? c1 : c2), __fmul_rn(t, g.hf));
@@ -1149,18 +1324,27 @@ __device__ __forceinline__ void mc_emit_vertex(const float *__restrict__ phi, co
     }
 }
 
-// Triangle k of the cell at lattice point i (case cs), into slot t: its
-// corners are the vertices of the cell edges the case table names; a point
-// q's first vertex is voff[q] (its offset within its scan tile) +
-// vbase[q / kScanTile], and its edges' vertices follow in axis order.
-__device__ __forceinline__ void mc_emit_tri(const TsdfGrid &g, const int8_t *__restrict__ tris_of,
-                                            const uint8_t *__restrict__ mask,
-                                            const uint16_t *__restrict__ voff,
-                                            const uint32_t *__restrict__ vbase,
-                                            int32_t *__restrict__ tris, int64_t i, int cs, int k,
+// What the triangles of a word's cells need of the words their corners lie
+// in: the words at the four offsets of corner_words, two each, kept in LDS
+// (read from memory per triangle corner, scattered, they took most of the
+// cache's lookups).
+struct McCorner {
+    uint64_t e[3];
+    uint32_t id;         // first vertex
+};
+
+// Triangle k of the cell at bit b of a word (case cs), into slot t: its
+// corners are the vertices of the cell edges the case table names.  The
+// vertex on edge `axis` of a point follows those of its word's earlier points
+// and of its own earlier axes.
+__device__ __forceinline__ void mc_emit_tri(const int8_t *__restrict__ tris_of,
+                                            const McCorner *__restrict__ corners,
+                                            const uint32_t off_bits[4],
+                                            int32_t *__restrict__ tris, uint32_t b, int cs, int k,
                                             uint32_t t)
 {
-    const int64_t sx = g.nx, sxy = (int64_t)g.nx * g.ny;
+    int32_t id[3];
+#pragma unroll
     for (int e = 0; e < 3; ++e) {
         const int edge = tris_of[cs * 15 + 3 * k + e];
         // edges are numbered (axis, lower corner): 4 per axis
@@ -1168,115 +1352,199 @@ __device__ __forceinline__ void mc_emit_tri(const TsdfGrid &g, const int8_t *__r
         // the nth corner (ascending) whose bit `axis` is clear
         const int lo = nth & ((1 << axis) - 1);
         const int corner = ((nth >> axis) << (axis + 1)) | lo;
-        const int64_t q = i + ((corner & 1) ? 1 : 0) + ((corner & 2) ? sx : 0) +
-                          ((corner & 4) ? sxy : 0);
-        const int mq = mask[q];
-        const uint32_t id = (uint32_t)voff[q] + vbase[q / kScanTile] +
-                            (uint32_t)__popc(mq & ((1 << axis) - 1));
-        tris[3 * (int64_t)t + e] = (int32_t)id;
+        const int o = corner >> 1;
+        const uint32_t ob = o == 0 ? off_bits[0] : o == 1 ? off_bits[1] : o == 2 ? off_bits[2]
+                                                                                 : off_bits[3];
+        const uint32_t at = ob + b + (uint32_t)(corner & 1);   // at most 63 + 63 + 1
+        const McCorner &m = corners[2 * o + (int)(at >> 6)];
+        const uint64_t bit = 1ull << (at & 63u);
+        // edges before (point, axis): all of earlier points, the point's of
+        // lower axes
+        const uint64_t m0 = axis > 0 ? (bit << 1) - 1ull : bit - 1ull;
+        const uint64_t m1 = axis > 1 ? (bit << 1) - 1ull : bit - 1ull;
+        id[e] = (int32_t)(m.id + (uint32_t)(__popcll(m.e[0] & m0) + __popcll(m.e[1] & m1) +
+                                            __popcll(m.e[2] & (bit - 1ull))));
     }
+    __builtin_memcpy(tris + 3 * (int64_t)t, id, sizeof id);
 }
 
-__device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *total)
+// One wave per group of listed words.  Their points need different amounts of
+// work (0 to 3 vertices, 0 to 5 triangles), so the wave lists its vertices, its
+// active cells, and the triangles of 64 cells at a time as items in LDS, and
+// each lane emits one item at a time: every lane runs the same code on every
+// item, and no wave waits for another.  Bound by VALU issue and by the chain
+// of a wave's reads: 104 us on 1.7M vertices and 3.4M triangles (142 us with
+// blocks of 1,024 points).
+constexpr int kMcEmitWords = (int)(kMcGroup / kMcMinWeight), kMcEmitWaves = kBlock / 64;
+constexpr int kMcSlice = kMcEmitWords;                                    // points of a lane
+
+__device__ __forceinline__ uint32_t wave_scan_excl(uint32_t v, int lane, uint32_t &tot)
 {
-    __shared__ uint32_t ws[kBlock / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t x = v;
+    uint32_t r = v;
+#pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
+        const uint32_t y = __shfl_up(r, o, 64);
+        if (lane >= o) r += y;
     }
-    if (lane == 63) ws[w] = x;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (int k = 0; k < kBlock / 64; ++k) {
-        if (k < w) off += ws[k];
-        tot += ws[k];
-    }
-    __syncthreads();
-    *total = tot;
-    return off + x - v;
+    tot = __shfl(r, 63, 64);
+    return r - v;
 }
 
-// One block per scan tile.  Points with a vertex or a triangle are a small
-// share of the grid and need different amounts of work (0 to 3 vertices, 0
-// to 5 triangles), so the block lists the tile's vertices, then its
-// triangles, as items in LDS, in slot order (the slots come from an
-// in-block scan of the per-point counts, the same offsets the count pass
-// stored), and each thread emits one item at a time: every lane runs the
-// same code on every item.
+// LDS written by this wave is read by it next
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 __global__ __launch_bounds__(kBlock) void k_mc_emit(const float *__restrict__ phi, TsdfGrid g,
-                                                    float iso, const uint8_t *__restrict__ ntri,
+                                                    float iso, int64_t nw, uint32_t nb,
+                                                    uint32_t ngroups,
+                                                    const uint8_t *__restrict__ ntri,
                                                     const int8_t *__restrict__ tris_of,
-                                                    const uint8_t *__restrict__ mask,
-                                                    const uint8_t *__restrict__ cases,
-                                                    const uint16_t *__restrict__ voff,
+                                                    const uint64_t *__restrict__ inside,
+                                                    const McWord *__restrict__ words,
+                                                    const uint64_t *__restrict__ cells,
+                                                    const uint8_t *__restrict__ list,
+                                                    const uint8_t *__restrict__ group,
+                                                    const uint32_t *__restrict__ nlist,
                                                     const uint32_t *__restrict__ vbase,
                                                     const uint32_t *__restrict__ tbase,
+                                                    const uint32_t *__restrict__ gbase,
                                                     float *__restrict__ verts,
                                                     int32_t *__restrict__ tris,
                                                     float *__restrict__ normals)
 {
-    static_assert(kScanItems == 4, "one word of mask and case bytes per thread");
-    static_assert(kScanTile == 1024, "item packing: point in tile in bits 0..9");
+    constexpr int WL = 64 / kMcEmitWords;         // lanes of a word
+    constexpr int PTS = 64 * kMcEmitWords;        // points of a wave
+    static_assert(WL == 8 && WL * kMcSlice == 64, "a lane a corner word");
+    static_assert(PTS <= 1024, "point in bits 0..9 of an item");
+    // vertex items (point | axis << 10), then cell items (point)
+    __shared__ uint16_t s_item[kMcEmitWaves][3 * PTS];
+    __shared__ uint16_t s_tri[kMcEmitWaves][5 * 64];         // lane of the cell | k << 6
+    __shared__ uint32_t s_cell[kMcEmitWaves][64];            // point | case << 10
+    __shared__ uint64_t s_c[kMcEmitWaves][kMcEmitWords][8];  // corners of the words
+    __shared__ McCorner s_k[kMcEmitWaves][kMcEmitWords][8];
+    // a word's first lattice point, its first vertex's and triangle's slots
+    // less their items' places, its first cell's place
+    __shared__ int64_t s_base[kMcEmitWaves][kMcEmitWords];
+    __shared__ uint32_t s_v[kMcEmitWaves][kMcEmitWords], s_t[kMcEmitWaves][kMcEmitWords];
     __shared__ uint8_t nt_lds[256];
-    // vertex items (point | axis << 10), then triangle items (point |
-    // k << 10 | case << 13): at most 3 and 5 per point
-    __shared__ uint32_t items[5 * kScanTile];
-    // the case table's triangle edges (256 x 15 bytes, word aligned), read
-    // from LDS by the triangle items
+    // the case table's triangle edges (256 x 15 bytes, word aligned)
     __shared__ uint32_t tri_lds[256 * 15 / 4];
     nt_lds[threadIdx.x] = ntri[threadIdx.x];              // kBlock == 256 cases
     for (int k = threadIdx.x; k < 256 * 15 / 4; k += kBlock)
         tri_lds[k] = reinterpret_cast<const uint32_t *>(tris_of)[k];
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    const int64_t p0 = base + (int64_t)threadIdx.x * kScanItems;
-    uint32_t mw = 0, cw = 0;
-    if (p0 + 4 <= g.n) {                                  // p0 is a multiple of 4
-        mw = *reinterpret_cast<const uint32_t *>(mask + p0);
-        cw = *reinterpret_cast<const uint32_t *>(cases + p0);
-    } else {
-        for (int k = 0; p0 + k < g.n && k < 4; ++k) {
-            mw |= (uint32_t)mask[p0 + k] << (8 * k);
-            cw |= (uint32_t)cases[p0 + k] << (8 * k);
+    const int lane = (int)(threadIdx.x & 63), wv = (int)(threadIdx.x >> 6);
+    const int wi = lane / WL, part_w = lane % WL, b0 = part_w * kMcSlice;
+    const uint32_t grp = blockIdx.x * kMcEmitWaves + wv;
+    if (grp >= ngroups) return;                           // whole waves
+    // the count block: the last whose first group is not beyond grp, by a
+    // search of 64 places at a time
+    uint32_t blk = 0;
+    for (uint32_t span = nb; span > 1;) {
+        const uint32_t step = (span + 63u) / 64u, at = blk + lane * step;
+        const bool le = lane * step < span && gbase[at] <= grp;
+        const uint32_t top = 63u - (uint32_t)__builtin_clzll(__ballot(le));   // lane 0 always
+        blk += top * step;
+        span = span - top * step < step ? span - top * step : step;
+    }
+    const uint32_t gk = grp - gbase[blk], nl = nlist[blk];
+    const uint32_t gn = blk + 1 < nb ? gbase[blk + 1] - gbase[blk] : ngroups - gbase[blk];
+    const uint8_t *gs = group + (int64_t)blk * kMcWords + gk;
+    const uint32_t l = gs[0] + (uint32_t)wi, lend = gk + 1 < gn ? gs[1] : nl;
+    const uint32_t vb = vbase[blk], tb = tbase[blk];
+    const int64_t sxy = (int64_t)g.nx * g.ny;
+    const uint32_t off_bits[4] = {0u, (uint32_t)g.nx & 63u, (uint32_t)(sxy & 63),
+                                  (uint32_t)((sxy + g.nx) & 63)};
+    uint32_t e[3] = {0, 0, 0}, act = 0, v0 = 0, t0 = 0;
+    int64_t w = 0;
+    if (l < lend) {
+        w = (int64_t)blk * kMcWords + list[(int64_t)blk * kMcWords + l];
+        const McWord m = words[w];
+        const uint32_t low = (uint32_t)((1ull << kMcSlice) - 1ull);
+        v0 = vb + m.v;
+        t0 = tb + m.t;
+        for (int a = 0; a < 3; ++a) e[a] = (uint32_t)(m.e[a] >> b0) & low;
+        act = (uint32_t)(cells[w] >> b0) & low;
+        const int o = part_w >> 1;
+        const int64_t off = (o & 1 ? (int64_t)g.nx : 0) + (o & 2 ? sxy : 0);
+        const int64_t q = w + (off >> 6) + (part_w & 1);
+        if (q < nw) {                  // a word without vertices is not named
+            const McWord mq = words[q];
+            McCorner &k = s_k[wv][wi][part_w];
+            for (int a = 0; a < 3; ++a) k.e[a] = mq.e[a];
+            k.id = vbase[q / kMcWords] + mq.v;
+        }
+        if ((part_w & 1) == 0) {
+            uint64_t u, v;
+            corner_words(inside, nw, w, off, u, v);
+            s_c[wv][wi][2 * o] = u;
+            s_c[wv][wi][2 * o + 1] = v;
         }
     }
-    uint32_t tc[kScanItems], sv = 0, st = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        tc[k] = p0 + k < g.n ? (uint32_t)nt_lds[(cw >> (8 * k)) & 0xffu] : 0u;
-        st += tc[k];
-        sv += (uint32_t)__popc((mw >> (8 * k)) & 7u);
-    }
-    // both counts in one scan: a tile has at most 3072 vertices, so they
-    // stay in the low 16 bits
+    // at most 3 PTS vertices and PTS cells
     uint32_t tot;
-    const uint32_t r = block_scan_excl(sv | (st << 16), &tot);
-    const uint32_t nv = tot & 0xffffu, ntr = tot >> 16;
-    uint32_t rv = r & 0xffffu, rt = r >> 16;
-    const uint32_t lp = threadIdx.x * kScanItems;
-    for (int k = 0; k < kScanItems; ++k) {
-        const uint32_t m = (mw >> (8 * k)) & 7u;
-        for (int a = 0; a < 3; ++a)
-            if ((m >> a) & 1u) items[rv++] = (lp + k) | ((uint32_t)a << 10);
+    const uint32_t r = wave_scan_excl((uint32_t)(__popc(e[0]) + __popc(e[1]) + __popc(e[2])) |
+                                          ((uint32_t)__popc(act) << 16), lane, tot);
+    const uint32_t nv = tot & 0xffffu, nc = tot >> 16;
+    uint32_t rv = r & 0xffffu, rc = r >> 16;
+    if (part_w == 0) {
+        s_base[wv][wi] = 64 * w;
+        s_v[wv][wi] = v0 - rv;
     }
-    __syncthreads();
-    const uint32_t vb = vbase[blockIdx.x], tb = tbase[blockIdx.x];
-    for (uint32_t j = threadIdx.x; j < nv; j += kBlock) {
-        const uint32_t e = items[j];
-        mc_emit_vertex(phi, g, iso, verts, normals, base + (e & 1023u), (int)(e >> 10), vb + j);
+    uint32_t todo = e[0] | e[1] | e[2];
+    while (todo) {
+        const int b = __builtin_ctz(todo);
+        todo &= todo - 1;
+        const uint32_t pt = (uint32_t)(lane * kMcSlice + b);
+#pragma unroll
+        for (uint32_t a = 0; a < 3; ++a)
+            if ((e[a] >> b) & 1u) s_item[wv][rv++] = (uint16_t)(pt | (a << 10));
     }
-    __syncthreads();
-    for (int k = 0; k < kScanItems; ++k) {
-        const uint32_t cs = (cw >> (8 * k)) & 0xffu;
-        for (uint32_t q = 0; q < tc[k]; ++q) items[rt++] = (lp + k) | (q << 10) | (cs << 13);
+    wave_lds_fence();
+    for (uint32_t j = lane; j < nv; j += 64) {
+        const uint32_t it = s_item[wv][j], pt = it & 1023u;
+        mc_emit_vertex(phi, g, iso, verts, normals, s_base[wv][pt >> 6] + (pt & 63u),
+                       (int)(it >> 10), s_v[wv][pt >> 6] + j);
     }
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < ntr; j += kBlock) {
-        const uint32_t e = items[j];
-        mc_emit_tri(g, reinterpret_cast<const int8_t *>(tri_lds), mask, voff, vbase, tris,
-                    base + (e & 1023u), (int)(e >> 13),
-                    (int)((e >> 10) & 7u), tb + j);
+    wave_lds_fence();
+    const bool first = part_w == 0;
+    uint32_t word_c0 = rc;      // place of the word's first cell (first lanes)
+    while (act) {
+        const int b = __builtin_ctz(act);
+        act &= act - 1;
+        s_item[wv][rc++] = (uint16_t)(lane * kMcSlice + b);
+    }
+    wave_lds_fence();
+    uint32_t done = 0;          // triangles of earlier cells
+    for (uint32_t j0 = 0; j0 < nc; j0 += 64) {
+        const uint32_t j = j0 + lane;
+        uint32_t n = 0;
+        if (j < nc) {
+            const uint32_t pt = s_item[wv][j];
+            uint32_t cs = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                cs |= (uint32_t)((s_c[wv][pt >> 6][k] >> (pt & 63u)) & 1ull) << k;
+            s_cell[wv][lane] = pt | (cs << 10);
+            n = nt_lds[cs];
+        }
+        uint32_t nt;
+        const uint32_t rt = wave_scan_excl(n, lane, nt);
+        for (uint32_t k = 0; k < n; ++k) s_tri[wv][rt + k] = (uint16_t)(lane | (k << 6));
+        // the triangles before a word's first cell, if it lies in these 64
+        const uint32_t at = __shfl(rt, (int)((word_c0 - j0) & 63u), 64);
+        if (first && word_c0 - j0 < 64u) s_t[wv][wi] = t0 - (done + at);
+        wave_lds_fence();
+        for (uint32_t q = lane; q < nt; q += 64) {
+            const uint32_t it = s_tri[wv][q], cc = s_cell[wv][it & 63u], pt = cc & 1023u;
+            mc_emit_tri(reinterpret_cast<const int8_t *>(tri_lds), s_k[wv][pt >> 6], off_bits, tris,
+                        pt & 63u, (int)(cc >> 10), (int)(it >> 6), s_t[wv][pt >> 6] + done + q);
+        }
+        done += nt;
+        wave_lds_fence();
     }
 }
 
@@ -1301,66 +1569,9 @@ __global__ __launch_bounds__(kBlock) void k_scan_tiles(const uint32_t *__restric
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
-// Marching-cubes scan tiles: the vertex count (edges set in the mask) and
-// the triangle count (of the cell's case) of each point are formed here
-// from the count pass's two bytes; each point gets its vertex offset within
-// the tile, and the tile its two totals (the emit pass scans the triangle
-// counts of its tile again, since only the point itself needs them).
-__global__ __launch_bounds__(kBlock) void k_mc_scan_tiles(const uint8_t *__restrict__ mask,
-                                                          const uint8_t *__restrict__ cases,
-                                                          const uint8_t *__restrict__ ntri,
-                                                          int64_t n, uint16_t *__restrict__ voff,
-                                                          uint32_t *__restrict__ vsums,
-                                                          uint32_t *__restrict__ tsums)
-{
-    static_assert(kScanItems == 4, "one word of mask and case bytes per thread");
-    __shared__ uint8_t nt_lds[256];
-    nt_lds[threadIdx.x] = ntri[threadIdx.x];              // kBlock == 256 cases
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    uint32_t mw = 0, cw = 0;
-    if (base + 4 <= n) {                                  // base is a multiple of 4
-        mw = *reinterpret_cast<const uint32_t *>(mask + base);
-        cw = *reinterpret_cast<const uint32_t *>(cases + base);
-    } else {
-        for (int k = 0; base + k < n && k < 4; ++k) {
-            mw |= (uint32_t)mask[base + k] << (8 * k);
-            cw |= (uint32_t)cases[base + k] << (8 * k);
-        }
-    }
-    uint32_t vc[kScanItems], sv = 0, st = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        const bool in = base + k < n;
-        vc[k] = in ? (uint32_t)__popc((mw >> (8 * k)) & 0xffu) : 0u;
-        st += in ? (uint32_t)nt_lds[(cw >> (8 * k)) & 0xffu] : 0u;
-        sv += vc[k];
-    }
-    // both totals in one scan: a tile has at most 3 * kScanTile = 3072
-    // vertices, so they stay in the low 16 bits (and a point's offset
-    // within its tile fits a u16)
-    static_assert(3 * kScanTile < (1 << 16), "tile vertex offsets in 16 bits");
-    uint32_t tot;
-    uint32_t rv = block_scan_excl(sv | (st << 16), &tot) & 0xffffu;
-    uint16_t o[kScanItems];
-    for (int k = 0; k < kScanItems; ++k) {
-        o[k] = (uint16_t)rv;
-        rv += vc[k];
-    }
-    if (base + 4 <= n) {                                  // 8-byte aligned: base % 4 == 0
-        *reinterpret_cast<uint2 *>(voff + base) =
-            make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
-    } else {
-        for (int k = 0; base + k < n && k < 4; ++k) voff[base + k] = o[k];
-    }
-    if (threadIdx.x == 0) {
-        vsums[blockIdx.x] = tot & 0xffffu;
-        tsums[blockIdx.x] = tot >> 16;
-    }
-}
-
 // One 1024-thread block: exclusive scans of the vertex and the triangle
 // tile totals in place, grand totals after them.
-constexpr int kSums2Block = 1024;
+constexpr int kSums3Block = 1024;
 
 __device__ __forceinline__ uint32_t block_scan_excl_1024(uint32_t v, uint32_t *total,
                                                          uint32_t *ws)
@@ -1374,7 +1585,7 @@ __device__ __forceinline__ uint32_t block_scan_excl_1024(uint32_t v, uint32_t *t
     if (lane == 63) ws[w] = x;
     __syncthreads();
     uint32_t off = 0, tot = 0;
-    for (int k = 0; k < kSums2Block / 64; ++k) {
+    for (int k = 0; k < kSums3Block / 64; ++k) {
         if (k < w) off += ws[k];
         tot += ws[k];
     }
@@ -1383,62 +1594,60 @@ __device__ __forceinline__ uint32_t block_scan_excl_1024(uint32_t v, uint32_t *t
     return off + x - v;
 }
 
-// Chunks of kSums2Chunk entries of both arrays go through LDS: loaded and
-// stored coalesced, scanned there with eight consecutive entries per
-// thread (one block on one CU: per-thread contiguous global reads were
-// uncoalesced and took 95 us for 32k tiles).
-constexpr int kSums2Chunk = kSums2Block * 8;
+// Exclusive scans of three arrays of nb entries in place, grand totals to
+// totals[3].  Chunks of kSums3Chunk entries of each go through LDS: loaded
+// and stored coalesced, scanned there with four consecutive entries per
+// thread (per-thread contiguous global reads were uncoalesced).
+constexpr int kSums3Chunk = kSums3Block * 4;
 
-__global__ __launch_bounds__(kSums2Block) void k_scan_sums2(uint32_t *__restrict__ a,
-                                                            uint32_t *__restrict__ b, int nb)
+__global__ __launch_bounds__(kSums3Block) void k_scan_sums3(uint32_t *__restrict__ a0,
+                                                            uint32_t *__restrict__ a1,
+                                                            uint32_t *__restrict__ a2, int nb,
+                                                            uint32_t *__restrict__ totals)
 {
-    __shared__ uint32_t la[kSums2Chunk], lb[kSums2Chunk];
-    __shared__ uint32_t ws[kSums2Block / 64];
-    uint32_t carry_a = 0, carry_b = 0;
-    for (int c0 = 0; c0 < nb; c0 += kSums2Chunk) {
-        const int m = nb - c0 < kSums2Chunk ? nb - c0 : kSums2Chunk;
+    __shared__ uint32_t l[3][kSums3Chunk];
+    __shared__ uint32_t ws[kSums3Block / 64];
+    uint32_t *const a[3] = {a0, a1, a2};
+    uint32_t carry[3] = {0, 0, 0};
+    for (int c0 = 0; c0 < nb; c0 += kSums3Chunk) {
+        const int m = nb - c0 < kSums3Chunk ? nb - c0 : kSums3Chunk;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int i = k * kSums2Block + (int)threadIdx.x;
-            la[i] = i < m ? a[c0 + i] : 0u;
-            lb[i] = i < m ? b[c0 + i] : 0u;
-        }
-        __syncthreads();
-        uint32_t va[8], vb[8], sa = 0, sb = 0;
+        for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            va[k] = la[8 * threadIdx.x + k];
-            vb[k] = lb[8 * threadIdx.x + k];
-            sa += va[k];
-            sb += vb[k];
-        }
-        uint32_t ta, tb;
-        uint32_t ra = carry_a + block_scan_excl_1024(sa, &ta, ws);
-        uint32_t rb = carry_b + block_scan_excl_1024(sb, &tb, ws);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            la[8 * threadIdx.x + k] = ra;
-            lb[8 * threadIdx.x + k] = rb;
-            ra += va[k];
-            rb += vb[k];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int i = k * kSums2Block + (int)threadIdx.x;
-            if (i < m) {
-                a[c0 + i] = la[i];
-                b[c0 + i] = lb[i];
+            for (int k = 0; k < 4; ++k) {
+                const int i = k * kSums3Block + (int)threadIdx.x;
+                l[q][i] = i < m ? a[q][c0 + i] : 0u;
             }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            uint32_t v[4], sum = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[k] = l[q][4 * threadIdx.x + k];
+                sum += v[k];
+            }
+            uint32_t tot;
+            uint32_t r = carry[q] + block_scan_excl_1024(sum, &tot, ws);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                l[q][4 * threadIdx.x + k] = r;
+                r += v[k];
+            }
+            carry[q] += tot;
         }
-        carry_a += ta;
-        carry_b += tb;
-        __syncthreads();   // la / lb are refilled by the next chunk
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = k * kSums3Block + (int)threadIdx.x;
+                if (i < m) a[q][c0 + i] = l[q][i];
+            }
+        __syncthreads();   // refilled by the next chunk
     }
-    if (threadIdx.x == 0) {
-        a[nb] = carry_a;
-        b[nb] = carry_b;
-    }
+    if (threadIdx.x == 0)
+        for (int q = 0; q < 3; ++q) totals[q] = carry[q];
 }
 
 // one block: exclusive scan of the tile sums in place, grand total after
@@ -1828,27 +2037,33 @@ hipError_t tsdf_shells_phi_launch(const uint8_t *vt, const uint64_t *O, uint8_t 
     return hipGetLastError();
 }
 
+int64_t mc_words(int64_t n) { return (n + 63) / 64; }
+int64_t mc_blocks(int64_t n) { return (mc_words(n) + kMcWords - 1) / kMcWords; }
+size_t mc_word_bytes() { return sizeof(McWord); }
+
 hipError_t mc_count_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
-                           uint8_t *mask, uint8_t *cases, uint16_t *voff, uint32_t *vsums,
-                           uint32_t *tsums, hipStream_t s)
+                           const McBuffers &b, hipStream_t s)
 {
-    const dim3 tiles((unsigned)((g.nx + kMcTX - 1) / kMcTX), (unsigned)((g.ny + kMcTY - 1) / kMcTY),
-                     (unsigned)((g.nz + kMcTZ - 1) / kMcTZ));
-    hipLaunchKernelGGL(k_mc_count_tile, tiles, dim3(kBlock), 0, s, phi, g, iso, mask, cases);
-    const int64_t nb = (g.n + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_mc_scan_tiles, dim3((unsigned)nb), dim3(kBlock), 0, s, mask, cases, ntri,
-                       g.n, voff, vsums, tsums);
-    hipLaunchKernelGGL(k_scan_sums2, dim3(1), dim3(kSums2Block), 0, s, vsums, tsums, (int)nb);
+    const int64_t nw = mc_words(g.n), nb = mc_blocks(g.n);
+    hipLaunchKernelGGL(k_mc_inside, dim3(grid_for(nw, kMcInsideRun * (kBlock / 64))), dim3(kBlock),
+                       0, s, phi, g.n, iso, b.inside);
+    hipLaunchKernelGGL(k_mc_count, dim3((unsigned)nb), dim3(kMcWords), 0, s, b.inside, g, nw, ntri,
+                       static_cast<McWord *>(b.words), b.cells, b.list, b.group, b.nlist, b.vsums, b.tsums,
+                       b.gsums);
+    hipLaunchKernelGGL(k_scan_sums3, dim3(1), dim3(kSums3Block), 0, s, b.vsums, b.tsums, b.gsums,
+                       (int)nb, b.totals);
     return hipGetLastError();
 }
 
 hipError_t mc_emit_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
-                          const int8_t *tris_of, const uint8_t *mask, const uint8_t *cases,
-                          const uint16_t *voff, const uint32_t *vsums, const uint32_t *tsums,
+                          const int8_t *tris_of, const McBuffers &b, uint32_t ngroups,
                           float *verts, int32_t *tris, float *normals, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mc_emit, dim3(grid_for(g.n, kScanTile)), dim3(kBlock), 0, s, phi, g, iso,
-                       ntri, tris_of, mask, cases, voff, vsums, tsums, verts, tris, normals);
+    if (ngroups == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_mc_emit, dim3(grid_for(ngroups, kMcEmitWaves)), dim3(kBlock), 0, s, phi, g,
+                       iso, mc_words(g.n), (uint32_t)mc_blocks(g.n), ngroups, ntri, tris_of,
+                       b.inside, static_cast<const McWord *>(b.words), b.cells, b.list, b.group,
+                       b.nlist, b.vsums, b.tsums, b.gsums, verts, tris, normals);
     return hipGetLastError();
 }
 

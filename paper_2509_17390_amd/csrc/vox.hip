@@ -543,29 +543,31 @@ rc_status rc_marching_cubes(rc_ctx *c, const rc_grid *grid, const float *phi, fl
     const int8_t *tris_of = reinterpret_cast<const int8_t *>(c->mc_table + 256);
     std::lock_guard<std::mutex> lk(c->mesh_mu);
     Scratch ws(c);
-    uint8_t *mask, *cases;
-    uint16_t *voff;
-    uint32_t *vs, *ts;
-    const int64_t ns = mc_scan_sums_len(g.n);
-    ws.take(&mask, g.n);
-    ws.take(&cases, g.n);
-    ws.take(&voff, sizeof(uint16_t) * g.n);
-    ws.take(&vs, sizeof(uint32_t) * ns);
-    ws.take(&ts, sizeof(uint32_t) * ns);
+    McBuffers b;
+    const int64_t nw = mc_words(g.n), nb = mc_blocks(g.n);
+    ws.take(&b.inside, sizeof(uint64_t) * nw);
+    ws.take(&b.words, mc_word_bytes() * nw);
+    ws.take(&b.cells, sizeof(uint64_t) * nw);
+    ws.take(&b.list, (size_t)256 * nb);
+    ws.take(&b.group, (size_t)256 * nb);
+    ws.take(&b.nlist, sizeof(uint32_t) * (4 * nb + 3));
     st = ws.commit();
     if (st != RC_OK) return st;
-    HIP_TRY(mc_count_launch(phi, g, iso, ntri, mask, cases, voff, vs, ts, s));
-    uint32_t tot[2];
-    HIP_TRY(hipMemcpyAsync(&tot[0], vs + ns - 1, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&tot[1], ts + ns - 1, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    b.vsums = b.nlist + nb;
+    b.tsums = b.vsums + nb;
+    b.gsums = b.tsums + nb;
+    b.totals = b.gsums + nb;
+    HIP_TRY(mc_count_launch(phi, g, iso, ntri, b, s));
+    uint32_t tot[3];
+    HIP_TRY(hipMemcpyAsync(tot, b.totals, sizeof tot, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     *n_verts = tot[0];
     *n_tris = tot[1];
     if (!out_verts) return RC_OK;
     if (cap_verts < (int64_t)tot[0] || cap_tris < (int64_t)tot[1])
         return fail(RC_E_NOMEM, "mesh needs %u vertices and %u triangles", tot[0], tot[1]);
-    HIP_TRY(mc_emit_launch(phi, g, iso, ntri, tris_of, mask, cases, voff, vs, ts, out_verts,
-                           out_tris, out_normals, s));
+    HIP_TRY(mc_emit_launch(phi, g, iso, ntri, tris_of, b, tot[2], out_verts, out_tris, out_normals,
+                           s));
     HIP_TRY(hipStreamSynchronize(s));
     return RC_OK;
 }

@@ -339,3 +339,45 @@ def test_marching_cubes_many_scan_tiles(ctx):
     np.testing.assert_array_equal(tg.cpu().numpy(), to)
     np.testing.assert_array_equal(vg.cpu().numpy().view(np.uint32), vo.view(np.uint32))
     np.testing.assert_array_equal(ng.cpu().numpy().view(np.uint32), no.view(np.uint32))
+
+
+@pytest.mark.parametrize("shape,share", [
+    ((2, 2, 2), 0.5), ((1, 5, 7), 0.5), ((5, 3, 1), 0.5), ((3, 4, 63), 0.5), ((3, 4, 64), 0.5),
+    ((3, 5, 65), 0.5), ((2, 130, 129), 0.5), ((3, 64, 86), 0.02), ((17, 31, 63), 0.001),
+    ((40, 90, 130), 0.5), ((40, 90, 130), 0.003)])
+def test_marching_cubes_word_edges(ctx, shape, share):
+    # rows that begin anywhere in a 64-point word, grids of one and of many
+    # 256-word blocks, words of 0 to 192 vertices in groups of one to eight:
+    # a lattice of independent signs, `share` of them inside
+    rng = np.random.default_rng(sum(shape))
+    mag = rng.uniform(0.1, 1.0, shape).astype(np.float32)
+    phi = np.where(rng.random(shape) < share, -mag, mag)
+    phi.reshape(-1)[0] = -0.5
+    nz, ny, nx = shape
+    g = ctx.grid((0.5, -0.25, 0.125), 0.25, (nx, ny, nz), 0.0)
+    log(f"marching cubes, {shape}, {share}")
+    check_mc(ctx, phi, g, (0.5, -0.25, 0.125), 0.25, 0.0, tag=f"{shape}")
+
+
+def test_marching_cubes_scan_of_many_blocks(ctx):
+    # 80M lattice points: 4,900 blocks of 16,384, more than the 4,096 one LDS
+    # chunk of the offset scan holds.  Two balls, in the first and the last
+    # layers; the spacing is a power of two, so the last one's mesh is that of
+    # its own layers moved by whole voxels, with its ids behind the first one's
+    import torch
+    nz, ny, nx = 80, 1000, 1001
+    phi = torch.ones((nz, ny, nx), dtype=torch.float32, device="cuda")
+    z, y, x = np.meshgrid(np.arange(12), np.arange(60), np.arange(70), indexing="ij")
+    ball = (np.sqrt((x - 31.3) ** 2 + (y - 28.2) ** 2 + (z - 5.1) ** 2) - 4.4).astype(np.float32)
+    part = np.full((12, ny, nx), 1.0, np.float32)
+    part[:, 300:360, 500:570] = np.minimum(ball, 1.0)
+    phi[:12] = torch.from_numpy(part).cuda()
+    phi[-12:] = torch.from_numpy(part).cuda()
+    g = ctx.grid((0.0, 0.0, 0.0), 0.5, (nx, ny, nz), 0.0)
+    log(f"marching cubes on {phi.numel()} points")
+    vg, tg = ctx.marching_cubes(g, phi, 0.0)
+    sub = part[:, 295:365, 495:575]
+    v0, t0 = ot.marching_cubes(sub, (495 * 0.5, 295 * 0.5, 0.0), 0.5, 0.0)
+    v1, t1 = ot.marching_cubes(sub, (495 * 0.5, 295 * 0.5, (nz - 12) * 0.5), 0.5, 0.0)
+    np.testing.assert_array_equal(vg.cpu().numpy(), np.concatenate([v0, v1]))
+    np.testing.assert_array_equal(tg.cpu().numpy(), np.concatenate([t0, t1 + len(v0)]))
