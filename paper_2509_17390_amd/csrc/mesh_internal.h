@@ -31,18 +31,15 @@ struct Binomial {
     uint32_t w[2 * kMaxBinomial + 1];
 };
 
-// V~ = [sum >= thr] of the separable binomial smoothing of `surf`; abuf and
-// bbuf (tsdf_smooth_a_bytes / _b_bytes, 8-byte aligned) hold the x and xy
-// passes (narrow and padded for kernels of at most 3 steps when surf and
-// vt are 4-byte aligned, else u32 and u64).
+// V~ = [sum >= thr] of the separable binomial smoothing of `surf`; a and b
+// (tsdf_smooth_a_bytes / _b_bytes) hold the x and xy passes.
 size_t tsdf_smooth_a_bytes(const TsdfGrid &g);
 size_t tsdf_smooth_b_bytes(const TsdfGrid &g);
-hipError_t tsdf_smooth_launch(const uint8_t *surf, void *abuf, void *bbuf, uint8_t *vt,
+hipError_t tsdf_smooth_launch(const uint8_t *surf, uint32_t *a, uint64_t *b, uint8_t *vt,
                               const TsdfGrid &g, const Binomial &w, uint64_t thr, hipStream_t s);
-// The integer sums of the same smoothing ([nz][ny][nx] uint64, u32 x and
-// u64 xy passes in abuf / bbuf), and V~ = [sums >= *thr] with thr on the
-// device (the quantile re-threshold).
-hipError_t tsdf_smooth_sums_launch(const uint8_t *surf, void *abuf, void *bbuf, uint64_t *sums,
+// The integer sums of the same smoothing ([nz][ny][nx] uint64), and V~ =
+// [sums >= *thr] with thr on the device (the quantile re-threshold).
+hipError_t tsdf_smooth_sums_launch(const uint8_t *surf, uint32_t *a, uint64_t *b, uint64_t *sums,
                                    const TsdfGrid &g, const Binomial &w, hipStream_t s);
 hipError_t tsdf_threshold_launch(const uint64_t *sums, const uint64_t *thr, uint8_t *vt,
                                  int64_t n, hipStream_t s);
@@ -56,11 +53,12 @@ hipError_t mc_stride_gather_launch(const float *phi, const TsdfGrid &g, int step
 // (*changed set when O grew).
 int tsdf_words_per_row(const TsdfGrid &g);
 int64_t tsdf_seg_words(const TsdfGrid &g);
-// Smoothing, threshold and packing in one tiled pass (V~ into vt, the free
-// and cleared outside words into F and O), for kernels of 1 to 3 steps.
-bool tsdf_smooth_pack_fused(const Binomial &w);
-hipError_t tsdf_smooth_pack_launch(const uint8_t *surf, uint8_t *vt, uint64_t *F, uint64_t *O,
-                                   const TsdfGrid &g, const Binomial &w, uint64_t thr,
+// Smoothing, threshold and packing on packed surface words (bits: one word
+// per F word), for kernels of 1 to 3 steps: V~ into vt (null: not wanted),
+// the free and cleared outside words into F and O.
+bool tsdf_smooth_on_bits(const Binomial &w);
+hipError_t tsdf_smooth_bits_launch(const uint8_t *surf, uint64_t *bits, uint8_t *vt, uint64_t *F,
+                                   uint64_t *O, const TsdfGrid &g, const Binomial &w, uint64_t thr,
                                    hipStream_t s);
 hipError_t tsdf_pack_launch(const uint8_t *vt, uint64_t *F, uint64_t *O, const TsdfGrid &g,
                             hipStream_t s);
@@ -69,6 +67,12 @@ hipError_t tsdf_pack_launch(const uint8_t *vt, uint64_t *F, uint64_t *O, const T
 hipError_t tsdf_flood_round_launch(const uint64_t *F, uint64_t *O, uint64_t *seg,
                                    const TsdfGrid &g, const int32_t *prev, int32_t *changed,
                                    hipStream_t s);
+// Shells and phi from the packed words, for 1 to 4 shells; nothing while
+// *unsettled (the last enqueued round's *changed) is set.
+bool tsdf_shells_on_bits(int shells);
+hipError_t tsdf_shells_phi_bits_launch(const uint64_t *F, const uint64_t *O, float *phi,
+                                       const TsdfGrid &g, int shells, float h, float r,
+                                       const int32_t *unsettled, hipStream_t s);
 // Shells and phi.  p (one byte per voxel) must be 4-byte aligned with
 // tsdf_shell_pad(g) readable bytes before and after it.
 int64_t tsdf_shell_pad(const TsdfGrid &g);

@@ -400,11 +400,13 @@ struct Scratch {
 
 }  // namespace
 
-// Outside-labelling rounds enqueued per flag read: 6 first (the usual
-// masks settle in 5 to 10 rounds), then 2, 4 and 8 at a time, so that few
-// rounds run after the fixed point and a slow mask still costs few reads.
+// Outside-labelling rounds enqueued per flag read.  The usual masks settle in
+// 2 to 5 rounds on small grids and 5 to 8 on large ones; a flag read costs the
+// stream some 25 us, a round after the last one 5 us.  4 first up to 2^22
+// voxels (8 there: +8 us of 370 at 350,200 voxels), 8 beyond (6 and a second
+// read: +40 us of 480 at 34.2M), then 4 and 8 at a time.
 constexpr int kFloodBatchMax = 8;
-inline int flood_batch(int k) { return k == 0 ? 6 : (k == 1 ? 2 : (k == 2 ? 4 : 8)); }
+inline int flood_batch(int64_t k, int64_t n) { return k == 1 || (k == 0 && n <= (1 << 22)) ? 4 : 8; }
 
 rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_tsdf_opts *opts,
                   float *out_phi, uint8_t *out_vtilde, void *stream)
@@ -453,18 +455,25 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
     hipStream_t s = static_cast<hipStream_t>(stream);
     std::lock_guard<std::mutex> lk(c->mesh_mu);
     Scratch ws(c);
-    uint32_t *a;
-    uint64_t *b;
-    uint8_t *vt = out_vtilde, *pbuf;
+    uint32_t *a = nullptr;
+    uint64_t *b = nullptr, *bits = nullptr;
+    uint8_t *vt = out_vtilde, *pbuf = nullptr;
     uint64_t *fw, *ow, *seg;
     int32_t *flag;
+    const int64_t nwords = (int64_t)tsdf_words_per_row(g) * g.ny * g.nz;
+    // on bits, V~ is a word array; bytes only where they are asked for or
+    // the general passes read them
+    const bool smooth_bits = !quant && tsdf_smooth_on_bits(w), shell_bits = tsdf_shells_on_bits(shells);
     // the shell kernel reads whole words up to one z-layer beyond the grid
     const int64_t pad = tsdf_shell_pad(g);
-    const int64_t nwords = (int64_t)tsdf_words_per_row(g) * g.ny * g.nz;
-    ws.take(&a, tsdf_smooth_a_bytes(g));
-    ws.take(&b, tsdf_smooth_b_bytes(g));
-    if (!vt) ws.take(&vt, g.n);
-    ws.take(&pbuf, g.n + 2 * pad + 4);
+    if (smooth_bits) {
+        ws.take(&bits, sizeof(uint64_t) * nwords);
+    } else {
+        ws.take(&a, tsdf_smooth_a_bytes(g));
+        ws.take(&b, tsdf_smooth_b_bytes(g));
+    }
+    if (!vt && !(smooth_bits && shell_bits)) ws.take(&vt, g.n);
+    if (!shell_bits) ws.take(&pbuf, g.n + 2 * pad + 4);
     ws.take(&fw, sizeof(uint64_t) * nwords);
     ws.take(&ow, sizeof(uint64_t) * nwords);
     ws.take(&seg, sizeof(uint64_t) * 5 * tsdf_seg_words(g));
@@ -477,36 +486,42 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
     }
     st = ws.commit();
     if (st != RC_OK) return st;
-    uint8_t *p = pbuf + pad;
     if (quant) {
         HIP_TRY(tsdf_smooth_sums_launch(surf, a, b, sums, g, w, s));
         HIP_TRY(radix_select_u64_launch(sums, g.n, q_rank, sel, s));
         HIP_TRY(tsdf_threshold_launch(sums, radix_select_value(sel), vt, g.n, s));
         HIP_TRY(tsdf_pack_launch(vt, fw, ow, g, s));
-    } else if (tsdf_smooth_pack_fused(w)) {
-        HIP_TRY(tsdf_smooth_pack_launch(surf, vt, fw, ow, g, w, thr, s));
+    } else if (smooth_bits) {
+        HIP_TRY(tsdf_smooth_bits_launch(surf, bits, vt, fw, ow, g, w, thr, s));
     } else {
         HIP_TRY(tsdf_smooth_launch(surf, a, b, vt, g, w, thr, s));
         HIP_TRY(tsdf_pack_launch(vt, fw, ow, g, s));
     }
     // rounds until one changes nothing, enqueued in batches with one flag
     // read per batch: a round after a round that changed nothing returns at
-    // once, and repeating a settled round changes nothing
+    // once, and repeating a settled round changes nothing.  phi from bits is
+    // enqueued behind each batch and does nothing if that had not settled, so
+    // that it does not wait for the flag's way to the host.
     for (int64_t it = 0, k = 0;; ++k) {
-        const int nb = flood_batch((int)(k < 3 ? k : 3));
+        const int nb = flood_batch(k, g.n);
         int32_t changed[kFloodBatchMax];
         HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int32_t) * nb, s));
         for (int r = 0; r < nb; ++r)
             HIP_TRY(tsdf_flood_round_launch(fw, ow, seg, g, r ? flag + r - 1 : nullptr, flag + r,
                                             s));
+        if (shell_bits)
+            HIP_TRY(tsdf_shells_phi_bits_launch(fw, ow, out_phi, g, shells, g.hf, r, flag + nb - 1,
+                                                s));
         HIP_TRY(hipMemcpyAsync(changed, flag, sizeof(int32_t) * nb, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         if (!changed[nb - 1]) break;
         it += nb;
         if (it > g.n) return fail(RC_E_DEVICE, "outside labelling did not settle");
     }
-    HIP_TRY(tsdf_shells_phi_launch(vt, ow, p, out_phi, g, shells, g.hf, r, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    if (!shell_bits) {
+        HIP_TRY(tsdf_shells_phi_launch(vt, ow, pbuf + pad, out_phi, g, shells, g.hf, r, s));
+        HIP_TRY(hipStreamSynchronize(s));
+    }
     return RC_OK;
 }
 

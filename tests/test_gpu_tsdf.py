@@ -381,3 +381,29 @@ def test_marching_cubes_scan_of_many_blocks(ctx):
     v1, t1 = ot.marching_cubes(sub, (495 * 0.5, 295 * 0.5, (nz - 12) * 0.5), 0.5, 0.0)
     np.testing.assert_array_equal(vg.cpu().numpy(), np.concatenate([v0, v1]))
     np.testing.assert_array_equal(tg.cpu().numpy(), np.concatenate([t0, t1 + len(v0)]))
+
+
+@pytest.mark.parametrize("shape", [
+    (1, 1, 1), (2, 3, 5), (1, 17, 64), (16, 16, 65), (17, 33, 63), (18, 15, 130), (3, 9, 577),
+    (33, 2, 1), (2, 577, 40), (2, 3073, 65)])
+def test_bit_words_and_tiles(ctx, shape):
+    # words of one to 64 voxels, rows of one to ten words (more than a sweep
+    # reads together), rows of a slice on either side of its threads and of a
+    # lane's nine, a slice that does not fit LDS; smoothing of 1 to 3 steps on
+    # bits and of 4 by voxels, 1 to 4 shells on bits and 5 by voxels, with and
+    # without V~; masks between open and closed, the second time of any
+    # non-zero bytes, which count as 1 (the oracle adds up the mask's values
+    # and takes 0 and 1)
+    import torch
+    h = 0.5
+    rng = np.random.default_rng(sum(shape))
+    nz, ny, nx = shape
+    for n, shells in ((1, 1), (1, 3), (2, 2), (3, 4), (1, 5), (4, 3)):
+        sigma, band = h * float(np.sqrt(n / 2)), (shells - 0.5) * h
+        surf = np.where(rng.random(shape) < 0.45, rng.integers(1, 256, shape), 0).astype(np.uint8)
+        log(f"{shape}: n = {n}, {shells} shells")
+        phi, g = check_tsdf(ctx, (surf != 0).astype(np.uint8), (0.25, 0.5, -0.125), h, sigma, 0.46, band, tag=f"{shape}")
+        alone = torch.empty(shape, dtype=torch.float32, device="cuda")
+        ctx.tsdf(g, cuda(surf), alone, sigma, 0.46, band)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(alone.cpu().numpy().view(np.uint32), phi.view(np.uint32))
