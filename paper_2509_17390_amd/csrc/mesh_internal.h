@@ -226,13 +226,15 @@ struct QemBuffers {
     int32_t *nb;          // [nv][kQemNbrs] distinct neighbours, ascending
     int32_t *ndeg;        // [nv]
     uint32_t *nlarge;     // [nv] neighbours above the vertex
-    uint32_t *eoff;       // [nv] first edge number of the vertex
+    // first edge number of the vertex within its block of 256 vertices, and
+    // the blocks' ([nv / 256, rounded up])
+    uint32_t *eoff, *ebase;
     uint64_t *key;        // [3 nt] candidate key (cost bits << 32 | pi(edge)) or ~0
     uint8_t *cand;        // [3 nt] edge is a candidate
     double *X;            // [3 nt][3] contraction point of a candidate
-    // the previous step's eoff, key, cand and X (the host swaps the pairs
-    // before each step): an edge whose two ends are clean keeps its result
-    uint32_t *eoff_old;
+    // the previous step's eoff, ebase, key, cand and X (the host swaps the
+    // pairs before each step): an edge whose two ends are clean keeps its result
+    uint32_t *eoff_old, *ebase_old;
     uint64_t *key_old;
     uint8_t *cand_old;
     double *X_old;
@@ -240,47 +242,47 @@ struct QemBuffers {
     int32_t *eu_old, *ev_old;   // the previous step's
     unsigned long long *best;   // [nv]
     int32_t *remap;       // [nv] contracted into (or -1)
-    // [nv] in the closed one-rings of an edge contracted in the last step:
-    // the vertex's faces, neighbours and edges are evaluated anew
-    uint8_t *dirty;
+    // [nv] in the closed one-rings of an edge contracted in the last step
+    // (dirty; this step's into dirty_next, swapped as above): the vertex's
+    // faces, neighbours and edges are evaluated anew
+    uint8_t *dirty, *dirty_next;
     int32_t *absorbed;    // [nv] the vertex contracted into this one in the last step, or -1
-    uint32_t *counters;   // [4] candidates, contracted, live faces, flags
-    char *sel;            // qem_sel_bytes(): radix-select state
+    char *sel;            // qem_sel_bytes(): the loop's and the select's state, zeroed at first
+    char *slots;          // the step's counters, within sel
 };
 
-size_t qem_sel_bytes();
+// What the host reads of the state (at qem_sel_loop() of sel).
+enum QemError : uint32_t { kQemManyFaces = 1, kQemManyNbrs = 2, kQemStuck = 3, kQemMismatch = 4 };
+struct QemLoop {
+    int64_t nf, target;   // live faces; the round's target
+    uint32_t n_edges;     // of the last step
+    uint32_t steps;       // steps so far that had candidates
+    uint32_t removed;     // faces dropped by the last of them
+    uint32_t done;        // the round is over: target reached, no candidate, or an error
+    uint32_t error;       // QemError
+};
+
+size_t qem_sel_bytes(int64_t ne_cap);   // ne_cap = 3 nt
+size_t qem_sel_slots(int64_t ne_cap);
+size_t qem_sel_loop();
 // P from the float32 vertices; F from the triangles, faces with a repeated
 // corner removed.
 hipError_t qem_init_launch(const float *verts, int64_t nv, const int32_t *tris, int64_t nt,
                            double *P, int32_t *F, hipStream_t s);
-// Incident faces, neighbours and neighbour counts above each vertex; at a
-// round's start from all live faces, with the quadrics and protected
-// flags, else for the dirty vertices only, from their previous lists.
-// counters[3] |= 1 (2) when a vertex has more than kQemFaces faces
-// (kQemNbrs neighbours).
-hipError_t qem_incidence_launch(const QemBuffers &b, int64_t nv, int64_t nt, int round_start,
-                                hipStream_t s);
-// Candidate keys and points of every edge (eoff must hold the exclusive
-// scan of nlarge, n_edges its total); counters[0] += candidates.  At a
-// round's start every edge is evaluated; later the n_old edges of the
-// previous step (eu_old, ev_old, eoff_old, key_old, cand_old, X_old) whose
-// lower end is clean move to their new numbers, keeping their result when
-// the upper end is clean too, and only edges with a dirty end are
-// evaluated.
-hipError_t qem_edges_launch(const QemBuffers &b, int64_t nv, int64_t n_edges, int64_t n_old,
-                            int round_start, hipStream_t s);
-// Eligibility: the need smallest candidate keys; all of them when need is
-// at least counters[0] (decided on the device), else a radix select of the
-// need-th smallest of the n_edges keys.
-hipError_t qem_select_launch(const QemBuffers &b, int64_t n_edges, uint64_t need, hipStream_t s);
-// counters[2] += live faces.
+// Live faces into the state's nf.
 hipError_t qem_live_launch(const QemBuffers &b, int64_t nt, hipStream_t s);
-// Contract the chosen edges among the eligible ones (as qem_select_launch
-// left them): u takes x and Q_u + Q_v, v's
-// faces are renamed to u (the two on the edge dropped), the closed
-// one-rings are marked dirty (after clearing the marks); counters[1] +=
-// contractions, counters[2] += faces dropped.
-hipError_t qem_contract_launch(const QemBuffers &b, int64_t nv, int64_t n_edges, hipStream_t s);
+// A round's start: its target, the incident faces and neighbours of every
+// vertex, the quadrics and protected flags.
+hipError_t qem_round_launch(const QemBuffers &b, int64_t nv, int64_t nt, int64_t nf, int64_t target,
+                            hipStream_t s);
+// One step (nothing once the round is done): the dirty vertices' faces and
+// neighbours (but at a round's start), the edges' numbers, candidate keys and
+// points, eligibility (the smallest half-of-what-is-left keys, or every
+// candidate), and the contractions: u takes x and Q_u + Q_v, v's faces are
+// renamed to u (the two on the edge dropped), the closed one-rings are marked
+// dirty.  max_edges bounds the number of edges.
+hipError_t qem_step_launch(const QemBuffers &b, int64_t nv, int64_t nt, int64_t max_edges,
+                           int round_start, hipStream_t s);
 // keep[t] = live face, used[v] = 1 for their corners (used zeroed first).
 hipError_t qem_used_launch(const int32_t *F, int64_t nt, uint32_t *used, uint32_t *keep,
                            hipStream_t s);
@@ -291,11 +293,11 @@ hipError_t qem_emit_launch(const double *P, int64_t nv, const uint32_t *used,
                            const uint32_t *keep, const uint32_t *tpos, float *out_verts,
                            int32_t *out_tris, hipStream_t s);
 
-// Radix select over 64-bit keys (qem.hip): the rank-th smallest (1-based,
-// rank <= n) of keys[0..n) into the state (radix_select_state_bytes()),
-// readable on the device through radix_select_value(state) once the
-// launches have run.
+// Radix select over 64-bit keys below 2^bits (qem.hip): the rank-th smallest
+// (1-based, rank <= n) of keys[0..n) into the state
+// (radix_select_state_bytes()), readable on the device through
+// radix_select_value(state) once the launches have run.
 size_t radix_select_state_bytes();
-hipError_t radix_select_u64_launch(const uint64_t *keys, int64_t n, uint64_t rank, char *state,
-                                   hipStream_t s);
+hipError_t radix_select_u64_launch(const uint64_t *keys, int64_t n, uint64_t rank, int bits,
+                                   char *state, hipStream_t s);
 const uint64_t *radix_select_value(const char *state);

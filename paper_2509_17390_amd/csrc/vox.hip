@@ -488,7 +488,7 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
     if (st != RC_OK) return st;
     if (quant) {
         HIP_TRY(tsdf_smooth_sums_launch(surf, a, b, sums, g, w, s));
-        HIP_TRY(radix_select_u64_launch(sums, g.n, q_rank, sel, s));
+        HIP_TRY(radix_select_u64_launch(sums, g.n, q_rank, 6 * w.n + 1, sel, s));
         HIP_TRY(tsdf_threshold_launch(sums, radix_select_value(sel), vt, g.n, s));
         HIP_TRY(tsdf_pack_launch(vt, fw, ow, g, s));
     } else if (smooth_bits) {
@@ -560,14 +560,14 @@ rc_status rc_marching_cubes(rc_ctx *c, const rc_grid *grid, const float *phi, fl
     Scratch ws(c);
     McBuffers b;
     const int64_t nw = mc_words(g.n), nb = mc_blocks(g.n);
-    ws.take(&b.inside, sizeof(uint64_t) * nw);
+    ws.take(&b.inside, 2 * sizeof(uint64_t) * nw);
     ws.take(&b.words, mc_word_bytes() * nw);
-    ws.take(&b.cells, sizeof(uint64_t) * nw);
-    ws.take(&b.list, (size_t)256 * nb);
-    ws.take(&b.group, (size_t)256 * nb);
+    ws.take(&b.list, (size_t)512 * nb);
     ws.take(&b.nlist, sizeof(uint32_t) * (4 * nb + 3));
     st = ws.commit();
     if (st != RC_OK) return st;
+    b.cells = b.inside + nw;
+    b.group = b.list + 256 * nb;
     b.vsums = b.nlist + nb;
     b.tsums = b.vsums + nb;
     b.gsums = b.tsums + nb;
@@ -1014,7 +1014,7 @@ rc_status rc_decimate_qem(rc_ctx *c, const float *verts, int64_t nv, const int32
     std::lock_guard<std::mutex> lk(c->mesh_mu);
     Scratch ws(c);
     QemBuffers b;
-    uint32_t *used, *newid, *keep, *tpos, *sums;
+    uint32_t *sums;
     int32_t *flags;
     const int64_t ne_cap = 3 * nt;
     const size_t nss = (size_t)mc_scan_sums_len(nv > nt ? nv : nt);
@@ -1029,14 +1029,17 @@ rc_status rc_decimate_qem(rc_ctx *c, const float *verts, int64_t nv, const int32
     ws.take(&b.ndeg, sizeof(int32_t) * (size_t)nv);
     ws.take(&b.nlarge, sizeof(uint32_t) * (size_t)nv);
     ws.take(&b.eoff, sizeof(uint32_t) * (size_t)nv);
+    ws.take(&b.ebase, sizeof(uint32_t) * (size_t)((nv + 255) / 256));
     ws.take(&b.key, sizeof(uint64_t) * (size_t)ne_cap);
     ws.take(&b.cand, (size_t)ne_cap);
     ws.take(&b.X, sizeof(double) * 3 * (size_t)ne_cap);
     ws.take(&b.eoff_old, sizeof(uint32_t) * (size_t)nv);
+    ws.take(&b.ebase_old, sizeof(uint32_t) * (size_t)((nv + 255) / 256));
     ws.take(&b.key_old, sizeof(uint64_t) * (size_t)ne_cap);
     ws.take(&b.cand_old, (size_t)ne_cap);
     ws.take(&b.X_old, sizeof(double) * 3 * (size_t)ne_cap);
     ws.take(&b.dirty, (size_t)nv);
+    ws.take(&b.dirty_next, (size_t)nv);
     ws.take(&b.absorbed, sizeof(int32_t) * (size_t)nv);
     ws.take(&b.eu, sizeof(int32_t) * (size_t)ne_cap);
     ws.take(&b.ev, sizeof(int32_t) * (size_t)ne_cap);
@@ -1044,12 +1047,7 @@ rc_status rc_decimate_qem(rc_ctx *c, const float *verts, int64_t nv, const int32
     ws.take(&b.ev_old, sizeof(int32_t) * (size_t)ne_cap);
     ws.take(&b.best, sizeof(unsigned long long) * (size_t)nv);
     ws.take(&b.remap, sizeof(int32_t) * (size_t)nv);
-    ws.take(&b.counters, sizeof(uint32_t) * 4);
-    ws.take(&b.sel, qem_sel_bytes());
-    ws.take(&used, sizeof(uint32_t) * (size_t)nv);
-    ws.take(&newid, sizeof(uint32_t) * (size_t)nv);
-    ws.take(&keep, sizeof(uint32_t) * (size_t)nt);
-    ws.take(&tpos, sizeof(uint32_t) * (size_t)nt);
+    ws.take(&b.sel, qem_sel_bytes(ne_cap));
     ws.take(&sums, sizeof(uint32_t) * nss);
     ws.take(&flags, sizeof(int32_t));
     rc_status st = ws.commit();
@@ -1062,62 +1060,61 @@ rc_status rc_decimate_qem(rc_ctx *c, const float *verts, int64_t nv, const int32
     if (hf) return fail(RC_E_INVAL, "invalid mesh:%s%s", (hf & 1) ? " index out of range" : "",
                         (hf & 2) ? " non-finite vertex" : "");
     HIP_TRY(qem_init_launch(verts, nv, tris, nt, b.P, b.F, s));
-    uint32_t hc[4] = {0, 0, 0, 0};
+    b.slots = b.sel + qem_sel_slots(ne_cap);
+    HIP_TRY(hipMemsetAsync(b.sel, 0, qem_sel_bytes(ne_cap), s));
     // live faces after dropping repeated-corner faces
-    HIP_TRY(hipMemsetAsync(b.counters, 0, sizeof(uint32_t) * 4, s));
     HIP_TRY(qem_live_launch(b, nt, s));
-    HIP_TRY(hipMemcpyAsync(hc, b.counters, sizeof hc, hipMemcpyDeviceToHost, s));
+    QemLoop loop;
+    HIP_TRY(hipMemcpyAsync(&loop, b.sel + qem_sel_loop(), sizeof loop, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const int64_t f0 = hc[2];
-    int64_t nf = f0;
-    int64_t n_old = 0;
-    int32_t steps = 0;
+    const int64_t f0 = loop.nf;
     const double r = (double)ratio;
+    // every edge lies on a live face: at most three per face; a contraction
+    // adds none
+    int64_t max_edges = ne_cap;
     for (int k = 1; k <= rounds; ++k) {
         const int64_t target = (int64_t)ceil((double)f0 * pow(r, (double)k / (double)rounds));
-        for (int first = 1;; first = 0) {
-            if (nf <= target) break;
-            // the previous step's edge results become the old ones
-            std::swap(b.eoff, b.eoff_old);
-            std::swap(b.key, b.key_old);
-            std::swap(b.cand, b.cand_old);
-            std::swap(b.X, b.X_old);
-            std::swap(b.eu, b.eu_old);
-            std::swap(b.ev, b.ev_old);
-            // incidence of the live faces (a round's start also sums the
-            // quadrics and protects boundary vertices), edge numbering
-            HIP_TRY(hipMemsetAsync(b.counters, 0, sizeof(uint32_t) * 4, s));
-            HIP_TRY(qem_incidence_launch(b, nv, nt, first, s));
-            HIP_TRY(scan_u32_launch(b.nlarge, b.eoff, nv, sums, s));
-            uint32_t n_edges = 0;
-            HIP_TRY(hipMemcpyAsync(&n_edges, sums + mc_scan_sums_len(nv) - 1, sizeof(uint32_t),
+        if (loop.nf <= target) continue;
+        HIP_TRY(qem_round_launch(b, nv, nt, loop.nf, target, s));
+        // steps in batches with one read of the state each: as many as the
+        // last one's progress asks for, at most kQemBatch (a read costs the
+        // stream some 25 us, a step after the round's last one as much)
+        constexpr int64_t kQemBatch = 8;
+        int64_t batch = 4;
+        for (int first = 1;;) {
+            for (int64_t i = 0; i < batch; ++i, first = 0) {
+                // the previous step's edge results become the old ones
+                std::swap(b.eoff, b.eoff_old);
+                std::swap(b.ebase, b.ebase_old);
+                std::swap(b.key, b.key_old);
+                std::swap(b.cand, b.cand_old);
+                std::swap(b.X, b.X_old);
+                std::swap(b.eu, b.eu_old);
+                std::swap(b.ev, b.ev_old);
+                std::swap(b.dirty, b.dirty_next);
+                HIP_TRY(qem_step_launch(b, nv, nt, max_edges, first, s));
+            }
+            HIP_TRY(hipMemcpyAsync(&loop, b.sel + qem_sel_loop(), sizeof loop,
                                    hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipMemcpyAsync(hc, b.counters, sizeof hc, hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
-            if (hc[3] & 1) return fail(RC_E_INVAL, "a vertex has more than %d incident triangles",
-                                       kQemFaces);
-            if (hc[3] & 2) return fail(RC_E_INVAL, "a vertex has more than %d neighbours",
-                                       kQemNbrs);
-            // every edge lies on a live face: at most three per face
-            if ((int64_t)n_edges > ne_cap) return fail(RC_E_DEVICE, "edge count overflow");
-            HIP_TRY(qem_edges_launch(b, nv, n_edges, n_old, first, s));
-            n_old = n_edges;
-            // candidates, eligibility and contraction without a host read in
-            // between: the select decides on the device whether every
-            // candidate is eligible, and no candidate contracts nothing
-            const uint64_t need = (uint64_t)((nf - target + 1) / 2);
-            HIP_TRY(qem_select_launch(b, n_edges, need, s));
-            HIP_TRY(qem_contract_launch(b, nv, n_edges, s));
-            HIP_TRY(hipMemcpyAsync(hc, b.counters, sizeof hc, hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            if (hc[0] == 0) break;
-            ++steps;
-            if (hc[1] == 0) return fail(RC_E_DEVICE, "decimation step contracted nothing");
-            // a contraction drops exactly the two faces on its edge
-            if (hc[2] != 2 * hc[1]) return fail(RC_E_DEVICE, "decimation face count mismatch");
-            nf -= hc[2];
+            switch (loop.error) {
+            case kQemManyFaces:
+                return fail(RC_E_INVAL, "a vertex has more than %d incident triangles", kQemFaces);
+            case kQemManyNbrs:
+                return fail(RC_E_INVAL, "a vertex has more than %d neighbours", kQemNbrs);
+            case kQemStuck: return fail(RC_E_DEVICE, "decimation step contracted nothing");
+            case kQemMismatch: return fail(RC_E_DEVICE, "decimation face count mismatch");
+            default: break;
+            }
+            max_edges = loop.n_edges;
+            if (loop.done) break;
+            batch = loop.removed ? (loop.nf - target + loop.removed - 1) / loop.removed : 1;
+            batch = batch < kQemBatch ? batch : kQemBatch;
         }
     }
+    // free now: the edges' ends and the vertices' maps
+    uint32_t *keep = reinterpret_cast<uint32_t *>(b.eu), *tpos = reinterpret_cast<uint32_t *>(b.ev);
+    uint32_t *used = reinterpret_cast<uint32_t *>(b.remap), *newid = reinterpret_cast<uint32_t *>(b.absorbed);
     HIP_TRY(hipMemsetAsync(used, 0, sizeof(uint32_t) * (size_t)nv, s));
     HIP_TRY(qem_used_launch(b.F, nt, used, keep, s));
     uint32_t tot[2] = {0, 0};
@@ -1131,6 +1128,6 @@ rc_status rc_decimate_qem(rc_ctx *c, const float *verts, int64_t nv, const int32
     HIP_TRY(hipStreamSynchronize(s));
     *n_verts_out = tot[0];
     *n_tris_out = tot[1];
-    if (n_steps_out) *n_steps_out = steps;
+    if (n_steps_out) *n_steps_out = (int32_t)loop.steps;
     return RC_OK;
 }

@@ -141,3 +141,25 @@ def test_large_marching_cubes_mesh_properties(ctx, h):
     assert steps2 == steps and np.array_equal(gt2.cpu().numpy(), gt)
     assert np.array_equal(gv2.cpu().numpy().view(np.uint32), gv.view(np.uint32))
     log(f"qem large: {len(t)} -> {len(gt)} faces in {steps} steps")
+
+
+@pytest.mark.parametrize("mesh,ratio,rounds", [("fans", 0.3, 2), ("fans", 0.15, 1), ("wide", 0.98, 1)])
+def test_long_lists_and_wide_select(ctx, mesh, ratio, rounds):
+    # fans: two vertices of 50 faces and what merges into them (lists too long
+    # for eight lanes, more faces about an edge than are read ahead); wide:
+    # 3 x 23,232 edge places take 11-bit digits and 64 lines of counters, and
+    # the steps' blocks are many.  Bit-exact against the oracle
+    rng = np.random.default_rng(5)
+    v, t = (synth.uv_sphere((0.0, 0.0, 0.0), 1.0, 50, 8) if mesh == "fans"
+            else synth.grid_box((0.0, 0.0, 0.0), (2.0, 1.5, 1.0), 44))
+    v = (v + rng.normal(scale=0.003, size=v.shape)).astype(np.float32)
+    check(ctx, v, t, ratio, rounds, f"{mesh} {ratio}")
+
+
+def test_too_many_faces_at_a_vertex_is_an_error(ctx):
+    # 70 faces about a pole are refused, 64 are not
+    v, t = synth.uv_sphere((0.0, 0.0, 0.0), 1.0, 70, 6)
+    with pytest.raises(RcastError) as e:
+        ctx.decimate_qem(cuda(v), cuda(t), 0.5, 1)
+    assert e.value.status == RC_E_INVAL
+    check(ctx, *synth.uv_sphere((0.0, 0.0, 0.0), 1.0, 64, 6), 0.5, 1, "64 faces about a pole")
