@@ -18,12 +18,12 @@
 //                     exact float32 comparison
 //   k_gauss_records   64-byte evaluation records in leaf order: mu, the
 //                     whitening matrix M = c0 S^-1 R^T and alpha^2 * 2^31
-//   k_voxelize        one wave per tile.  Query: breadth-first from the root
-//                     until 64 subtrees are pending, then one depth-first
-//                     walk per lane; culling-set members go to an LDS ring.
-//                     Every 64 members the wave stages their records in LDS
-//                     (in the tile's voxel-unit frame) and each lane
-//                     evaluates one 8-voxel column of the tile against them.
+//   k_voxelize        one wave per tile, or four.  Query: 64 nodes off an LDS
+//                     stack at a time; culling-set members go to an LDS ring.
+//                     Every 64 members the wave stages their
+//                     records in LDS (in the tile's voxel-unit frame) and each
+//                     lane evaluates one 8-voxel column of the tile against
+//                     them.
 //   k_surface         6-neighbour test on the occupancy bytes
 //
 // The density is accumulated in 64-bit fixed point (units of 2^-31 per
@@ -38,9 +38,16 @@
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kRing = 256;        // LDS ring of culling-set members (<= 191 pending)
-constexpr int kFront = 128;       // breadth-first frontier (< 64 nodes, 2 children each)
-constexpr int kDfs = 64;          // per-lane stack; the tree depth is at most 62
+// per wave of a tile: the ring holds what is pending after a step (< 64 + 128)
+// and what the last flush may still be read from (64)
+constexpr int kRing = 256;        // LDS ring of culling-set members
+constexpr int kStack = 320;       // LDS stack of a wave's pending nodes
+constexpr int kDepth = 64;        // the tree depth is at most 62
+// Tiles up to which four waves share one: a launch that leaves the chip's 1,024
+// SIMDs idle or with one tile each.  One wave / four, us: 87 / 40 at 192
+// tiles, 111 / 89 at 1,768, 155 / 172 at 5,700, 248 / 333 at 11,550.
+constexpr int64_t kSharedTiles = 3072;
+constexpr int kSkipRun = 2;       // voxels of a column that are left out together
 constexpr float kQSkip = 33.0f;   // exp2(-q) * 2^31 < 1/4 beyond this
 constexpr double kC0 = 0.8493218002880191;   // sqrt(log2(e) / 2)
 constexpr double kFix = 2147483648.0;        // 2^31: fixed-point unit of one term
@@ -154,18 +161,42 @@ __device__ __forceinline__ void test_children(const NodeRec *__restrict__ nodes,
     hr = meets(nr.q0.z, nr.q0.w, nr.q1.z, nr.q1.w, nr.q2.z, nr.q2.w, tb);
 }
 
-// MODE 0: density and occupancy.  MODE 1: |C_tile| per tile only.
-template <int MODE>
-__global__ __launch_bounds__(64) void k_voxelize(const NodeRec *__restrict__ nodes,
-                                                 const GaussRec *__restrict__ recs,
-                                                 const float *__restrict__ boxes, int64_t n_gauss,
-                                                 VoxGrid g, float *__restrict__ density,
-                                                 uint8_t *__restrict__ occ,
-                                                 int32_t *__restrict__ counts)
+// LDS written by this wave is read by it next
+__device__ __forceinline__ void wave_lds_fence()
 {
-    __shared__ int32_t ring[kRing];
-    __shared__ int32_t front[kFront];
-    __shared__ float4 stage[64 * 4];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// MODE 0: density and occupancy.  MODE 1: |C_tile| per tile only.
+//
+// Bound by VALU issue on a grid of many tiles, 88 instructions a member and
+// wave, eight of them quarter-rate exponentials: 510 x 410 x 160 voxels and 1M
+// Gaussians (4.7M members) take 882 us; 964 with a test and a branch per voxel
+// and a depth-first walk per lane for the query, 926 with tests per voxel, 925
+// per four, 938 with none.  (The matrix cores' 4 x 4 outer products for u give
+// the same bits, but the moves to and from their registers cost more than the
+// 21 multiply-adds: 1,223.)
+//
+// WAVES: a launch of few tiles ends with its heaviest one, so four waves share
+// a tile: the stack, the ring, and a quarter of the members each; their sums
+// are whole numbers and add up to the same density in any order.
+template <int MODE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(6))) void
+k_voxelize(const NodeRec *__restrict__ nodes,
+                                                         const GaussRec *__restrict__ recs,
+                                                         const float *__restrict__ boxes,
+                                                         int64_t n_gauss, VoxGrid g,
+                                                         float *__restrict__ density,
+                                                         uint8_t *__restrict__ occ,
+                                                         int32_t *__restrict__ counts)
+{
+    static_assert(MODE == 0 || WAVES == 1, "one wave counts a tile");
+    constexpr int kThreads = 64 * WAVES, kSlots = kRing * WAVES, kNodes = kStack * WAVES;
+    __shared__ int32_t ring[kSlots];
+    __shared__ int32_t stack[kNodes];
+    __shared__ float4 s_stage[WAVES][64 * 4];
+    __shared__ uint32_t s_count[2][WAVES];      // leaves | inner nodes << 16, of a step's parity
 
     // Workgroups are dealt to the 8 XCDs in turn (workgroup b on XCD b % 8):
     // give each XCD one contiguous run of tiles so that neighbouring tiles,
@@ -173,7 +204,9 @@ __global__ __launch_bounds__(64) void k_voxelize(const NodeRec *__restrict__ nod
     const int64_t per = (int64_t)gridDim.x / 8;
     const int64_t tile = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
     if (tile >= g.n_tiles) return;
-    const int lane = threadIdx.x;
+    const int lane = (int)(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    float4 *stage = s_stage[wave];
     const int ti = (int)(tile % g.tx);
     const int tj = (int)((tile / g.tx) % g.ty);
     const int tk = (int)(tile / ((int64_t)g.tx * g.ty));
@@ -203,16 +236,18 @@ __global__ __launch_bounds__(64) void k_voxelize(const NodeRec *__restrict__ nod
     uint32_t head = 0, tail = 0;   // ring positions (wave-uniform)
     int64_t total = 0;
 
-    // Evaluate the next m (<= 64) members of the ring against this lane's
-    // column and drop them from the ring.
-    auto flush = [&](uint32_t m) {
+    // Evaluate the next m (<= kThreads) members of the ring against this lane's
+    // column, each wave its share, and drop them from the ring.
+    auto flush = [&](uint32_t all) {
         if (MODE == 1) {
-            total += m;
-            head += m;
+            total += all;
+            head += all;
             return;
         }
+        const uint32_t share = (all + WAVES - 1) / WAVES, from = share * (uint32_t)wave;
+        const uint32_t m = all > from ? min(share, all - from) : 0u;
         if ((uint32_t)lane < m) {
-            const GaussRec r = recs[ring[(head + lane) & (kRing - 1)]];
+            const GaussRec r = recs[ring[(head + from + lane) & (kSlots - 1)]];
             const float M[9] = {r.r1.x * hf, r.r1.y * hf, r.r1.z * hf, r.r1.w * hf, r.r2.x * hf,
                                 r.r2.y * hf, r.r2.z * hf, r.r2.w * hf, r.r3.x * hf};
             const double c0 = ((double)r.r0.x - v0x) * inv_h;
@@ -227,7 +262,7 @@ __global__ __launch_bounds__(64) void k_voxelize(const NodeRec *__restrict__ nod
             stage[4 * lane + 2] = make_float4(M[6], M[7], M[8], a[2]);
             stage[4 * lane + 3] = make_float4(r.r0.w, 0.0f, 0.0f, 0.0f);
         }
-        __syncthreads();
+        wave_lds_fence();
         for (uint32_t r = 0; r < m; ++r) {
             const float4 s0 = stage[4 * r + 0], s1 = stage[4 * r + 1], s2 = stage[4 * r + 2];
             const float A = stage[4 * r + 3].x;
@@ -236,73 +271,89 @@ __global__ __launch_bounds__(64) void k_voxelize(const NodeRec *__restrict__ nod
             const float b1 = fmaf(s1.y, py, fmaf(s1.z, pz, -s1.w));
             const float b2 = fmaf(s2.y, py, fmaf(s2.z, pz, -s2.w));
 #pragma unroll
-            for (int x = 0; x < kVoxTile; ++x) {
-                const float u0 = fmaf(s0.x, (float)x, b0);
-                const float u1 = fmaf(s1.x, (float)x, b1);
-                const float u2 = fmaf(s2.x, (float)x, b2);
-                const float q = fmaf(u0, u0, fmaf(u1, u1, u2 * u2));
-                if (q <= kQSkip) {
-                    const float w = __builtin_amdgcn_exp2f(-q);
-                    acc[x] += (uint32_t)fmaf(w, A, 0.5f);
+            for (int x0 = 0; x0 < kVoxTile; x0 += kSkipRun) {
+                float q[kSkipRun], least = INFINITY;
+#pragma unroll
+                for (int k = 0; k < kSkipRun; ++k) {
+                    const int x = x0 + k;
+                    const float u0 = x ? fmaf(s0.x, (float)x, b0) : b0;
+                    const float u1 = x ? fmaf(s1.x, (float)x, b1) : b1;
+                    const float u2 = x ? fmaf(s2.x, (float)x, b2) : b2;
+                    q[k] = fmaf(u0, u0, fmaf(u1, u1, u2 * u2));
+                    least = fminf(least, q[k]);
+                }
+                // terms with q > 33 (or no number) round to 0: left out where
+                // that holds in every lane (of a launch that VALU issue
+                // bounds), added elsewhere
+                if (WAVES > 1 || __ballot(least <= kQSkip)) {
+#pragma unroll
+                    for (int k = 0; k < kSkipRun; ++k)
+                        acc[x0 + k] += (uint32_t)fmaf(__builtin_amdgcn_exp2f(-q[k]), A, 0.5f);
                 }
             }
         }
-        __syncthreads();
-        head += m;
+        wave_lds_fence();
+        head += all;
     };
 
-    // Append the leaves among this lane's two children to the ring
-    // (ballot compaction; the order within a step is irrelevant).
-    auto append = [&](bool ll, int32_t cl, bool lr, int32_t cr) {
-        const uint64_t bl = __ballot(ll), br = __ballot(lr);
-        if (ll) ring[(tail + below(bl, lane)) & (kRing - 1)] = ~cl;
-        if (lr) ring[(tail + (uint32_t)__popcll(bl) + below(br, lane)) & (kRing - 1)] = ~cr;
-        tail += (uint32_t)(__popcll(bl) + __popcll(br));
+    auto sync = [&]() {
+        if (WAVES > 1) __syncthreads();
+        else wave_lds_fence();
     };
-
     if (n_gauss == 1) {
         if (meets(boxes[0], boxes[3], boxes[1], boxes[4], boxes[2], boxes[5], tb)) {
-            if (lane == 0) ring[0] = 0;
+            if (threadIdx.x == 0) ring[0] = 0;
             tail = 1;
         }
-        __syncthreads();
+        sync();
     } else if (n_gauss > 1) {
-        // breadth-first from the root while fewer than 64 nodes are pending
-        int nf = 1;
-        if (lane == 0) front[0] = 0;
-        __syncthreads();
-        while (nf > 0 && nf < 64) {
-            const int32_t node = lane < nf ? front[lane] : -1;
-            __syncthreads();
+        // as many nodes as threads off the top of the stack at a time; near its
+        // end fewer, down to one, which never needs more than the tree's depth
+        // beyond what is there
+        int top = 1, step = 0;
+        if (threadIdx.x == 0) stack[0] = 0;
+        sync();
+        while (top > 0) {
+            const int room = kNodes - kDepth - top;
+            const int k = min(min(kThreads, top), max(1, room));
+            const int32_t node = (int)threadIdx.x < k ? stack[top - 1 - (int)threadIdx.x] : -1;
+            top -= k;
             int32_t cl = 0, cr = 0;
             bool hl = false, hr = false;
             if (node >= 0) test_children(nodes, node, tb, cl, cr, hl, hr);
-            append(hl && cl < 0, cl, hr && cr < 0, cr);
-            const bool il = hl && cl >= 0, ir = hr && cr >= 0;
+            // children that are leaves go to the ring, the others to the stack
+            // (ballot compaction; the order within a step is irrelevant)
+            const bool ll = hl && cl < 0, lr = hr && cr < 0, il = hl && cl >= 0, ir = hr && cr >= 0;
+            const uint64_t bll = __ballot(ll), blr = __ballot(lr);
             const uint64_t bil = __ballot(il), bir = __ballot(ir);
-            if (il) front[below(bil, lane)] = cl;
-            if (ir) front[(uint32_t)__popcll(bil) + below(bir, lane)] = cr;
-            nf = __popcll(bil) + __popcll(bir);
-            __syncthreads();
-            while (tail - head >= 64) flush(64);
-        }
-        // then one depth-first walk per lane over its (at most two) subtrees
-        int32_t stk[kDfs];
-        int sp = 0;
-        if (lane < nf) stk[sp++] = front[lane];
-        if (lane + 64 < nf) stk[sp++] = front[lane + 64];
-        while (__ballot(sp > 0)) {
-            int32_t cl = 0, cr = 0;
-            bool hl = false, hr = false;
-            if (sp > 0) {
-                const int32_t node = stk[--sp];
-                test_children(nodes, node, tb, cl, cr, hl, hr);
-                if (hl && cl >= 0 && sp < kDfs) stk[sp++] = cl;
-                if (hr && cr >= 0 && sp < kDfs) stk[sp++] = cr;
+            const uint32_t nl = (uint32_t)(__popcll(bll) + __popcll(blr));
+            const uint32_t ni = (uint32_t)(__popcll(bil) + __popcll(bir));
+            uint32_t l0 = tail, i0w = (uint32_t)top, nl_all = nl, ni_all = ni;
+            if (WAVES > 1) {
+                if (lane == 0) s_count[step & 1][wave] = nl | (ni << 16);
+                __syncthreads();               // and every node of the step is read
+                nl_all = ni_all = 0;
+                for (int w = 0; w < WAVES; ++w) {
+                    const uint32_t c = s_count[step & 1][w];
+                    if (w < wave) {
+                        l0 += c & 0xffffu;
+                        i0w += c >> 16;
+                    }
+                    nl_all += c & 0xffffu;
+                    ni_all += c >> 16;
+                }
+            } else {
+                wave_lds_fence();
             }
-            append(hl && cl < 0, cl, hr && cr < 0, cr);
-            __syncthreads();
-            while (tail - head >= 64) flush(64);
+            if (ll) ring[(l0 + below(bll, lane)) & (kSlots - 1)] = ~cl;
+            if (lr) ring[(l0 + (uint32_t)__popcll(bll) + below(blr, lane)) & (kSlots - 1)] = ~cr;
+            if (il) stack[i0w + below(bil, lane)] = cl;
+            if (ir) stack[i0w + (uint32_t)__popcll(bil) + below(bir, lane)] = cr;
+            tail += nl_all;
+            top += (int)ni_all;
+            ++step;
+            sync();
+            while (tail - head >= (uint32_t)kThreads) flush(kThreads);
         }
     }
     if (tail > head) flush(tail - head);
@@ -311,16 +362,30 @@ __global__ __launch_bounds__(64) void k_voxelize(const NodeRec *__restrict__ nod
         if (lane == 0) counts[tile] = (int32_t)total;
         return;
     }
-    const int y = j0 + cy, z = k0 + cz;
-    if (y < je && z < ke) {
-        const int64_t row = ((int64_t)z * g.ny + y) * g.nx;
+    if (WAVES > 1) {
+        // each wave adds up and writes its share of the columns' voxels
+        uint64_t *sums = reinterpret_cast<uint64_t *>(stage);
+        static_assert(sizeof s_stage[0] == 8 * 64 * sizeof(uint64_t), "a wave's sums fit its stage");
 #pragma unroll
-        for (int x = 0; x < kVoxTile; ++x) {
-            if (i0 + x < ie) {
-                const float d = (float)((double)acc[x] * (1.0 / kFix));
-                if (density) density[row + i0 + x] = d;
-                if (occ) occ[row + i0 + x] = d > g.theta ? 1 : 0;
-            }
+        for (int k = 0; k < 8; ++k) sums[64 * k + lane] = acc[k];
+        __syncthreads();
+    }
+    const uint64_t *all = reinterpret_cast<const uint64_t *>(s_stage);
+    const int y = j0 + cy, z = k0 + cz;
+    if (y >= je || z >= ke) return;
+    const int64_t row = ((int64_t)z * g.ny + y) * g.nx;
+#pragma unroll
+    for (int x = 0; x < kVoxTile; ++x) {
+        if (WAVES > 1 && x % WAVES != wave) continue;
+        uint64_t sum = acc[x];
+        if (WAVES > 1) {
+            sum = 0;
+            for (int w = 0; w < WAVES; ++w) sum += all[8 * 64 * w + 64 * x + lane];
+        }
+        if (i0 + x < ie) {
+            const float d = (float)((double)sum * (1.0 / kFix));
+            if (density) density[row + i0 + x] = d;
+            if (occ) occ[row + i0 + x] = d > g.theta ? 1 : 0;
         }
     }
 }
@@ -360,6 +425,44 @@ __global__ __launch_bounds__(kBlock) void k_surface(const uint8_t *__restrict__ 
         }
         surf[i] = s;
     }
+}
+
+// The same for rows of 16 voxels and more, 16 per thread: the five rows' bytes
+// (0 or 1) as four words each, the x neighbours by byte shifts, one store.  A
+// row's last thread takes its last 16 voxels, some of them its neighbour's too
+// (equal stores).  Bound by memory: 23 us on 33.5M voxels; four voxels a
+// thread, seven byte reads each, took 83 us.
+__global__ __launch_bounds__(kBlock) void k_surface16(const uint8_t *__restrict__ occ,
+                                                      uint8_t *__restrict__ surf, int nx, int ny,
+                                                      int nz, uint32_t n_threads, int runs,
+                                                      UDiv div_runs, UDiv div_ny)
+{
+    const uint32_t t = blockIdx.x * (uint32_t)kBlock + threadIdx.x;
+    if (t >= n_threads) return;
+    const uint32_t row = udiv32(t, div_runs);
+    int x0 = 16 * (int)(t - row * (uint32_t)runs);
+    if (x0 > nx - 16) x0 = nx - 16;
+    const uint32_t zz = udiv32(row, div_ny);
+    const int y = (int)(row - zz * (uint32_t)ny), z = (int)zz;
+    const int64_t sxy = (int64_t)nx * ny, i = (int64_t)row * nx + x0;
+    // a row outside the grid is free: read the own row in its place
+    const bool ym = y > 0, yp = y < ny - 1, zm = z > 0, zp = z < nz - 1;
+    uint32_t c[4], n[4][4];
+    __builtin_memcpy(c, occ + i, 16);
+    __builtin_memcpy(n[0], occ + (ym ? i - nx : i), 16);
+    __builtin_memcpy(n[1], occ + (yp ? i + nx : i), 16);
+    __builtin_memcpy(n[2], occ + (zm ? i - sxy : i), 16);
+    __builtin_memcpy(n[3], occ + (zp ? i + sxy : i), 16);
+    const uint32_t before = x0 > 0 ? occ[i - 1] : 0u, after = x0 + 16 < nx ? occ[i + 16] : 0u;
+    const uint32_t inside = ym && yp && zm && zp ? 0xffffffffu : 0u;
+    uint32_t out[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t l = __builtin_amdgcn_alignbyte(c[k], k ? c[k > 0 ? k - 1 : 0] : before << 24, 3u);
+        const uint32_t r = __builtin_amdgcn_alignbyte(k < 3 ? c[k < 3 ? k + 1 : 3] : after, c[k], 1u);
+        out[k] = c[k] & ~(l & r & n[0][k] & n[1][k] & n[2][k] & n[3][k] & inside);
+    }
+    __builtin_memcpy(surf + i, out, 16);
 }
 
 inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
@@ -405,11 +508,14 @@ hipError_t voxelize_launch(int mode, const NodeRec *nodes, const GaussRec *recs,
     if (g.n_tiles <= 0) return hipSuccess;
     const int64_t blocks = (g.n_tiles + 7) / 8 * 8;   // a multiple of the XCD count
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (mode == 0)
-        hipLaunchKernelGGL(k_voxelize<0>, dim3((unsigned)blocks), dim3(64), 0, s, nodes, recs,
+    if (mode != 0)
+        hipLaunchKernelGGL((k_voxelize<1, 1>), dim3((unsigned)blocks), dim3(64), 0, s, nodes, recs,
+                           boxes, n_gauss, g, density, occ, tile_counts);
+    else if (g.n_tiles <= kSharedTiles)
+        hipLaunchKernelGGL((k_voxelize<0, 4>), dim3((unsigned)blocks), dim3(256), 0, s, nodes, recs,
                            boxes, n_gauss, g, density, occ, tile_counts);
     else
-        hipLaunchKernelGGL(k_voxelize<1>, dim3((unsigned)blocks), dim3(64), 0, s, nodes, recs,
+        hipLaunchKernelGGL((k_voxelize<0, 1>), dim3((unsigned)blocks), dim3(64), 0, s, nodes, recs,
                            boxes, n_gauss, g, density, occ, tile_counts);
     return hipGetLastError();
 }
@@ -421,6 +527,14 @@ hipError_t surface_launch(const uint8_t *occ, uint8_t *surf, const VoxGrid &g, h
     const int64_t threads = (int64_t)quads * rows;
     if (threads <= 0) return hipSuccess;
     if (threads > 0xffffff00LL) return hipErrorInvalidValue;
+    if (g.nx >= 16) {
+        const int runs = (g.nx + 15) / 16;
+        const int64_t n = (int64_t)runs * rows;
+        hipLaunchKernelGGL(k_surface16, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, occ, surf,
+                           g.nx, g.ny, g.nz, (uint32_t)n, runs, udiv_magic((uint32_t)runs),
+                           udiv_magic((uint32_t)g.ny));
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_surface, dim3(grid_for(threads, kBlock)), dim3(kBlock), 0, s, occ, surf,
                        g.nx, g.ny, g.nz, (uint32_t)threads, quads, udiv_magic((uint32_t)quads),
                        udiv_magic((uint32_t)g.ny));

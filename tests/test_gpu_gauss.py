@@ -272,3 +272,39 @@ def test_invalid_inputs_are_rejected(ctx):
         ctx.build_gaussians(g, cutoff_sigma=-1.0)
     assert e.value.status == rcast.RC_E_INVAL
     ctx.release_gaussians(g)
+
+
+@pytest.mark.parametrize("dims", [(15, 9, 5), (16, 16, 8), (17, 3, 9), (31, 17, 2), (33, 8, 17)])
+def test_row_lengths_about_a_surface_run(ctx, dims):
+    # rows shorter than 16 voxels, of one run, and of runs that overlap; the
+    # mask between empty and full, so that every neighbour decides somewhere
+    rng = np.random.default_rng(sum(dims))
+    hi = tuple(0.1 * d for d in dims)
+    params = synth.random_gaussians(rng, 150, (0, 0, 0), hi, 0.02, 0.15)
+    grid = og.Grid((0, 0, 0), 0.1, dims, tile=8, theta=0.05)
+    res = run(ctx, params, grid)
+    check(params, grid, res, tag=f"{dims}")
+    assert 0 < res["surf"].sum() <= res["occ"].sum() < res["occ"].size
+    ctx.release_gaussians(res["set"])
+
+
+def test_many_tiles_equal_few(ctx):
+    # 3,600 tiles (one wave each) against the same tiles among 336 (four waves
+    # share one): a tile's members, frame and sums are the same, so are the bits;
+    # the few are checked against the oracle, with tiles of over 256 members
+    rng = np.random.default_rng(31)
+    some = synth.random_gaussians(rng, 3000, (0, 0, 0), (12, 11, 11), 0.03, 0.5)
+    dense = synth.random_gaussians(rng, 900, (1, 1, 1), (1.6, 1.6, 1.6), 0.02, 0.1)
+    params = tuple(np.concatenate([x, y]) for x, y in zip(some, dense))
+    few = og.Grid((0, 0, 0), 0.1, (64, 56, 48), tile=8, theta=0.3)
+    many = og.Grid((0, 0, 0), 0.1, (123, 118, 113), tile=8, theta=0.3)
+    a = run(ctx, params, few)
+    check(params, few, a, tag="few tiles")
+    assert a["counts"].max() > 256
+    b = run(ctx, params, many)
+    np.testing.assert_array_equal(b["counts"][:6, :7, :8], a["counts"])
+    np.testing.assert_array_equal(b["D"][:48, :56, :64].view(np.uint32), a["D"].view(np.uint32))
+    np.testing.assert_array_equal(b["occ"], (b["D"] > np.float32(0.3)).astype(np.uint8))
+    np.testing.assert_array_equal(b["surf"], og.surface(b["occ"]))
+    for r in (a, b):
+        ctx.release_gaussians(r["set"])
