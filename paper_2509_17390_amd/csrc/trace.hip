@@ -1474,14 +1474,15 @@ hipError_t launch_persistent(const TraceConfig &cfg, const DevJob *jobs, int n_j
 // us per call for indoor 18k / indoor 1.03M / terrain 3M / terrain 52k
 // triangles, rays in rows:
 //                quantised: 1 lane       4 lanes            plain: 1 lane          2 lanes             4 lanes
-//      5,760   110 152 137 116     85 102  95  81     113 157 145 121     91 118 115  96     81  98  92  80
-//    131,072   140 217 249 146    105 146 177 120     149 230 288 164    115 162 210 129    110 151 175 122
-//    262,144   127 260 247 128    131 210 177 129     147 298 259 142    125 214 204 122    129 208 176 131
-//    524,288   178 267 321 212    190 271 272 210     195 297 353 233    170 254 266 194    191 269 266 214
-//  1,048,576   232 355 394 262    296 408 455 343     249 390 440 289    239 355 409 280    297 392 461 337
-//  2,097,152   314 480 581 397    505 678 740 560     352 550 686 446    394 557 645 448    501 673 739 569
-// (262,144 is one dense frame, the others 1,024 azimuths an environment; the
-// calls' host side is some 45 us of each.)
+//      5,760    68 106  98  76     40  61  55  42      72 114 106  80     53  81  75  62     39  58  52  40
+//    131,072    96 163 213 105     68 101 125  78     109 192 247 119     78 120 165  95     66  97 121  76
+//    262,144    86 208 202  88     94 162 130  86     103 256 218 104     84 170 155  83     91 160 126  83
+//    393,216   119 213 257 146    133 202 207 138     137 225 297 156    114 190 212 122    127 192 196 136
+//    524,288   129 228 273 176    158 243 244 171     152 251 304 195    127 218 225 151    153 237 237 166
+//  1,048,576   182 307 344 217    270 404 466 319     204 344 390 248    198 323 373 244    261 389 454 313
+//  2,097,152   270 438 536 349    497 747 812 581     311 501 635 400    337 528 610 411    484 717 787 570
+// (262,144 is one dense frame, the others 1,024 azimuths an environment; some
+// 15 us of each are the call's host side.)
 constexpr int64_t kFourLaneRays = 3 << 17;
 constexpr int64_t kTwoLaneRays = 3 << 19;   // plain nodes
 

@@ -895,11 +895,17 @@ rc_status rc_decimate(rc_ctx *c, const float *verts, int64_t nv, const int32_t *
     ws.take(&partial, sizeof(float) * 6 * kMinmaxBlocks);
     ws.take(&box, sizeof(float) * 8);
     ws.take(&lo, sizeof(double) * 4);
-    ws.take(&sortws, radix_sort_ws_bytes(nv));
     ws.take(&cpart, count_kept_ws_bytes());
     ws.take(&flags, sizeof(int32_t));
     rc_status st = ws.commit();
     if (st != RC_OK) return st;
+    // the sorts run when the incidence lists (and, of a few vertices, the box's
+    // parts) are done with
+    const size_t sort_bytes = radix_sort_ws_bytes(nv);
+    static_assert(sizeof(float) * 6 * kMinmaxBlocks >= 6144, "holds the sort of one tile");
+    if (sizeof(int32_t) * kNbrCap * (size_t)nv >= sort_bytes) sortws = reinterpret_cast<char *>(slots);
+    else if (sizeof(float) * 6 * kMinmaxBlocks >= sort_bytes) sortws = reinterpret_cast<char *>(partial);
+    else return fail(RC_E_DEVICE, "sort workspace");
     int32_t hf = 0;
     HIP_TRY(hipMemsetAsync(flags, 0, sizeof(int32_t), s));
     HIP_TRY(validate_mesh_launch(verts, nv, tris, nt, flags, s));
