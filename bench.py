@@ -889,7 +889,7 @@ def ingest(spec):
 
         def window(d):
             ids = sorted(d)
-            a = max(i for i in ids if "k_smooth" in d[i][0])
+            a = max(i for i in ids if "k_pack_bits" in d[i][0])
             b = next(i for i in ids if i > a and "k_mc_emit" in d[i][0])
             return [i for i in ids if a <= i <= b]
         wf, ww = window(fetch), window(write)
@@ -1339,21 +1339,19 @@ MIN_COMPONENT_FACES = 32
 # Narrow-band TSDF + marching cubes: HBM bytes per voxel of each pass as
 # built (reads + writes of the dense arrays; neighbour and tile-halo
 # re-reads hit the caches): for kernels of 1 to 3 steps (as here) and the
-# fixed threshold one tiled pass from the mask to V~ and the packed free
-# bits (else smoothing u8 -> u8 -> u16 -> V~ and the packing to 2-bit
-# labels as passes of their own), then for bands of at most
-# 4 shells one tiled pass from V~ and the outside bits to phi float32 (S_0
-# and the shells stay in LDS; wider bands: S_0 and each shell as byte
-# passes, then phi), the marching-cubes count writing mask and case bytes,
-# the tile scan forming both counts from those bytes and writing each
-# point's u16 vertex offset within its tile, and the emit pass reading mask
-# and case (the surface points' outputs are counted separately)
+# fixed threshold the mask is packed to bits and smoothed bit-sliced into the
+# free and outside words (else smoothing u8 -> u32 -> u64 -> V~ and the packing
+# as passes of their own), then for bands of at most 4 shells one pass from
+# those words to phi float32 (wider bands: S_0 and each shell as byte passes,
+# then phi); marching cubes reads phi into inside bits, the count writes 41
+# bytes for a word of 64 points that has vertices (all of them, here), and the
+# emit pass reads them (the surface points' outputs are counted separately)
 TSDF_PASS_BYTES = {
-    "smooth_pack_tiled": 1 + 1 + 0.25,
-    "smooth_x": 1 + 1, "smooth_y": 1 + 2, "smooth_z": 2 + 1, "pack": 1 + 0.25,
-    "flood_sweep": 0.375, "shells_phi_tiled": 1 + 0.125 + 4,
+    "pack_mask": 1 + 0.125, "smooth_bits": 0.125 + 0.25,
+    "smooth_x": 1 + 4, "smooth_y": 4 + 8, "smooth_z": 8 + 1, "pack": 1 + 0.25,
+    "flood_sweep": 0.375, "shells_phi_bits": 0.25 + 4,
     "shell0": 1 + 1, "shell": 1 + 1, "phi": 1 + 0.125 + 4,
-    "mc_count": 4 + 1 + 1, "mc_scans": 1 + 1 + 2, "mc_emit": 1 + 1,
+    "mc_inside": 4 + 0.125, "mc_count": 0.125 + 0.64, "mc_emit": 0.125 + 0.64,
 }
 
 
@@ -1361,13 +1359,13 @@ def tsdf_bytes_per_voxel(shells: int, steps: int, quantile: bool = False) -> flo
     """Bytes per voxel of TSDF_PASS_BYTES for a band of `shells` shells and a
     smoothing kernel of `steps` steps."""
     b = TSDF_PASS_BYTES
-    total = b["flood_sweep"] + b["mc_count"] + b["mc_scans"] + b["mc_emit"]
+    total = b["flood_sweep"] + b["mc_inside"] + b["mc_count"] + b["mc_emit"]
     if 1 <= steps <= 3 and not quantile:
-        total += b["smooth_pack_tiled"]
+        total += b["pack_mask"] + b["smooth_bits"]
     else:
         total += b["smooth_x"] + b["smooth_y"] + b["smooth_z"] + b["pack"]
     if shells <= 4:
-        return total + b["shells_phi_tiled"]
+        return total + b["shells_phi_bits"]
     return total + b["shell0"] + shells * b["shell"] + b["phi"]
 
 

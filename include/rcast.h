@@ -548,9 +548,10 @@ typedef struct {
 /* TSDF of the DEVICE uint8 surface mask `surf` [nz][ny][nx] into the DEVICE
  * float32 `out_phi` (same layout); `out_vtilde` (DEVICE uint8, or NULL)
  * receives V~.  Runs on `stream` and returns when phi is complete (the
- * outside labelling repeats until it settles, reading a flag each round).
- * Scratch device memory of about 14 bytes per voxel (22 with the quantile
- * re-threshold, which keeps the smoothing's integer sums) is kept by the context
+ * outside labelling repeats until it settles, reading a flag per 4 to 8
+ * rounds).  Scratch device memory of about 0.5 bytes per voxel (14 with more
+ * than 3 smoothing steps or 4 shells, 22 with the quantile re-threshold, which
+ * keeps the smoothing's integer sums) is kept by the context
  * (grown on demand, reused by later calls, freed by rc_destroy).
  * Errors: RC_E_INVAL (grid, options), RC_E_NOMEM, RC_E_DEVICE. */
 rc_status rc_tsdf(rc_ctx *ctx, const rc_grid *grid, const uint8_t *surf,
@@ -567,7 +568,7 @@ rc_status rc_tsdf(rc_ctx *ctx, const rc_grid *grid, const uint8_t *surf,
  * difference, one-sided on the grid's faces, interpolated along the
  * vertex's edge like its position; they point toward growing phi, out of
  * the solid; (0, 0, 0) where the gradient vanishes.  Synchronous.  Scratch
- * of about 4 bytes per voxel is kept by the context like rc_tsdf's.  Grids
+ * of about 0.8 bytes per voxel is kept by the context like rc_tsdf's.  Grids
  * up to 2^29 voxels.
  * Errors: RC_E_INVAL, RC_E_NOMEM (capacity too small: sizes still written),
  * RC_E_DEVICE. */
