@@ -550,7 +550,7 @@ typedef struct {
  * receives V~.  Runs on `stream` and returns when phi is complete (the
  * outside labelling repeats until it settles, reading a flag per 4 to 8
  * rounds).  Scratch device memory of about 0.5 bytes per voxel (14 with more
- * than 3 smoothing steps or 4 shells, 22 with the quantile re-threshold, which
+ * than 3 smoothing steps or 4 shells, 21 to 23 with the quantile re-threshold, which
  * keeps the smoothing's integer sums) is kept by the context
  * (grown on demand, reused by later calls, freed by rc_destroy).
  * Errors: RC_E_INVAL (grid, options), RC_E_NOMEM, RC_E_DEVICE. */

@@ -38,11 +38,12 @@ size_t tsdf_smooth_b_bytes(const TsdfGrid &g);
 hipError_t tsdf_smooth_launch(const uint8_t *surf, uint32_t *a, uint64_t *b, uint8_t *vt,
                               const TsdfGrid &g, const Binomial &w, uint64_t thr, hipStream_t s);
 // The integer sums of the same smoothing ([nz][ny][nx] uint64), and V~ =
-// [sums >= *thr] with thr on the device (the quantile re-threshold).
+// [sums >= *thr] with thr on the device (the quantile re-threshold) as free
+// and cleared outside words, and bytes (vt; null: not wanted).
 hipError_t tsdf_smooth_sums_launch(const uint8_t *surf, uint32_t *a, uint64_t *b, uint64_t *sums,
                                    const TsdfGrid &g, const Binomial &w, hipStream_t s);
-hipError_t tsdf_threshold_launch(const uint64_t *sums, const uint64_t *thr, uint8_t *vt,
-                                 int64_t n, hipStream_t s);
+hipError_t tsdf_threshold_pack_launch(const uint64_t *sums, const uint64_t *thr, uint8_t *vt,
+                                      uint64_t *F, uint64_t *O, const TsdfGrid &g, hipStream_t s);
 // phi at every step-th lattice point of each axis ([mz][my][mx], m = (n - 1)
 // / step + 1 per axis) into out.
 hipError_t mc_stride_gather_launch(const float *phi, const TsdfGrid &g, int step, int mx, int my,
@@ -81,7 +82,8 @@ hipError_t tsdf_shells_phi_launch(const uint8_t *vt, const uint64_t *O, uint8_t 
 
 // Marching cubes: the case table (count[256], tri[256][15] edge ids, -1
 // padded), the count pass into the buffers below, and the emit pass (normals:
-// float32 [nv][3] or null).
+// float32 [nv][3] or null), which writes nothing if the totals are beyond the
+// capacity.
 void mc_table_copy(uint8_t *count, int8_t *tri);
 int64_t mc_words(int64_t n);        // words of 64 points
 int64_t mc_blocks(int64_t n);       // count blocks
@@ -100,8 +102,9 @@ struct McBuffers {
 hipError_t mc_count_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
                            const McBuffers &b, hipStream_t s);
 hipError_t mc_emit_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
-                          const int8_t *tris_of, const McBuffers &b, uint32_t ngroups,
-                          float *verts, int32_t *tris, float *normals, hipStream_t s);
+                          const int8_t *tris_of, const McBuffers &b, uint32_t cap_verts,
+                          uint32_t cap_tris, float *verts, int32_t *tris, float *normals,
+                          hipStream_t s);
 // Entries of the sums array of scan_u32_launch.
 int64_t mc_scan_sums_len(int64_t n);
 

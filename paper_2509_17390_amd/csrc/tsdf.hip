@@ -126,14 +126,6 @@ __global__ __launch_bounds__(kBlock) void k_smooth_z_sum(const uint64_t *__restr
     out[i] = s;
 }
 
-__global__ __launch_bounds__(kBlock) void k_threshold_sums(const uint64_t *__restrict__ sums,
-                                                           const uint64_t *__restrict__ thr,
-                                                           uint8_t *__restrict__ vt, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) vt[i] = sums[i] >= *thr ? 1 : 0;
-}
-
 // Tile number of a block, consecutive tiles on one XCD (workgroups go to the 8
 // XCDs in turn): neighbouring tiles share lines of packed words in its L2.
 __device__ __forceinline__ uint32_t xcd_tile()
@@ -219,6 +211,49 @@ __global__ __launch_bounds__(kBlock) void k_pack_bits(const uint8_t *__restrict_
         if ((part & 1) == 0 && w < nw) {
             reinterpret_cast<uint32_t *>(bits)[2 * w + (part >> 1)] = m;
             if (FREE) reinterpret_cast<uint32_t *>(O)[2 * w + (part >> 1)] = 0;
+        }
+    }
+}
+
+// V~ = [sums >= *thr] as free words (and bytes, if asked for), with clear
+// outside words: a ballot a word, kPackSums words' reads in flight.  (Bytes and
+// a packing launch behind them took 4 + 7 us on 350,200 voxels, this 4.)
+constexpr int kPackSums = 4;
+
+__global__ __launch_bounds__(kBlock) void k_threshold_pack(const uint64_t *__restrict__ sums,
+                                                           const uint64_t *__restrict__ thr,
+                                                           uint8_t *__restrict__ vt, TsdfGrid g,
+                                                           int W, uint64_t *__restrict__ F,
+                                                           uint64_t *__restrict__ O)
+{
+    const int64_t w0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * kPackSums;
+    const int64_t nw = (int64_t)W * g.ny * g.nz;
+    if (w0 >= nw) return;                                 // whole waves
+    const int lane = (int)(threadIdx.x & 63);
+    const uint64_t t = *thr;
+    int64_t row = w0 / W, at[kPackSums];
+    int wx = (int)(w0 - row * W);
+    uint64_t v[kPackSums];
+    bool ok[kPackSums];
+#pragma unroll
+    for (int k = 0; k < kPackSums; ++k) {
+        const int x = 64 * wx + lane;
+        ok[k] = w0 + k < nw && x < g.nx;
+        at[k] = ok[k] ? row * g.nx + x : 0;
+        v[k] = sums[at[k]];
+        if (++wx == W) {
+            wx = 0;
+            ++row;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPackSums; ++k) {
+        const bool one = v[k] >= t;
+        const uint64_t f = __ballot(ok[k] && !one);
+        if (vt && ok[k]) vt[at[k]] = one ? 1 : 0;
+        if (lane == 0 && w0 + k < nw) {
+            F[w0 + k] = f;
+            O[w0 + k] = 0;
         }
     }
 }
@@ -1161,7 +1196,7 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t v, uint32_t *total)
 // byte and one 16-bit vertex offset a point, written, scanned and read again,
 // took 137 + 35 + 26 us and 142 us in the emission on 34.2M points with 1.7M
 // vertices; these take 26 + 21 + 8 us, the first at the rate of a copy, and
-// 104 us.)
+// 93 us.)
 struct __align__(16) McWord {
     uint64_t e[3];    // points whose +x / +y / +z edge is crossed
     uint32_t v, t;    // vertices and triangles of the block's earlier words
@@ -1501,10 +1536,14 @@ __device__ __forceinline__ void mc_emit_tri(const int8_t *__restrict__ tris_of,
 // active cells, and the triangles of 64 cells at a time as items in LDS, and
 // each lane emits one item at a time: every lane runs the same code on every
 // item, and no wave waits for another.  Bound by VALU issue and by the chain
-// of a wave's reads: 104 us on 1.7M vertices and 3.4M triangles (142 us with
+// of a wave's reads: 93 us on 1.7M vertices and 3.4M triangles (142 us with
 // blocks of 1,024 points).
 constexpr int kMcEmitWords = (int)(kMcGroup / kMcMinWeight), kMcEmitWaves = kBlock / 64;
-constexpr int kMcSlice = kMcEmitWords;                                    // points of a lane
+constexpr int kMcSlice = kMcEmitWords;        // points of a lane
+// Blocks of the emission, each over several groups where there are more: the
+// host does not know the number of groups when it enqueues them.  (1.7M
+// vertices: 93 us; 1,280 blocks 100, 2,048 103.)
+constexpr unsigned kMcEmitBlocks = 4096;
 
 __device__ __forceinline__ uint32_t wave_scan_excl(uint32_t v, int lane, uint32_t &tot)
 {
@@ -1527,7 +1566,8 @@ __device__ __forceinline__ void wave_lds_fence()
 
 __global__ __launch_bounds__(kBlock) void k_mc_emit(const float *__restrict__ phi, TsdfGrid g,
                                                     float iso, int64_t nw, uint32_t nb,
-                                                    uint32_t ngroups,
+                                                    const uint32_t *__restrict__ totals,
+                                                    uint32_t cap_v, uint32_t cap_t,
                                                     const uint8_t *__restrict__ ntri,
                                                     const int8_t *__restrict__ tris_of,
                                                     const uint64_t *__restrict__ inside,
@@ -1560,119 +1600,124 @@ __global__ __launch_bounds__(kBlock) void k_mc_emit(const float *__restrict__ ph
     __shared__ uint8_t nt_lds[256];
     // the case table's triangle edges (256 x 15 bytes, word aligned)
     __shared__ uint32_t tri_lds[256 * 15 / 4];
+    // the caller's capacity: the host reads the totals behind this launch
+    const uint32_t ngroups = totals[2];
+    if (totals[0] > cap_v || totals[1] > cap_t) return;
     nt_lds[threadIdx.x] = ntri[threadIdx.x];              // kBlock == 256 cases
     for (int k = threadIdx.x; k < 256 * 15 / 4; k += kBlock)
         tri_lds[k] = reinterpret_cast<const uint32_t *>(tris_of)[k];
     __syncthreads();
     const int lane = (int)(threadIdx.x & 63), wv = (int)(threadIdx.x >> 6);
     const int wi = lane / WL, part_w = lane % WL, b0 = part_w * kMcSlice;
-    const uint32_t grp = blockIdx.x * kMcEmitWaves + wv;
-    if (grp >= ngroups) return;                           // whole waves
-    // the count block: the last whose first group is not beyond grp, by a
-    // search of 64 places at a time
-    uint32_t blk = 0;
-    for (uint32_t span = nb; span > 1;) {
-        const uint32_t step = (span + 63u) / 64u, at = blk + lane * step;
-        const bool le = lane * step < span && gbase[at] <= grp;
-        const uint32_t top = 63u - (uint32_t)__builtin_clzll(__ballot(le));   // lane 0 always
-        blk += top * step;
-        span = span - top * step < step ? span - top * step : step;
-    }
-    const uint32_t gk = grp - gbase[blk], nl = nlist[blk];
-    const uint32_t gn = blk + 1 < nb ? gbase[blk + 1] - gbase[blk] : ngroups - gbase[blk];
-    const uint8_t *gs = group + (int64_t)blk * kMcWords + gk;
-    const uint32_t l = gs[0] + (uint32_t)wi, lend = gk + 1 < gn ? gs[1] : nl;
-    const uint32_t vb = vbase[blk], tb = tbase[blk];
     const int64_t sxy = (int64_t)g.nx * g.ny;
     const uint32_t off_bits[4] = {0u, (uint32_t)g.nx & 63u, (uint32_t)(sxy & 63),
                                   (uint32_t)((sxy + g.nx) & 63)};
-    uint32_t e[3] = {0, 0, 0}, act = 0, v0 = 0, t0 = 0;
-    int64_t w = 0;
-    if (l < lend) {
-        w = (int64_t)blk * kMcWords + list[(int64_t)blk * kMcWords + l];
-        const McWord m = words[w];
-        const uint32_t low = (uint32_t)((1ull << kMcSlice) - 1ull);
-        v0 = vb + m.v;
-        t0 = tb + m.t;
-        for (int a = 0; a < 3; ++a) e[a] = (uint32_t)(m.e[a] >> b0) & low;
-        act = (uint32_t)(cells[w] >> b0) & low;
-        const int o = part_w >> 1;
-        const int64_t off = (o & 1 ? (int64_t)g.nx : 0) + (o & 2 ? sxy : 0);
-        const int64_t q = w + (off >> 6) + (part_w & 1);
-        if (q < nw) {                  // a word without vertices is not named
-            const McWord mq = words[q];
-            McCorner &k = s_k[wv][wi][part_w];
-            for (int a = 0; a < 3; ++a) k.e[a] = mq.e[a];
-            k.id = vbase[q / kMcWords] + mq.v;
+    for (uint32_t grp = blockIdx.x * kMcEmitWaves + wv; grp < ngroups;
+         grp += gridDim.x * kMcEmitWaves) {
+        // the count block: the last whose first group is not beyond grp, by a
+        // search of 64 places at a time
+        uint32_t blk = 0;
+        for (uint32_t span = nb; span > 1;) {
+            const uint32_t step = (span + 63u) / 64u, at = blk + lane * step;
+            const bool le = lane * step < span && gbase[at] <= grp;
+            const uint32_t top = 63u - (uint32_t)__builtin_clzll(__ballot(le));   // lane 0 always
+            blk += top * step;
+            span = span - top * step < step ? span - top * step : step;
         }
-        if ((part_w & 1) == 0) {
-            uint64_t u, v;
-            corner_words(inside, nw, w, off, u, v);
-            s_c[wv][wi][2 * o] = u;
-            s_c[wv][wi][2 * o + 1] = v;
+        const uint32_t gk = grp - gbase[blk], nl = nlist[blk];
+        const uint32_t gn = blk + 1 < nb ? gbase[blk + 1] - gbase[blk] : ngroups - gbase[blk];
+        const uint8_t *gs = group + (int64_t)blk * kMcWords + gk;
+        const uint32_t l = gs[0] + (uint32_t)wi, lend = gk + 1 < gn ? gs[1] : nl;
+        const uint32_t vb = vbase[blk], tb = tbase[blk];
+        uint32_t e[3] = {0, 0, 0}, act = 0, v0 = 0, t0 = 0;
+        int64_t w = 0;
+        if (l < lend) {
+            w = (int64_t)blk * kMcWords + list[(int64_t)blk * kMcWords + l];
+            const McWord m = words[w];
+            const uint32_t low = (uint32_t)((1ull << kMcSlice) - 1ull);
+            v0 = vb + m.v;
+            t0 = tb + m.t;
+            for (int a = 0; a < 3; ++a) e[a] = (uint32_t)(m.e[a] >> b0) & low;
+            act = (uint32_t)(cells[w] >> b0) & low;
+            const int o = part_w >> 1;
+            const int64_t off = (o & 1 ? (int64_t)g.nx : 0) + (o & 2 ? sxy : 0);
+            const int64_t q = w + (off >> 6) + (part_w & 1);
+            if (q < nw) {                  // a word without vertices is not named
+                const McWord mq = words[q];
+                McCorner &k = s_k[wv][wi][part_w];
+                for (int a = 0; a < 3; ++a) k.e[a] = mq.e[a];
+                k.id = vbase[q / kMcWords] + mq.v;
+            }
+            if ((part_w & 1) == 0) {
+                uint64_t u, v;
+                corner_words(inside, nw, w, off, u, v);
+                s_c[wv][wi][2 * o] = u;
+                s_c[wv][wi][2 * o + 1] = v;
+            }
         }
-    }
-    // at most 3 PTS vertices and PTS cells
-    uint32_t tot;
-    const uint32_t r = wave_scan_excl((uint32_t)(__popc(e[0]) + __popc(e[1]) + __popc(e[2])) |
-                                          ((uint32_t)__popc(act) << 16), lane, tot);
-    const uint32_t nv = tot & 0xffffu, nc = tot >> 16;
-    uint32_t rv = r & 0xffffu, rc = r >> 16;
-    if (part_w == 0) {
-        s_base[wv][wi] = 64 * w;
-        s_v[wv][wi] = v0 - rv;
-    }
-    uint32_t todo = e[0] | e[1] | e[2];
-    while (todo) {
-        const int b = __builtin_ctz(todo);
-        todo &= todo - 1;
-        const uint32_t pt = (uint32_t)(lane * kMcSlice + b);
+        // at most 3 PTS vertices and PTS cells
+        uint32_t tot;
+        const uint32_t r = wave_scan_excl((uint32_t)(__popc(e[0]) + __popc(e[1]) + __popc(e[2])) |
+                                              ((uint32_t)__popc(act) << 16), lane, tot);
+        const uint32_t nv = tot & 0xffffu, nc = tot >> 16;
+        uint32_t rv = r & 0xffffu, rc = r >> 16;
+        if (part_w == 0) {
+            s_base[wv][wi] = 64 * w;
+            s_v[wv][wi] = v0 - rv;
+        }
+        uint32_t todo = e[0] | e[1] | e[2];
+        while (todo) {
+            const int b = __builtin_ctz(todo);
+            todo &= todo - 1;
+            const uint32_t pt = (uint32_t)(lane * kMcSlice + b);
 #pragma unroll
-        for (uint32_t a = 0; a < 3; ++a)
-            if ((e[a] >> b) & 1u) s_item[wv][rv++] = (uint16_t)(pt | (a << 10));
-    }
-    wave_lds_fence();
-    for (uint32_t j = lane; j < nv; j += 64) {
-        const uint32_t it = s_item[wv][j], pt = it & 1023u;
-        mc_emit_vertex(phi, g, iso, verts, normals, s_base[wv][pt >> 6] + (pt & 63u),
-                       (int)(it >> 10), s_v[wv][pt >> 6] + j);
-    }
-    wave_lds_fence();
-    const bool first = part_w == 0;
-    uint32_t word_c0 = rc;      // place of the word's first cell (first lanes)
-    while (act) {
-        const int b = __builtin_ctz(act);
-        act &= act - 1;
-        s_item[wv][rc++] = (uint16_t)(lane * kMcSlice + b);
-    }
-    wave_lds_fence();
-    uint32_t done = 0;          // triangles of earlier cells
-    for (uint32_t j0 = 0; j0 < nc; j0 += 64) {
-        const uint32_t j = j0 + lane;
-        uint32_t n = 0;
-        if (j < nc) {
-            const uint32_t pt = s_item[wv][j];
-            uint32_t cs = 0;
+            for (uint32_t a = 0; a < 3; ++a)
+                if ((e[a] >> b) & 1u) s_item[wv][rv++] = (uint16_t)(pt | (a << 10));
+        }
+        wave_lds_fence();
+        for (uint32_t j = lane; j < nv; j += 64) {
+            const uint32_t it = s_item[wv][j], pt = it & 1023u;
+            mc_emit_vertex(phi, g, iso, verts, normals, s_base[wv][pt >> 6] + (pt & 63u),
+                           (int)(it >> 10), s_v[wv][pt >> 6] + j);
+        }
+        wave_lds_fence();
+        const bool first = part_w == 0;
+        uint32_t word_c0 = rc;      // place of the word's first cell (first lanes)
+        while (act) {
+            const int b = __builtin_ctz(act);
+            act &= act - 1;
+            s_item[wv][rc++] = (uint16_t)(lane * kMcSlice + b);
+        }
+        wave_lds_fence();
+        uint32_t done = 0;          // triangles of earlier cells
+        for (uint32_t j0 = 0; j0 < nc; j0 += 64) {
+            const uint32_t j = j0 + lane;
+            uint32_t n = 0;
+            if (j < nc) {
+                const uint32_t pt = s_item[wv][j];
+                uint32_t cs = 0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-                cs |= (uint32_t)((s_c[wv][pt >> 6][k] >> (pt & 63u)) & 1ull) << k;
-            s_cell[wv][lane] = pt | (cs << 10);
-            n = nt_lds[cs];
+                for (int k = 0; k < 8; ++k)
+                    cs |= (uint32_t)((s_c[wv][pt >> 6][k] >> (pt & 63u)) & 1ull) << k;
+                s_cell[wv][lane] = pt | (cs << 10);
+                n = nt_lds[cs];
+            }
+            uint32_t nt;
+            const uint32_t rt = wave_scan_excl(n, lane, nt);
+            for (uint32_t k = 0; k < n; ++k) s_tri[wv][rt + k] = (uint16_t)(lane | (k << 6));
+            // the triangles before a word's first cell, if it lies in these 64
+            const uint32_t at = __shfl(rt, (int)((word_c0 - j0) & 63u), 64);
+            if (first && word_c0 - j0 < 64u) s_t[wv][wi] = t0 - (done + at);
+            wave_lds_fence();
+            for (uint32_t q = lane; q < nt; q += 64) {
+                const uint32_t it = s_tri[wv][q], cc = s_cell[wv][it & 63u], pt = cc & 1023u;
+                mc_emit_tri(reinterpret_cast<const int8_t *>(tri_lds), s_k[wv][pt >> 6], off_bits, tris,
+                            pt & 63u, (int)(cc >> 10), (int)(it >> 6), s_t[wv][pt >> 6] + done + q);
+            }
+            done += nt;
+            wave_lds_fence();
         }
-        uint32_t nt;
-        const uint32_t rt = wave_scan_excl(n, lane, nt);
-        for (uint32_t k = 0; k < n; ++k) s_tri[wv][rt + k] = (uint16_t)(lane | (k << 6));
-        // the triangles before a word's first cell, if it lies in these 64
-        const uint32_t at = __shfl(rt, (int)((word_c0 - j0) & 63u), 64);
-        if (first && word_c0 - j0 < 64u) s_t[wv][wi] = t0 - (done + at);
-        wave_lds_fence();
-        for (uint32_t q = lane; q < nt; q += 64) {
-            const uint32_t it = s_tri[wv][q], cc = s_cell[wv][it & 63u], pt = cc & 1023u;
-            mc_emit_tri(reinterpret_cast<const int8_t *>(tri_lds), s_k[wv][pt >> 6], off_bits, tris,
-                        pt & 63u, (int)(cc >> 10), (int)(it >> 6), s_t[wv][pt >> 6] + done + q);
-        }
-        done += nt;
-        wave_lds_fence();
+        wave_lds_fence();             // the next group refills the lists
     }
 }
 
@@ -2000,11 +2045,12 @@ hipError_t mc_stride_gather_launch(const float *phi, const TsdfGrid &g, int step
     return hipGetLastError();
 }
 
-hipError_t tsdf_threshold_launch(const uint64_t *sums, const uint64_t *thr, uint8_t *vt,
-                                 int64_t n, hipStream_t s)
+hipError_t tsdf_threshold_pack_launch(const uint64_t *sums, const uint64_t *thr, uint8_t *vt,
+                                      uint64_t *F, uint64_t *O, const TsdfGrid &g, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_threshold_sums, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, sums,
-                       thr, vt, n);
+    const int W = (g.nx + 63) / 64;
+    hipLaunchKernelGGL(k_threshold_pack, dim3(grid_for((int64_t)W * g.ny * g.nz, kPackSums * (kBlock / 64))),
+                       dim3(kBlock), 0, s, sums, thr, vt, g, W, F, O);
     return hipGetLastError();
 }
 
@@ -2166,14 +2212,18 @@ hipError_t mc_count_launch(const float *phi, const TsdfGrid &g, float iso, const
 }
 
 hipError_t mc_emit_launch(const float *phi, const TsdfGrid &g, float iso, const uint8_t *ntri,
-                          const int8_t *tris_of, const McBuffers &b, uint32_t ngroups,
-                          float *verts, int32_t *tris, float *normals, hipStream_t s)
+                          const int8_t *tris_of, const McBuffers &b, uint32_t cap_verts,
+                          uint32_t cap_tris, float *verts, int32_t *tris, float *normals,
+                          hipStream_t s)
 {
-    if (ngroups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mc_emit, dim3(grid_for(ngroups, kMcEmitWaves)), dim3(kBlock), 0, s, phi, g,
-                       iso, mc_words(g.n), (uint32_t)mc_blocks(g.n), ngroups, ntri, tris_of,
-                       b.inside, static_cast<const McWord *>(b.words), b.cells, b.list, b.group,
-                       b.nlist, b.vsums, b.tsums, b.gsums, verts, tris, normals);
+    // at most one group a word; waves go on to further groups
+    const int64_t nw = mc_words(g.n);
+    const unsigned blocks = grid_for(nw, kMcEmitWaves);
+    hipLaunchKernelGGL(k_mc_emit, dim3(blocks < kMcEmitBlocks ? blocks : kMcEmitBlocks),
+                       dim3(kBlock), 0, s, phi, g, iso, nw, (uint32_t)mc_blocks(g.n), b.totals,
+                       cap_verts, cap_tris, ntri, tris_of, b.inside,
+                       static_cast<const McWord *>(b.words), b.cells, b.list, b.group, b.nlist,
+                       b.vsums, b.tsums, b.gsums, verts, tris, normals);
     return hipGetLastError();
 }
 

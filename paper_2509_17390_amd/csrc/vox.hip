@@ -472,7 +472,7 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
         ws.take(&a, tsdf_smooth_a_bytes(g));
         ws.take(&b, tsdf_smooth_b_bytes(g));
     }
-    if (!vt && !(smooth_bits && shell_bits)) ws.take(&vt, g.n);
+    if (!vt && !((smooth_bits || quant) && shell_bits)) ws.take(&vt, g.n);
     if (!shell_bits) ws.take(&pbuf, g.n + 2 * pad + 4);
     ws.take(&fw, sizeof(uint64_t) * nwords);
     ws.take(&ow, sizeof(uint64_t) * nwords);
@@ -489,8 +489,7 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
     if (quant) {
         HIP_TRY(tsdf_smooth_sums_launch(surf, a, b, sums, g, w, s));
         HIP_TRY(radix_select_u64_launch(sums, g.n, q_rank, 6 * w.n + 1, sel, s));
-        HIP_TRY(tsdf_threshold_launch(sums, radix_select_value(sel), vt, g.n, s));
-        HIP_TRY(tsdf_pack_launch(vt, fw, ow, g, s));
+        HIP_TRY(tsdf_threshold_pack_launch(sums, radix_select_value(sel), vt, fw, ow, g, s));
     } else if (smooth_bits) {
         HIP_TRY(tsdf_smooth_bits_launch(surf, bits, vt, fw, ow, g, w, thr, s));
     } else {
@@ -573,7 +572,16 @@ rc_status rc_marching_cubes(rc_ctx *c, const rc_grid *grid, const float *phi, fl
     b.gsums = b.tsums + nb;
     b.totals = b.gsums + nb;
     HIP_TRY(mc_count_launch(phi, g, iso, ntri, b, s));
-    uint32_t tot[3];
+    // the mesh is enqueued before its size is known here (nothing is written
+    // beyond the capacity), so that it does not wait for the host
+    if (out_verts) {
+        const int64_t most = 0xffffffffLL;
+        HIP_TRY(mc_emit_launch(phi, g, iso, ntri, tris_of, b,
+                               (uint32_t)(cap_verts < 0 ? 0 : (cap_verts < most ? cap_verts : most)),
+                               (uint32_t)(cap_tris < 0 ? 0 : (cap_tris < most ? cap_tris : most)),
+                               out_verts, out_tris, out_normals, s));
+    }
+    uint32_t tot[2];
     HIP_TRY(hipMemcpyAsync(tot, b.totals, sizeof tot, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     *n_verts = tot[0];
@@ -581,9 +589,6 @@ rc_status rc_marching_cubes(rc_ctx *c, const rc_grid *grid, const float *phi, fl
     if (!out_verts) return RC_OK;
     if (cap_verts < (int64_t)tot[0] || cap_tris < (int64_t)tot[1])
         return fail(RC_E_NOMEM, "mesh needs %u vertices and %u triangles", tot[0], tot[1]);
-    HIP_TRY(mc_emit_launch(phi, g, iso, ntri, tris_of, b, tot[2], out_verts, out_tris, out_normals,
-                           s));
-    HIP_TRY(hipStreamSynchronize(s));
     return RC_OK;
 }
 

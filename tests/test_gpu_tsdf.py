@@ -407,3 +407,58 @@ def test_bit_words_and_tiles(ctx, shape):
         ctx.tsdf(g, cuda(surf), alone, sigma, 0.46, band)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(alone.cpu().numpy().view(np.uint32), phi.view(np.uint32))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (3, 5, 63), (2, 1, 64), (5, 4, 65), (7, 3, 130),
+                                   (2, 3, 577)])
+def test_quantile_words(ctx, shape):
+    # quantile threshold straight to words: rows about a word's 64 voxels, word
+    # counts that a wave's four do and do not divide, with and without V~, and
+    # with the shells that read V~ bytes (5)
+    import torch
+    h = 0.5
+    surf = (np.random.default_rng(sum(shape)).random(shape) < 0.3).astype(np.uint8)
+    nz, ny, nx = shape
+    g = ctx.grid((0.0, 0.0, 0.0), h, (nx, ny, nz), 0.0)
+    for q, shells in ((0.4, 2), (0.9, 4), (0.7, 5)):
+        sigma, band = h, (shells - 0.5) * h
+        log(f"{shape}: quantile {q}, {shells} shells")
+        phi_o, vt_o, _, _ = ot.tsdf(surf, h, sigma, 0.0, band, quantile=q)
+        for vt in (None, torch.full(shape, 9, dtype=torch.uint8, device="cuda")):
+            phi = torch.full(shape, 7.0, dtype=torch.float32, device="cuda")
+            ctx.tsdf(g, cuda(surf), phi, sigma, 0.0, band, out_vtilde=vt, quantile=q)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(phi.cpu().numpy().view(np.uint32), phi_o.view(np.uint32))
+        np.testing.assert_array_equal(vt.cpu().numpy(), vt_o)
+
+
+@pytest.mark.parametrize("short", ["verts", "tris"])
+def test_marching_cubes_writes_nothing_beyond_capacity(ctx, short):
+    # one entry short in either array: the sizes come back, nothing is written;
+    # with just enough the mesh is the one extracted with room to spare
+    import ctypes
+
+    import torch
+    rng = np.random.default_rng(31)
+    field = cuda(rng.standard_normal((9, 20, 70)).astype(np.float32))
+    g = ctx.grid((0.0, 0.0, 0.0), 0.5, (70, 20, 9), 0.0)
+    v, t = ctx.marching_cubes(g, field, 0.0)
+    lib = rcast.load()
+    for less in (1, 0):
+        nv, nt = ctypes.c_int64(), ctypes.c_int64()
+        V = torch.full((len(v) + 1, 3), -7.0, dtype=torch.float32, device="cuda")
+        T = torch.full((len(t) + 1, 3), -7, dtype=torch.int32, device="cuda")
+        cv = len(v) - (less if short == "verts" else 0)
+        ct = len(t) - (less if short == "tris" else 0)
+        st = lib.rc_marching_cubes(ctx._h, ctypes.byref(g), field.data_ptr(), 0.0, V.data_ptr(),
+                                   T.data_ptr(), None, cv, ct, ctypes.byref(nv),
+                                   ctypes.byref(nt), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert (nv.value, nt.value) == (len(v), len(t))
+        if less:
+            assert st == rcast.RC_E_NOMEM
+            assert bool((V == -7.0).all()) and bool((T == -7).all())
+        else:
+            assert st == rcast.RC_OK
+            assert torch.equal(V[:-1], v) and torch.equal(T[:-1], t)
+            assert bool((V[-1] == -7.0).all()) and bool((T[-1] == -7).all())
