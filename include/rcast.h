@@ -548,8 +548,8 @@ typedef struct {
 /* TSDF of the DEVICE uint8 surface mask `surf` [nz][ny][nx] into the DEVICE
  * float32 `out_phi` (same layout); `out_vtilde` (DEVICE uint8, or NULL)
  * receives V~.  Runs on `stream` and returns when phi is complete (the
- * outside labelling repeats until it settles, reading a flag per 4 to 8
- * rounds).  Scratch device memory of about 0.5 bytes per voxel (14 with more
+ * outside labelling of grids beyond some 9,000 words of 64 voxels repeats
+ * until it settles, reading a flag per 4 to 8 rounds).  Scratch device memory of about 0.5 bytes per voxel (14 with more
  * than 3 smoothing steps or 4 shells, 21 to 23 with the quantile re-threshold, which
  * keeps the smoothing's integer sums) is kept by the context
  * (grown on demand, reused by later calls, freed by rc_destroy).

@@ -63,6 +63,10 @@ hipError_t tsdf_smooth_bits_launch(const uint8_t *surf, uint64_t *bits, uint8_t 
                                    hipStream_t s);
 hipError_t tsdf_pack_launch(const uint8_t *vt, uint64_t *F, uint64_t *O, const TsdfGrid &g,
                             hipStream_t s);
+// All rounds at once, for grids of up to 9,216 words (slices at odd words) of
+// at most 576 rows, slices and words a row.
+bool tsdf_label_small(const TsdfGrid &g);
+hipError_t tsdf_label_small_launch(const uint64_t *F, uint64_t *O, const TsdfGrid &g, hipStream_t s);
 // A round whose `prev` flag (the previous round's *changed; null: always
 // run) reads 0 does nothing, so rounds can be enqueued ahead in batches.
 hipError_t tsdf_flood_round_launch(const uint64_t *F, uint64_t *O, uint64_t *seg,

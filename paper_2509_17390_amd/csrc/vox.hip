@@ -400,11 +400,11 @@ struct Scratch {
 
 }  // namespace
 
-// Outside-labelling rounds enqueued per flag read.  The usual masks settle in
-// 2 to 5 rounds on small grids and 5 to 8 on large ones; a flag read costs the
-// stream some 25 us, a round after the last one 5 us.  4 first up to 2^22
-// voxels (8 there: +8 us of 370 at 350,200 voxels), 8 beyond (6 and a second
-// read: +40 us of 480 at 34.2M), then 4 and 8 at a time.
+// Outside-labelling rounds enqueued per flag read, for grids beyond one block's.
+// The usual masks settle in 2 to 5 rounds on small grids and 5 to 8 on large
+// ones; a flag read costs the stream some 25 us, a round after the last one
+// 5 us.  4 first up to 2^22 voxels (8 there: +8 us of 370 at 350,200 voxels), 8
+// beyond (6 and a second read: +40 us of 480 at 34.2M), then 4 and 8 at a time.
 constexpr int kFloodBatchMax = 8;
 inline int flood_batch(int64_t k, int64_t n) { return k == 1 || (k == 0 && n <= (1 << 22)) ? 4 : 8; }
 
@@ -501,7 +501,18 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
     // once, and repeating a settled round changes nothing.  phi from bits is
     // enqueued behind each batch and does nothing if that had not settled, so
     // that it does not wait for the flag's way to the host.
-    for (int64_t it = 0, k = 0;; ++k) {
+    // grids that one block's LDS holds settle in one launch: up to its limit
+    // the call was never slower (32^3 voxels 97 -> 45 us, 70 x 80 x 64 100 ->
+    // 61, 96 x 95 x 64 at the limit 97 -> 74, noise of many rounds 190 -> 132)
+    const bool small = tsdf_label_small(g);
+    if (small) {
+        HIP_TRY(tsdf_label_small_launch(fw, ow, g, s));
+        if (shell_bits) {
+            HIP_TRY(tsdf_shells_phi_bits_launch(fw, ow, out_phi, g, shells, g.hf, r, nullptr, s));
+            HIP_TRY(hipStreamSynchronize(s));
+        }
+    }
+    for (int64_t it = 0, k = 0; !small; ++k) {
         const int nb = flood_batch(k, g.n);
         int32_t changed[kFloodBatchMax];
         HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int32_t) * nb, s));

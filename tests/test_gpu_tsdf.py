@@ -462,3 +462,26 @@ def test_marching_cubes_writes_nothing_beyond_capacity(ctx, short):
             assert st == rcast.RC_OK
             assert torch.equal(V[:-1], v) and torch.equal(T[:-1], t)
             assert bool((V[-1] == -7.0).all()) and bool((T[-1] == -7).all())
+
+
+@pytest.mark.parametrize("shape", [(9, 10, 64), (10, 9, 65), (19, 73, 130), (73, 18, 20),
+                                   (576, 5, 40), (577, 5, 40), (5, 576, 70), (96, 95, 64),
+                                   (96, 96, 64), (4, 3, 3700)])
+def test_labelling_by_one_block(ctx, shape):
+    # columns about a lane's run of 9 and a wave's 576, rows of 1 to 58 words,
+    # grids on either side of what one block holds; noise, and a passage that
+    # goes to and fro through walls with one hole each (a round or two a wall)
+    nz, ny, nx = shape
+    rng = np.random.default_rng(nz + ny + nx)
+    passage = np.zeros(shape, np.uint8)
+    passage[:, [0, -1]] = 1
+    passage[:, :, [0, -1]] = 1
+    passage[0] = passage[-1] = 1
+    for i, z in enumerate(range(0, nz, 3)):
+        passage[z] = 1
+        passage[z, 1 if i % 2 else -2, 1 if i % 2 else -2] = 0
+    h = 0.5
+    for surf, sigma, tau in (((rng.random(shape) < 0.3).astype(np.uint8), h, 0.3),
+                             (passage, 0.25 * h, 0.5)):
+        log(f"{shape}: {int(surf.sum())} set")
+        check_tsdf(ctx, surf, (0.25, 0.5, -0.125), h, sigma, tau, 2 * h, tag=f"{shape}")
