@@ -346,24 +346,14 @@ __device__ int build_ring(const int32_t *__restrict__ F, const int32_t *f, int n
 // Per vertex: sort its faces, collect its distinct neighbours (ascending),
 // count those above it, sum its faces' plane quadrics (ascending face order)
 // and protect it when an edge at it is not on exactly two faces.  (A round's
-// start.)
-__global__ __launch_bounds__(kBlock) void k_qem_vertex(const double *__restrict__ P,
-                                                       const int32_t *__restrict__ F, int64_t nv,
-                                                       const uint32_t *__restrict__ fcnt,
-                                                       int32_t *__restrict__ fl,
-                                                       int32_t *__restrict__ fdeg,
-                                                       int32_t *__restrict__ nb,
-                                                       int32_t *__restrict__ ndeg,
-                                                       uint32_t *__restrict__ nlarge,
-                                                       double *__restrict__ Q,
-                                                       uint8_t *__restrict__ prot,
-                                                       int32_t *__restrict__ absorbed,
-                                                       uint32_t *__restrict__ flags)
+// start.)  One thread, any number of faces.
+__device__ void vertex_serial(const double *__restrict__ P, const int32_t *__restrict__ F,
+                              int64_t v, int n, int32_t *__restrict__ fl,
+                              int32_t *__restrict__ fdeg, int32_t *__restrict__ nb,
+                              int32_t *__restrict__ ndeg, uint32_t *__restrict__ nlarge,
+                              double *__restrict__ Q, uint8_t *__restrict__ prot,
+                              uint32_t *__restrict__ flags)
 {
-    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (v >= nv) return;
-    absorbed[v] = -1;
-    const int n = fcnt[v] < (uint32_t)kQemFaces ? (int)fcnt[v] : kQemFaces;
     int32_t *f = fl + v * kQemFaces;
     for (int k = 1; k < n; ++k) {
         const int32_t x = f[k];
@@ -454,15 +444,196 @@ __device__ uint32_t vertex_update_serial(const int32_t *__restrict__ F, int64_t 
     return above;
 }
 
-// The same by 8 lanes a vertex, for lists of at most kUpList faces together (a
-// thread a vertex, its lists merged and its ring sorted in place in memory, is
-// a chain of dependent reads and writes: 66 us a step on 262,000 vertices, now
-// 39 us): a face's place is the number of live faces below it, a
-// neighbour's the number of distinct ones below it.  Every vertex's first
-// edge number within its block, and the block's number of edges, follow.
-constexpr int kUpLanes = 8, kUpList = 32;
+constexpr int kUpLanes = 8, kUpList = 32, kUpEach = kUpList / kUpLanes;
 constexpr int32_t kGone = 0x7fffffff;
 
+// The lists of a vertex v from the faces t and their corners besides v, x, of
+// its 8 lanes (row q: faces 8 q on, kGone where there is none), which s_face
+// and s_ring hold in the same order: a face's place is the number of faces
+// below it, a neighbour's the number of distinct ones below it.  m and above:
+// this lane's neighbours, and those above v.  START: leaves s_face in order and
+// returns whether one of this lane's neighbours is not on exactly two faces.
+template <int ROWS, bool START>
+__device__ __forceinline__ bool group_lists(int gl, int64_t v, int4 *s_face,
+                                            int4 *s_ring, const int32_t (&t)[kUpEach],
+                                            int32_t (&x)[kUpEach][2], int32_t *fl,
+                                            int32_t *__restrict__ nb, uint32_t &m, uint32_t &above)
+{
+    constexpr int kUnroll = ROWS > 1 ? 1 : 4;
+    int32_t *faces = reinterpret_cast<int32_t *>(s_face);
+    int32_t *ring = reinterpret_cast<int32_t *>(s_ring);
+    int place[ROWS] = {}, met[ROWS][2] = {};
+    bool again[ROWS][2] = {};      // met before: the first of a value stays
+#pragma unroll(kUnroll)
+    for (int i = 0; i < 2 * ROWS; ++i) {
+        const int4 f = s_face[i];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q)
+            place[q] += (f.x < t[q]) + (f.y < t[q]) + (f.z < t[q]) + (f.w < t[q]);
+    }
+#pragma unroll(kUnroll)
+    for (int i = 0; i < 4 * ROWS; ++i) {
+        const int4 r = s_ring[i];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int e = 2 * (q * kUpLanes + gl) + k - 4 * i, y = x[q][k];
+                again[q][k] |= (e > 0 && r.x == y) || (e > 1 && r.y == y) ||
+                               (e > 2 && r.z == y) || (e > 3 && r.w == y);
+                if (START) met[q][k] += (r.x == y) + (r.y == y) + (r.z == y) + (r.w == y);
+            }
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+        if (t[q] != kGone) {
+            fl[v * kQemFaces + place[q]] = t[q];
+            if (START) faces[place[q]] = t[q];
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (again[q][k]) x[q][k] = ring[2 * (q * kUpLanes + gl) + k] = kGone;
+    }
+    wave_lds_fence();
+    int spot[ROWS][2] = {};
+#pragma unroll(kUnroll)
+    for (int i = 0; i < 4 * ROWS; ++i) {
+        const int4 r = s_ring[i];
+#pragma unroll
+        for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int y = x[q][k];
+                spot[q][k] += (r.x < y) + (r.y < y) + (r.z < y) + (r.w < y);
+            }
+    }
+    m = above = 0;
+    bool odd = false;
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (x[q][k] != kGone) {
+                nb[v * kQemNbrs + spot[q][k]] = x[q][k];
+                ++m;
+                above += x[q][k] > (int32_t)v ? 1u : 0u;
+                odd |= met[q][k] != 2;
+            }
+    }
+    return START && odd;
+}
+
+// By the wave's longest list: vertices have 6 faces and up to two rows when one
+// was contracted into them.  (One form for any number of rows: 79 and 22.7 us
+// for the two kernels where this takes 62 and 19.5, means of a decimation from
+// 262,000 vertices.)
+template <bool START>
+__device__ __forceinline__ bool wave_lists(int rows, int gl, int64_t v, int4 *s_face, int4 *s_ring,
+                                           const int32_t (&t)[kUpEach], int32_t (&x)[kUpEach][2],
+                                           int32_t *fl, int32_t *__restrict__ nb, uint32_t &m,
+                                           uint32_t &above)
+{
+    if (rows == 1) return group_lists<1, START>(gl, v, s_face, s_ring, t, x, fl, nb, m, above);
+    if (rows == 2) return group_lists<2, START>(gl, v, s_face, s_ring, t, x, fl, nb, m, above);
+    return group_lists<kUpEach, START>(gl, v, s_face, s_ring, t, x, fl, nb, m, above);
+}
+
+// rows of 8 faces for n faces here, 1, 2 or 4 for the whole wave
+__device__ __forceinline__ int wave_rows(int n)
+{
+    return __any(n > 2 * kUpLanes) ? kUpEach : (__any(n > kUpLanes) ? 2 : 1);
+}
+
+// A round's start by 8 lanes a vertex, for up to kUpList faces: its lists, then
+// its quadric, the faces of a row of 8 a lane each and their sums, a component
+// a lane, in ascending order.  (A thread a vertex sorted its lists in place in
+// memory, a chain of dependent reads and writes: 220 us on 262,000 vertices,
+// mean of three rounds, now 62.)
+__global__ __launch_bounds__(kBlock) void k_qem_vertex(const double *__restrict__ P,
+                                                       const int32_t *__restrict__ F, int64_t nv,
+                                                       const uint32_t *__restrict__ fcnt,
+                                                       int32_t *fl, int32_t *__restrict__ fdeg,
+                                                       int32_t *__restrict__ nb,
+                                                       int32_t *__restrict__ ndeg,
+                                                       uint32_t *__restrict__ nlarge,
+                                                       double *__restrict__ Q,
+                                                       uint8_t *__restrict__ prot,
+                                                       int32_t *__restrict__ absorbed,
+                                                       uint32_t *__restrict__ flags)
+{
+    constexpr int kGroups = kBlock / kUpLanes;
+    __shared__ int4 s_face[kGroups][kUpList / 4], s_ring[kGroups][kUpList / 2];
+    __shared__ double s_k[kGroups][kUpLanes][10];
+    const int gl = (int)threadIdx.x % kUpLanes, grp = (int)threadIdx.x / kUpLanes;
+    const int64_t v = (int64_t)blockIdx.x * kGroups + grp;
+    if (v >= nv) return;
+    const int n = fcnt[v] < (uint32_t)kQemFaces ? (int)fcnt[v] : kQemFaces;
+    if (gl == 0) absorbed[v] = -1;
+    if (n > kUpList) {
+        if (gl == 0)
+            vertex_serial(P, F, v, n, fl, fdeg, nb, ndeg, nlarge, Q, prot, flags);
+        return;
+    }
+    int32_t *faces = reinterpret_cast<int32_t *>(s_face[grp]);
+    int32_t *ring = reinterpret_cast<int32_t *>(s_ring[grp]);
+    const int rows = wave_rows(n);
+    int32_t t[kUpEach], x[kUpEach][2];
+#pragma unroll
+    for (int q = 0; q < kUpEach; ++q) {
+        const int i = q * kUpLanes + gl;
+        t[q] = i < n ? fl[v * kQemFaces + i] : kGone;
+    }
+#pragma unroll
+    for (int q = 0; q < kUpEach; ++q) {
+        if (q >= rows) break;
+        const int i = q * kUpLanes + gl;
+        const int64_t f = i < n ? t[q] : 0;
+        const int32_t c0 = F[3 * f], c1 = F[3 * f + 1], c2 = F[3 * f + 2];
+        const bool a = c0 == (int32_t)v, b = c1 == (int32_t)v;
+        x[q][0] = i < n ? (a ? c1 : c0) : kGone;
+        x[q][1] = i < n ? (a || b ? c2 : c1) : kGone;
+        faces[i] = t[q];
+        ring[2 * i] = x[q][0];
+        ring[2 * i + 1] = x[q][1];
+    }
+    wave_lds_fence();
+    uint32_t m, above;
+    const bool odd = wave_lists<true>(rows, gl, v, s_face[grp], s_ring[grp], t, x,
+                                       fl, nb, m, above);
+    const uint32_t both = group_sum<kUpLanes>(m | (above << 16));
+    const uint32_t odds = group_ballot<kUpLanes>(odd);
+    if (gl == 0) {
+        fdeg[v] = n;
+        ndeg[v] = (int32_t)(both & 0xffffu);
+        nlarge[v] = both >> 16;
+        prot[v] = odds ? 1 : 0;
+    }
+    double acc[2] = {0.0, 0.0};
+    for (int r = 0; r < n; r += kUpLanes) {
+        if (r + gl < n) {
+            const int64_t f = faces[r + gl];
+            double pa[3], pb[3], pc[3];
+            load3(P, F[3 * f], pa);
+            load3(P, F[3 * f + 1], pb);
+            load3(P, F[3 * f + 2], pc);
+            plane_quadric(pa, pb, pc, s_k[grp][gl]);
+        }
+        wave_lds_fence();
+        for (int k = 0; k < kUpLanes && r + k < n; ++k) {
+            acc[0] = acc[0] + s_k[grp][k][gl];
+            if (gl < 2) acc[1] = acc[1] + s_k[grp][k][8 + gl];
+        }
+        wave_lds_fence();
+    }
+    Q[10 * v + gl] = acc[0];
+    if (gl < 2) Q[10 * v + 8 + gl] = acc[1];
+}
+
+// Between a round's steps by 8 lanes a vertex, for lists of at most kUpList
+// faces together (a thread a vertex, its lists merged and its ring sorted in
+// place in memory: 66 us a step on 262,000 vertices, now 38).  Every vertex's
+// first edge number within its block, and the block's number of edges, follow.
 __global__ __launch_bounds__(kBlock) void k_qem_vertex_update(
     const int32_t *__restrict__ F, int64_t nv, const uint8_t *__restrict__ dirty,
     const int32_t *__restrict__ remap, int32_t *__restrict__ absorbed, int32_t *fl, int32_t *fdeg,
@@ -470,7 +641,7 @@ __global__ __launch_bounds__(kBlock) void k_qem_vertex_update(
     uint32_t *__restrict__ eoff, uint32_t *__restrict__ ebase, QemState *__restrict__ st)
 {
     if (st->loop.done) return;
-    constexpr int kGroups = kBlock / kUpLanes, kEach = kUpList / kUpLanes;
+    constexpr int kGroups = kBlock / kUpLanes, kEach = kUpEach;
     __shared__ uint16_t list[kBlock];
     __shared__ uint32_t count, s_above[kBlock];
     __shared__ int4 s_face[kGroups][kUpList / 4], s_ring[kGroups][kUpList / 2];
@@ -507,7 +678,7 @@ __global__ __launch_bounds__(kBlock) void k_qem_vertex_update(
         // whole rows of 8 faces, go to LDS to be compared with four at a time
         int32_t *faces = reinterpret_cast<int32_t *>(s_face[grp]);
         int32_t *ring = reinterpret_cast<int32_t *>(s_ring[grp]);
-        const int rows = (tot + kUpLanes - 1) / kUpLanes;
+        const int rows = wave_rows(tot);
         int32_t x[kEach][2];
         uint32_t n = 0;
 #pragma unroll
@@ -526,61 +697,9 @@ __global__ __launch_bounds__(kBlock) void k_qem_vertex_update(
         }
         n = group_sum<kUpLanes>(n);
         wave_lds_fence();
-        int place[kEach] = {};
-        bool again[kEach][2] = {};      // met before: the first of a value stays
-        for (int i = 0; i < 2 * rows; ++i) {
-            const int4 f = s_face[grp][i];
-#pragma unroll
-            for (int q = 0; q < kEach; ++q)
-                if (q < rows)
-                    place[q] += (f.x < t[q]) + (f.y < t[q]) + (f.z < t[q]) + (f.w < t[q]);
-        }
-        for (int i = 0; i < 4 * rows; ++i) {
-            const int4 r = s_ring[grp][i];
-#pragma unroll
-            for (int q = 0; q < kEach; ++q)
-                if (q < rows)
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const int e = 2 * (q * kUpLanes + gl) + k - 4 * i, y = x[q][k];
-                        again[q][k] |= (e > 0 && r.x == y) || (e > 1 && r.y == y) ||
-                                       (e > 2 && r.z == y) || (e > 3 && r.w == y);
-                    }
-        }
-        wave_lds_fence();
-#pragma unroll
-        for (int q = 0; q < kEach; ++q) {
-            if (q >= rows) break;
-            if (t[q] != kGone) fl[v * kQemFaces + place[q]] = t[q];
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if (again[q][k]) x[q][k] = ring[2 * (q * kUpLanes + gl) + k] = kGone;
-        }
-        wave_lds_fence();
-        int spot[kEach][2] = {};
-        for (int i = 0; i < 4 * rows; ++i) {
-            const int4 r = s_ring[grp][i];
-#pragma unroll
-            for (int q = 0; q < kEach; ++q)
-                if (q < rows)
-#pragma unroll
-                    for (int k = 0; k < 2; ++k) {
-                        const int y = x[q][k];
-                        spot[q][k] += (r.x < y) + (r.y < y) + (r.z < y) + (r.w < y);
-                    }
-        }
-        uint32_t m = 0, above = 0;
-#pragma unroll
-        for (int q = 0; q < kEach; ++q) {
-            if (q >= rows) break;
-#pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if (x[q][k] != kGone) {
-                    nb[v * kQemNbrs + spot[q][k]] = x[q][k];
-                    ++m;
-                    above += x[q][k] > (int32_t)v ? 1u : 0u;
-                }
-        }
+        uint32_t m, above;
+        wave_lists<false>(rows, gl, v, s_face[grp], s_ring[grp], t, x,
+                           fl, nb, m, above);
         const uint32_t both = group_sum<kUpLanes>(m | (above << 16));
         if (gl == 0) {
             fdeg[v] = (int32_t)n;
@@ -1250,9 +1369,9 @@ hipError_t qem_round_launch(const QemBuffers &b, int64_t nv, int64_t nt, int64_t
     hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(nv, kBlock)), dim3(kBlock), 0, s, b.fcnt, nv, 0u);
     hipLaunchKernelGGL(k_qem_fill_faces, dim3(grid_for(nt, kBlock)), dim3(kBlock), 0, s, b.F, nt,
                        b.fcnt, b.fl, &st->flags);
-    hipLaunchKernelGGL(k_qem_vertex, dim3(grid_for(nv, kBlock)), dim3(kBlock), 0, s, b.P, b.F, nv,
-                       b.fcnt, b.fl, b.fdeg, b.nb, b.ndeg, b.nlarge, b.Q, b.prot, b.absorbed,
-                       &st->flags);
+    hipLaunchKernelGGL(k_qem_vertex, dim3(grid_for(nv, kBlock / kUpLanes)), dim3(kBlock), 0, s, b.P,
+                       b.F, nv, b.fcnt, b.fl, b.fdeg, b.nb, b.ndeg, b.nlarge, b.Q, b.prot,
+                       b.absorbed, &st->flags);
     return hipGetLastError();
 }
 

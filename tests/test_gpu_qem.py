@@ -163,3 +163,19 @@ def test_too_many_faces_at_a_vertex_is_an_error(ctx):
         ctx.decimate_qem(cuda(v), cuda(t), 0.5, 1)
     assert e.value.status == RC_E_INVAL
     check(ctx, *synth.uv_sphere((0.0, 0.0, 0.0), 1.0, 64, 6), 0.5, 1, "64 faces about a pole")
+
+
+@pytest.mark.parametrize("faces", [7, 8, 9, 16, 17, 31, 32, 33])
+def test_round_start_by_rows_of_eight(ctx, faces):
+    # poles of about 8, 16 and 32 faces (rows of a vertex's eight lanes, and the
+    # longest lists they take), faces in any order; then a hole at one pole and
+    # a fin on an edge, whose ends are protected.  Bit-exact against the oracle
+    rng = np.random.default_rng(faces)
+    v, t = synth.uv_sphere((0.0, 0.0, 0.0), 1.0, faces, 9)
+    v = (v + rng.normal(scale=0.01, size=v.shape)).astype(np.float32)
+    t = t[rng.permutation(len(t))]
+    check(ctx, v, t, 0.4, 2, f"{faces} faces about a pole")
+    fin = np.array([[t[5, 1], t[5, 0], len(v)]], dtype=t.dtype)
+    v = np.concatenate([v, v[t[5, :1]] + np.float32(0.3)])
+    t = np.concatenate([np.delete(t, int(np.flatnonzero((t == t.max()).any(axis=1))[0]), axis=0), fin])
+    check(ctx, v, t, 0.5, 2, f"{faces} faces, hole and fin")
