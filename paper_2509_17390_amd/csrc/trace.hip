@@ -611,14 +611,25 @@ __device__ __forceinline__ bool node_step_q8(LaneRay &L, LaneStack<SS, STK, BLK>
 
 // Sort key of a candidate at distance t >= 0: the bits of t order like t, and
 // the candidate's number in the two lowest makes keys distinct, so an integer
-// minimum and maximum sort them.  The number raises t by at most three units
-// in the last place, far inside t_hi's margin.  kNoKey (+inf) and above: none.
+// minimum and maximum sort them.  kNoKey (+inf) and above: none.  Where a key
+// is compared with the ray's far end the two bits must not count (t_hi's
+// margin is relative: there is none about a hit at distance 0), so key_limit
+// has both of them set and key_t clears them.
 constexpr uint32_t kNoKey = 0x7f800000u;
 
 __device__ __forceinline__ uint32_t sort_key(bool in, float t, int k)
 {
     return ((in ? __float_as_uint(t + 0.0f) : kNoKey) & ~3u) | (uint32_t)k;
 }
+
+// the largest key of a candidate at t <= t_hi (a hit at -0 makes t_hi -0)
+__device__ __forceinline__ uint32_t key_limit(float t_hi)
+{
+    return __float_as_uint(fminf(t_hi, FLT_MAX) + 0.0f) | 3u;
+}
+
+// no more than the distance a key was made of
+__device__ __forceinline__ float key_t(uint32_t key) { return __uint_as_float(key & ~3u); }
 
 // Plain nodes, two levels a visit.  A node is named by its children
 // (pack_children): they are adjacent records, so both are fetched at once and
@@ -697,7 +708,7 @@ __device__ __forceinline__ bool node_step_wide(LaneRay &L, LaneStack<SS, STK, BL
     }
     RC_KSWAP(0, 1) RC_KSWAP(2, 3) RC_KSWAP(0, 2) RC_KSWAP(1, 3) RC_KSWAP(1, 2)
 #undef RC_KSWAP
-    const uint32_t lim = __float_as_uint(fminf(L.t_hi, FLT_MAX)) | 3u;
+    const uint32_t lim = key_limit(L.t_hi);
     auto name_of = [&](uint32_t w) {
         const uint32_t n01 = w & 1u ? name[1] : name[0], n23 = w & 1u ? name[3] : name[2];
         return (int)(w & 2u ? n23 : n01);
@@ -717,7 +728,7 @@ __device__ __forceinline__ bool node_step_wide(LaneRay &L, LaneStack<SS, STK, BL
         int n;
         float tt;
         S.get(L.sp, n, tt);
-        const bool ok = tt <= L.t_hi;
+        const bool ok = key_t(__float_as_uint(tt)) <= L.t_hi;
         L.node = ok ? n : L.node;
         more = ok;
         pop = !ok;
@@ -1325,7 +1336,7 @@ __global__ __launch_bounds__(64, G == 4 ? 5 : 6) void k_trace_group(InlineJobs, 
             uint64_t w;
             if (L.sp < kGroupLds) w = stk[RAYS * L.sp];
             else w = deep[L.sp - kGroupLds];
-            more = __uint_as_float((uint32_t)(w >> 32)) <= L.t_hi;
+            more = key_t((uint32_t)(w >> 32)) <= L.t_hi;
             entry = (uint32_t)w;
             pop = !more;
         }

@@ -827,3 +827,41 @@ def test_many_casts_in_flight_hold_their_scenes(ctx):
     assert torch.equal(rng_out, want[0]) and torch.equal(hit_out, want[1])
     assert torch.equal(other[0], r5) and torch.equal(other[1], h5)
     ctx.release_scene(a)
+
+
+@pytest.mark.parametrize("nodes", ["fp32", "q8"])
+@pytest.mark.parametrize("rays", [60, 3 << 18, (3 << 19) + 60])
+def test_hits_at_distance_zero(ctx, nodes, rays):
+    """Origins on the mesh with t_min = 0 (hits at +0 and -0, where the ray's
+    far end has no margin), by four, two and one lane a ray: every triangle of
+    a fan about the origin is hit at 0 and the lowest id wins; a plane seen
+    from within it; a scene of two triangles; the interval [0, 0]; all against
+    every triangle."""
+    import torch
+    rng = np.random.default_rng(41)
+    fmt = RC_NODE_Q8 if nodes == "q8" else RC_NODE_FP32
+    o = np.array([0.5, -0.25, 0.125], np.float32)
+    tip = rng.uniform(-2, 2, (400, 3, 3)).astype(np.float32)
+    tip[np.arange(400), rng.integers(0, 3, 400)] = o
+    flat = rng.uniform(-2, 2, (300, 3, 3)).astype(np.float32)
+    flat[:, :, 2] = o[2]
+    pair = np.concatenate([flat[:1], tip[:1]])
+    pair[0, :, :2] = [[-3, -3], [4, -3], [0, 5]]
+    d = np.concatenate([rng.normal(size=(54, 3)), np.eye(3), -np.eye(3)]).astype(np.float32)
+    pat = ctx.upload_pattern(d, 60)
+    poses = np.zeros((rays // 60, 12), np.float32)
+    poses[:, [0, 5, 10]] = 1
+    poses[:, [3, 7, 11]] = o
+    p = cuda(poses)
+    for name, tri in (("fan", tip), ("plane", flat), ("pair", pair)):
+        v, t = tri.reshape(-1, 3), np.arange(3 * len(tri), dtype=np.int32).reshape(-1, 3)
+        scene = ctx.upload_scene(v, t)
+        ctx.build(scene, node_format=fmt)
+        for t_max in (0.0, 30.0):
+            log(f"{name}, {nodes}, {rays} rays, t_max {t_max}")
+            r, h = ctx.cast([Job(scene, pat, p, 0.0, t_max, 0)])
+            rb, hb = ctx.cast([Job(scene, pat, p[:1], 0.0, t_max, 0)], mode="brute")
+            assert int((hb >= 0).sum()) >= 10    # (the plane at exactly 0: rays that mostly follow z)
+            assert torch.equal(h.reshape(-1, 60), hb.expand(rays // 60, 60))
+            assert torch.equal(r.reshape(-1, 60), rb.expand(rays // 60, 60))
+        ctx.release_scene(scene)
