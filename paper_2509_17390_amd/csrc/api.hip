@@ -123,23 +123,36 @@ void drop_holds(rc_ctx *c, Scene *const *s, size_t n)
 
 namespace {
 
-// Drop the references of the flights that have finished: those at the front
-// (oldest first), or with `all` wherever they are.
-void land_flights(rc_ctx *c, bool all)
+bool stream_capturing(hipStream_t s)
 {
-    std::lock_guard<std::mutex> lk(c->ref_mu);
-    for (size_t i = 0; i < c->flights.size();) {
-        Flight &f = c->flights[i];
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+}
+
+// Drop the references of the flights of a stream that have finished.  Caller
+// holds c->flight_mu.
+void land_stream(rc_ctx *c, std::deque<Flight> &q)
+{
+    while (!q.empty()) {
+        Flight &f = q.front();
         if (hipEventQuery(f.done) != hipSuccess) {
             (void)hipGetLastError();   // "not ready" is no error of the next launch
-            if (!all) return;
-            ++i;
-            continue;
+            return;
         }
-        for (Scene *s : f.held)
-            if (--s->refs == 0 && s->dead) c->reap.push_back(s);
+        drop_holds(c, f.held.data(), f.held.size());
         c->flight_events.push_back(f.done);
-        c->flights.erase(c->flights.begin() + (ptrdiff_t)i);
+        q.pop_front();
+        --c->n_flights;
+    }
+}
+
+// The same for every stream.
+void land_all(rc_ctx *c)
+{
+    for (auto it = c->flights.begin(); it != c->flights.end();) {
+        land_stream(c, it->second);
+        if (it->second.empty()) it = c->flights.erase(it);
+        else ++it;
     }
 }
 
@@ -147,7 +160,10 @@ void land_flights(rc_ctx *c, bool all)
 
 void reap_locked(rc_ctx *c)
 {
-    if (!c->mock) land_flights(c, true);
+    if (!c->mock) {
+        std::lock_guard<std::mutex> lk(c->flight_mu);
+        land_all(c);
+    }
     std::vector<Scene *> r;
     {
         std::lock_guard<std::mutex> lk(c->ref_mu);
@@ -159,24 +175,22 @@ void reap_locked(rc_ctx *c)
 
 namespace {
 
-// Host function behind a launch: no HIP call, no c->mu.  The record goes
-// back to the pool (clear() keeps its capacity).
+// Host function behind a launch or build: no HIP call, no c->mu.  A pooled
+// record goes back to the pool (clear() keeps its capacity).
 void drop_host_fn(void *arg)
 {
     DropRec *d = static_cast<DropRec *>(arg);
     rc_ctx *c = d->c;
     drop_holds(c, d->held.data(), d->held.size());
+    const int slot = d->slot;
+    if (slot < 0) delete d;
     std::lock_guard<std::mutex> lk(c->ref_mu);
-    d->held.clear();
-    c->drop_free.push_back(d->slot);
+    if (slot >= 0) {
+        d->held.clear();
+        c->drop_free.push_back(slot);
+    }
     --c->pending_drops;
     c->ref_cv.notify_all();
-}
-
-bool stream_capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
 }
 
 }  // namespace
@@ -206,51 +220,45 @@ rc_status enqueue_drop(rc_ctx *c, hipStream_t s, DropRec *d)
 rc_status drop_after(rc_ctx *c, hipStream_t s, std::vector<Scene *> &held)
 {
     if (held.empty()) return RC_OK;
-    auto drop_now = [&] {
+    if (stream_capturing(s)) {
         drop_holds(c, held.data(), held.size());
         held.clear();
-    };
-    if (stream_capturing(s)) {
-        drop_now();
         return RC_OK;
     }
-    land_flights(c, false);
-    Flight f;
-    Flight oldest;
     {
-        std::lock_guard<std::mutex> lk(c->ref_mu);
-        if (!c->flight_events.empty()) {
-            f.done = c->flight_events.back();
-            c->flight_events.pop_back();
-        }
-        if (c->flights.size() >= kMaxFlights) {
-            oldest = std::move(c->flights.front());
-            c->flights.pop_front();
+        std::lock_guard<std::mutex> lk(c->flight_mu);
+        auto own = c->flights.find(s);
+        if (own != c->flights.end()) land_stream(c, own->second);
+        // (streams come and go: a new one takes the empty queues away)
+        if (c->n_flights >= kMaxFlights || (own == c->flights.end() && c->flights.size() >= 64))
+            land_all(c);
+        if (c->n_flights < kMaxFlights) {
+            Flight f;
+            hipError_t e = hipSuccess;
+            if (!c->flight_events.empty()) {
+                f.done = c->flight_events.back();
+                c->flight_events.pop_back();
+            } else {
+                e = hipEventCreateWithFlags(&f.done, hipEventDisableTiming);
+            }
+            if (e == hipSuccess) {
+                e = hipEventRecord(f.done, s);
+                if (e != hipSuccess) c->flight_events.push_back(f.done);
+            }
+            if (e == hipSuccess) {
+                f.held.swap(held);
+                c->flights[s].push_back(std::move(f));
+                ++c->n_flights;
+                return RC_OK;
+            }
+            (void)hipGetLastError();
         }
     }
-    if (oldest.done) {   // too many to keep track of: wait for one
-        (void)hipEventSynchronize(oldest.done);
-        drop_holds(c, oldest.held.data(), oldest.held.size());
-        std::lock_guard<std::mutex> lk(c->ref_mu);
-        c->flight_events.push_back(oldest.done);
-    }
-    hipError_t e = hipSuccess;
-    if (!f.done) e = hipEventCreateWithFlags(&f.done, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(f.done, s);
-    if (e != hipSuccess) {
-        // no event: wait for the stream, then drop here
-        (void)hipStreamSynchronize(s);
-        drop_now();
-        if (f.done) {
-            std::lock_guard<std::mutex> lk(c->ref_mu);
-            c->flight_events.push_back(f.done);
-        }
-        return fail(RC_E_DEVICE, "hipEventRecord failed: %s", hipGetErrorString(e));
-    }
-    f.held.swap(held);
-    std::lock_guard<std::mutex> lk(c->ref_mu);
-    c->flights.push_back(std::move(f));
-    return RC_OK;
+    // too many to keep track of, or no event: a host function
+    DropRec *d = new DropRec();
+    d->c = c;
+    d->held.swap(held);
+    return enqueue_drop(c, s, d);
 }
 
 Pattern *get_pattern(rc_ctx *c, int32_t id)
@@ -666,7 +674,8 @@ void rc_destroy(rc_ctx *c)
         std::unique_lock<std::mutex> lk(c->ref_mu);
         c->ref_cv.wait(lk, [&] { return c->pending_drops == 0; });
     }
-    for (Flight &f : c->flights) (void)hipEventDestroy(f.done);   // all have landed
+    for (auto &q : c->flights)
+        for (Flight &f : q.second) (void)hipEventDestroy(f.done);   // all have landed
     for (hipEvent_t ev : c->flight_events) (void)hipEventDestroy(ev);
     for (auto &s : c->scenes)
         if (s.alive) free_scene(c, s);

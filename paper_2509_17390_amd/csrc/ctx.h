@@ -102,9 +102,10 @@ struct JobSlot {
 struct ServeState;  // serve.hip
 
 // References of one launch or build, dropped once `done` (recorded on its
-// stream behind its work) has passed.  Polled, never waited for: a host
-// function on the stream would drop them at once, but stalls the stream until
-// the host has run it (about 30 us a call).
+// stream behind its work) has passed.  Polled, never waited for, a queue per
+// stream, so that no stream's casts depend on another's.  (A host function on
+// the stream drops them at once, but stalls the stream until the host has run
+// it, about 30 us a call: it is taken for the launches beyond kMaxFlights.)
 struct Flight {
     hipEvent_t done = nullptr;
     std::vector<Scene *> held;
@@ -112,8 +113,8 @@ struct Flight {
 constexpr size_t kMaxFlights = 1024;
 
 // References dropped by a host function once the work enqueued before it on
-// a stream has finished: the launch entry point that allocates nothing, whose
-// records are preallocated.
+// a stream has finished.  Records with slot >= 0 belong to the context's
+// pool, preallocated for the launch entry point that allocates nothing.
 struct DropRec {
     rc_ctx *c = nullptr;
     std::vector<Scene *> held;
@@ -148,12 +149,16 @@ struct rc_ctx {
     rc_tuning tuning{};
     rc::ServeState *serve = nullptr;
     uint8_t *mc_table = nullptr;   // marching-cubes case table on the device (256 + 256 * 15 bytes)
-    // scene references (never held across a HIP call that waits for the
-    // device, so host functions on a stream can always take it)
+    // scene references (never held across a HIP call, so host functions on a
+    // stream can always take it)
     std::mutex ref_mu;
     std::condition_variable ref_cv;
     std::vector<rc::Scene *> reap;       // dead scenes without references, freed under mu
-    std::deque<rc::Flight> flights;      // launches and builds not known to have finished
+    // launches and builds not known to have finished, by stream, oldest first
+    // (taken inside mu, outside ref_mu)
+    std::mutex flight_mu;
+    std::map<hipStream_t, std::deque<rc::Flight>> flights;
+    size_t n_flights = 0;
     std::vector<hipEvent_t> flight_events;   // events of past ones, for the next
     int pending_drops = 0;               // drop host functions enqueued and not yet run
     std::vector<rc::DropRec> drop_pool;  // kDropPool records, each with room for
@@ -172,8 +177,9 @@ namespace rc {
 // drop_holds: any thread, makes no HIP call; a dead scene left without
 // references goes to c->reap.  reap_locked: caller holds c->mu; frees the
 // scenes on c->reap.  drop_after: drops `held` once the work enqueued so
-// far on `s` has finished (a host function; at once when `s` is being
-// captured into a graph, whose owner keeps the scenes alive); empties `held`.
+// far on `s` has finished (see Flight; at once when `s` is being captured
+// into a graph, whose owner keeps the scenes alive); empties `held`, and does
+// not wait for the device.
 void hold_scene(rc_ctx *c, Scene *s);
 void drop_holds(rc_ctx *c, Scene *const *s, size_t n);
 void reap_locked(rc_ctx *c);

@@ -865,3 +865,47 @@ def test_hits_at_distance_zero(ctx, nodes, rays):
             assert torch.equal(h.reshape(-1, 60), hb.expand(rays // 60, 60))
             assert torch.equal(r.reshape(-1, 60), rb.expand(rays // 60, 60))
         ctx.release_scene(scene)
+
+
+def _pattern_and_memory(ctx, s):
+    """The pattern, and the context's memory with it and the build workspace."""
+    pat = ctx.upload_pattern(s.dirs, s.n_az)
+    scene = ctx.upload_scene(s.verts, s.tris)
+    ctx.build(scene, node_format=RC_NODE_Q8)
+    ctx.release_scene(scene)
+    import torch
+    torch.cuda.synchronize()
+    return pat, ctx.device_bytes()
+
+
+def test_a_busy_stream_does_not_hold_another_streams_casts(ctx):
+    """Casts return once enqueued, however long another stream's work takes: a
+    stream with some tenths of a second of casts, and more casts on a second
+    one than launches are kept track of; both give their scenes back."""
+    import torch
+    s = synth.indoor_scene(seed=8, h=0.1, n_envs=512, n_az=1024)
+    pat, base = _pattern_and_memory(ctx, s)
+    a, b = ctx.upload_scene(s.verts, s.tris), ctx.upload_scene(s.verts, s.tris)
+    for scene in (a, b):
+        ctx.build(scene, node_format=RC_NODE_Q8)
+    p = cuda(s.poses)
+    long_job, job = [Job(a, pat, p, 0.0, 50.0)], [Job(b, pat, p[:1], 0.0, 50.0)]
+    want = ctx.cast(job)
+    big = [torch.empty(len(s.poses) * len(s.dirs), dtype=t, device="cuda")
+           for t in (torch.float32, torch.int32)]
+    out = [torch.empty_like(want[0]), torch.empty_like(want[1])]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    done = torch.cuda.Event()
+    torch.cuda.synchronize()
+    log("300 long casts and 1400 short ones on another stream")
+    for _ in range(300):
+        ctx.raycast(long_job, big[0], big[1], stream=streams[0])
+    done.record(streams[0])
+    for _ in range(1400):
+        ctx.raycast(job, out[0], out[1], stream=streams[1])
+    assert not done.query()
+    ctx.release_scene(a)
+    ctx.release_scene(b)
+    torch.cuda.synchronize()
+    assert ctx.device_bytes() == base
+    assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
