@@ -118,7 +118,10 @@ void drop_holds(rc_ctx *c, Scene *const *s, size_t n)
 {
     std::lock_guard<std::mutex> lk(c->ref_mu);
     for (size_t i = 0; i < n; ++i)
-        if (--s[i]->refs == 0 && s[i]->dead) c->reap.push_back(s[i]);
+        if (--s[i]->refs == 0 && s[i]->dead) {
+            c->reap.push_back(s[i]);
+            --c->dead_held;
+        }
 }
 
 namespace {
@@ -126,13 +129,24 @@ namespace {
 bool stream_capturing(hipStream_t s)
 {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
 }
 
-// Drop the references of the flights of a stream that have finished.  Caller
-// holds c->flight_mu.
-void land_stream(rc_ctx *c, std::deque<Flight> &q)
+// Asking an event for its state ends a capture that runs elsewhere, unless the
+// thread's capture mode is relaxed.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// Drop the references of the flights of stream s that have finished (nothing
+// while the stream is being captured).  Caller holds c->flight_mu.
+void land_stream(rc_ctx *c, hipStream_t s, std::deque<Flight> &q)
 {
+    if (stream_capturing(s)) return;
     while (!q.empty()) {
         Flight &f = q.front();
         if (hipEventQuery(f.done) != hipSuccess) {
@@ -150,7 +164,7 @@ void land_stream(rc_ctx *c, std::deque<Flight> &q)
 void land_all(rc_ctx *c)
 {
     for (auto it = c->flights.begin(); it != c->flights.end();) {
-        land_stream(c, it->second);
+        land_stream(c, it->first, it->second);
         if (it->second.empty()) it = c->flights.erase(it);
         else ++it;
     }
@@ -160,7 +174,13 @@ void land_all(rc_ctx *c)
 
 void reap_locked(rc_ctx *c)
 {
-    if (!c->mock) {
+    bool waited_for;
+    {
+        std::lock_guard<std::mutex> lk(c->ref_mu);
+        waited_for = c->dead_held > 0;
+    }
+    if (waited_for && !c->mock) {
+        RelaxedCapture relaxed;
         std::lock_guard<std::mutex> lk(c->flight_mu);
         land_all(c);
     }
@@ -226,9 +246,10 @@ rc_status drop_after(rc_ctx *c, hipStream_t s, std::vector<Scene *> &held)
         return RC_OK;
     }
     {
+        RelaxedCapture relaxed;
         std::lock_guard<std::mutex> lk(c->flight_mu);
         auto own = c->flights.find(s);
-        if (own != c->flights.end()) land_stream(c, own->second);
+        if (own != c->flights.end()) land_stream(c, s, own->second);
         // (streams come and go: a new one takes the empty queues away)
         if (c->n_flights >= kMaxFlights || (own == c->flights.end() && c->flights.size() >= 64))
             land_all(c);
@@ -885,6 +906,7 @@ rc_status rc_scene_release(rc_ctx *c, int32_t scene)
         std::lock_guard<std::mutex> rl(c->ref_mu);
         sc->dead = true;
         now = sc->refs == 0;
+        if (!now) ++c->dead_held;
     }
     // in use: the last reference to go puts it on the reap list instead
     if (now) free_scene(c, *sc);

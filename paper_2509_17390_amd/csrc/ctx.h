@@ -154,6 +154,7 @@ struct rc_ctx {
     std::mutex ref_mu;
     std::condition_variable ref_cv;
     std::vector<rc::Scene *> reap;       // dead scenes without references, freed under mu
+    int dead_held = 0;                   // dead scenes that still have some
     // launches and builds not known to have finished, by stream, oldest first
     // (taken inside mu, outside ref_mu)
     std::mutex flight_mu;

@@ -909,3 +909,48 @@ def test_a_busy_stream_does_not_hold_another_streams_casts(ctx):
     torch.cuda.synchronize()
     assert ctx.device_bytes() == base
     assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local"])
+def test_calls_beside_a_capture_leave_it_whole(mode):
+    """While a stream is captured, with casts in flight on another and a
+    released scene that waits for them: casts, builds and queries beside it,
+    and a build on the captured stream.  The graph then rebuilds the scene."""
+    import torch
+    ctx = Context(0)
+    s = synth.indoor_scene(seed=8, h=0.2, n_envs=64, n_az=1024)
+    pat, base = _pattern_and_memory(ctx, s)
+    ids = [ctx.upload_scene(s.verts, s.tris) for _ in range(3)]
+    for scene in ids:
+        ctx.build(scene, node_format=RC_NODE_Q8)
+    p = cuda(s.poses)
+    side, cap = torch.cuda.Stream(), torch.cuda.Stream()
+    jobs = [Job(ids[0], pat, p, 0.0, 50.0)]
+    gone = [Job(ids[2], pat, p, 0.0, 50.0)]
+    want = ctx.cast(jobs)
+    out = [torch.empty_like(want[0]), torch.empty_like(want[1])]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        ctx.raycast(gone, out[0], out[1], stream=side)
+        ctx.raycast(gone, out[0], out[1], stream=cap)
+    g = torch.cuda.CUDAGraph()
+    log(f"capture, {mode}")
+    with torch.cuda.graph(g, stream=cap, capture_error_mode=mode):
+        ctx.release_scene(ids[2])
+        ctx.raycast(jobs, out[0], out[1], stream=side)
+        ctx.build(ids[0], node_format=RC_NODE_Q8, stream=side)
+        ctx.build(ids[1], node_format=RC_NODE_Q8, stream=cap)
+        assert ctx.device_bytes() > base
+    torch.cuda.synchronize()        # (the builds beside the capture share its workspace)
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        r, h = ctx.cast([Job(ids[1], pat, p, 0.0, 50.0)])
+        assert torch.equal(r, want[0]) and torch.equal(h, want[1])
+    assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
+    del g
+    for scene in ids[:2]:
+        ctx.release_scene(scene)
+    torch.cuda.synchronize()
+    assert ctx.device_bytes() == base
+    ctx.close()
