@@ -128,12 +128,20 @@ __global__ __launch_bounds__(kBlock) void k_smooth_z_sum(const uint64_t *__restr
 
 // Tile number of a block, consecutive tiles on one XCD (workgroups go to the 8
 // XCDs in turn): neighbouring tiles share lines of packed words in its L2.
+// Launches of many tiles have several rows of kTileRow blocks: a tile of a thin
+// grid holds few voxels, and a launch's x axis ends at 2^32 work-items.
+constexpr int64_t kTileRow = 1 << 16;
+
 __device__ __forceinline__ uint32_t xcd_tile()
 {
-    return (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    return blockIdx.y * gridDim.x + (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
 }
 
-inline unsigned xcd_tiles(int64_t n) { return (unsigned)((n + 7) / 8 * 8); }
+inline dim3 xcd_tiles(int64_t n)
+{
+    if (n <= kTileRow) return dim3((unsigned)((n + 7) / 8 * 8));
+    return dim3((unsigned)kTileRow, (unsigned)((n + kTileRow - 1) / kTileRow));
+}
 
 // lane k's value, the same in every lane; and the lane's own bit of such a word
 __device__ __forceinline__ uint64_t read_lane64(uint64_t v, int k)
@@ -2211,7 +2219,7 @@ hipError_t tsdf_smooth_bits_launch(const uint8_t *surf, uint64_t *bits, uint8_t 
                                    hipStream_t s)
 {
     const int W = tsdf_words_per_row(g);
-    const dim3 tiles(xcd_tiles((int64_t)W * ((g.ny + kSmY - 1) / kSmY) * ((g.nz + kSmZ - 1) / kSmZ)));
+    const dim3 tiles = xcd_tiles((int64_t)W * ((g.ny + kSmY - 1) / kSmY) * ((g.nz + kSmZ - 1) / kSmZ));
     hipLaunchKernelGGL(k_pack_bits<false>, dim3(grid_for((int64_t)W * g.ny * g.nz, kPackRun * (kBlock / 4))),
                        dim3(kBlock), 0, s, surf, g, W, fastdiv_constant((uint32_t)W), bits,
                        (uint64_t *)nullptr);
@@ -2233,10 +2241,11 @@ hipError_t tsdf_pack_launch(const uint8_t *vt, uint64_t *F, uint64_t *O, const T
     return hipGetLastError();
 }
 
-// x and y together, where a slice's words fit LDS
+// x and y together, where a slice's words fit LDS (and a block a slice a launch)
 static bool sweep_slices(const TsdfGrid &g)
 {
-    return (int64_t)slice_pitch(tsdf_words_per_row(g)) * g.ny <= kSliceWords;
+    return (int64_t)slice_pitch(tsdf_words_per_row(g)) * g.ny <= kSliceWords &&
+           (int64_t)g.nz * kSliceBlock <= 0x7fffffffLL;
 }
 
 bool tsdf_label_small(const TsdfGrid &g)
@@ -2310,7 +2319,7 @@ hipError_t tsdf_shells_phi_bits_launch(const uint64_t *F, const uint64_t *O, flo
                                        const int32_t *unsettled, hipStream_t s)
 {
     const int W = tsdf_words_per_row(g);
-    const dim3 tiles(xcd_tiles((int64_t)W * ((g.ny + kShY - 1) / kShY) * ((g.nz + kShZ - 1) / kShZ)));
+    const dim3 tiles = xcd_tiles((int64_t)W * ((g.ny + kShY - 1) / kShY) * ((g.nz + kShZ - 1) / kShZ));
     switch (shells) {
     case 1: hipLaunchKernelGGL(k_shells_phi_bits<1>, tiles, dim3(kBlock), 0, s, F, O, phi, g, W, h, r, unsettled); break;
     case 2: hipLaunchKernelGGL(k_shells_phi_bits<2>, tiles, dim3(kBlock), 0, s, F, O, phi, g, W, h, r, unsettled); break;

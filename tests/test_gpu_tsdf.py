@@ -485,3 +485,13 @@ def test_labelling_by_one_block(ctx, shape):
                              (passage, 0.25 * h, 0.5)):
         log(f"{shape}: {int(surf.sum())} set")
         check_tsdf(ctx, surf, (0.25, 0.5, -0.125), h, sigma, tau, 2 * h, tag=f"{shape}")
+
+
+@pytest.mark.parametrize("shape", [((1 << 23) + 3, 1, 1), (1_100_000, 3, 2)])
+def test_thin_grids_of_many_tiles(ctx, shape):
+    # tiles of 16 and 96 voxels, more than one row of a launch's blocks; more
+    # slices than a launch has blocks of a sweep
+    rng = np.random.default_rng(sum(shape))
+    surf = (rng.random(shape, dtype=np.float32) < 0.6).astype(np.uint8)
+    log(f"{shape}")
+    check_tsdf(ctx, surf, (0.0, 0.0, 0.0), 0.5, 0.35, 0.2, 1.0, tag=f"{shape}")
