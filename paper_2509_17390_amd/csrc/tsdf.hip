@@ -494,7 +494,10 @@ __global__ __launch_bounds__(kBlock) void k_sweep_x(const uint64_t *__restrict__
 // LDS; then a wave takes a word column and each lane consecutive rows of it,
 // carries between lanes being a scan of (reach, free throughout) pairs.  F and
 // O are read once (apart: 16 us a round on 512 x 412 x 162 voxels, now
-// 11 us; bound by the chain load - sweep - scan - sweep of a block).
+// 11 us; bound by the chain load - sweep - scan - sweep of a block).  WORDS: a
+// slice's place in LDS.  Slices of up to kSliceSmall words run four blocks a
+// CU, where one at a time leaves most of its waves to the chain (512 x 256 x
+// 2,048 voxels, noise: 3,073 us a TSDF call with one, 2,715 with four).
 // Repeating both sweeps in LDS until the slice settled took 75 us in the first
 // round and saved two rounds of seven: what blocks a slice's fill is passed
 // in z.
@@ -503,6 +506,7 @@ __global__ __launch_bounds__(kBlock) void k_sweep_x(const uint64_t *__restrict__
 // through the free bits above it and clears them ((f + s) ^ f) & f, apart
 // from the seeds it meets); downwards the same on reversed words.
 constexpr int kSliceWords = 9216;     // 2 x 72 KB of LDS
+constexpr int kSliceSmall = 2304;     // 2 x 18 KB
 constexpr int kSliceBlock = 512;
 
 __device__ __forceinline__ uint64_t row_fill_up(uint64_t f, uint64_t s)
@@ -514,6 +518,7 @@ __device__ __forceinline__ uint64_t row_fill_up(uint64_t f, uint64_t s)
 // number: lanes hit different banks
 inline __host__ __device__ int slice_pitch(int W) { return W | 1; }
 
+template <int WORDS>
 __global__ __launch_bounds__(kSliceBlock) void k_sweep_slice(const uint64_t *__restrict__ Fg,
                                                              uint64_t *__restrict__ Og, TsdfGrid g,
                                                              int W, int32_t *__restrict__ changed,
@@ -522,7 +527,7 @@ __global__ __launch_bounds__(kSliceBlock) void k_sweep_slice(const uint64_t *__r
     // a round enqueued after the labelling settled does nothing
     if (skip && *skip == 0) return;
     constexpr int kRun = 8, kRows = 9;    // words of a row, rows of a column, read together
-    __shared__ uint64_t F[kSliceWords], O[kSliceWords];
+    __shared__ uint64_t F[WORDS], O[WORDS];
     const int P = slice_pitch(W);
     const int64_t base = (int64_t)blockIdx.x * g.ny * W;
     const int top = (g.nx - 1) & 63;                      // last voxel's bit in the last word
@@ -2241,11 +2246,23 @@ hipError_t tsdf_pack_launch(const uint8_t *vt, uint64_t *F, uint64_t *O, const T
     return hipGetLastError();
 }
 
-// x and y together, where a slice's words fit LDS (and a block a slice a launch)
+// x and y together, where a slice's words fit LDS, unless there are many thin
+// slices: a block's chain takes as long for few words, so that beyond one block
+// of each of the chip's 1,024 places (kSliceFew) the row sweep, which packs the
+// rows of many slices into a block, is the faster one on slices of fewer than
+// kSliceMany words.  us a TSDF call on noise, together / apart, by words a slice:
+//   64 x 64 x 1,024 (64): 549 / 584       64 x 16 x 20,000 (16): 3,209 / 2,224
+//   64 x 64 x 2,000 (64): 602 / 550       256 x 64 x 4,096 (256): 1,455 / 1,175
+//   64 x 256 x 1,400 (256): 653 / 665     256 x 128 x 2,048 (512): 1,224 / 1,137
+//   128 x 256 x 1,500 (512): 956 / 964    256 x 256 x 4,096 (1,024): 3,220 / 3,217
+//   320 x 200 x 3,000 (1,000): 2,436 / 2,488   512 x 256 x 2,048 (2,048): 2,715 / 3,660
+constexpr int kSliceFew = 1024, kSliceMany = 768;
+
 static bool sweep_slices(const TsdfGrid &g)
 {
-    return (int64_t)slice_pitch(tsdf_words_per_row(g)) * g.ny <= kSliceWords &&
-           (int64_t)g.nz * kSliceBlock <= 0x7fffffffLL;
+    const int64_t words = (int64_t)slice_pitch(tsdf_words_per_row(g)) * g.ny;
+    return words <= kSliceWords && (g.nz <= kSliceFew || words >= kSliceMany) &&
+           (int64_t)g.nz * kSliceBlock <= 0x7fffffffLL;       // a launch's blocks
 }
 
 bool tsdf_label_small(const TsdfGrid &g)
@@ -2268,9 +2285,12 @@ hipError_t tsdf_flood_round_launch(const uint64_t *F, uint64_t *O, uint64_t *seg
 {
     const int W = tsdf_words_per_row(g);
     const bool slices = sweep_slices(g);
-    if (slices)
-        hipLaunchKernelGGL(k_sweep_slice, dim3((unsigned)g.nz), dim3(kSliceBlock), 0, s, F, O, g, W,
-                           changed, prev);
+    if (slices && (int64_t)slice_pitch(W) * g.ny <= kSliceSmall)
+        hipLaunchKernelGGL(k_sweep_slice<kSliceSmall>, dim3((unsigned)g.nz), dim3(kSliceBlock), 0, s,
+                           F, O, g, W, changed, prev);
+    else if (slices)
+        hipLaunchKernelGGL(k_sweep_slice<kSliceWords>, dim3((unsigned)g.nz), dim3(kSliceBlock), 0, s,
+                           F, O, g, W, changed, prev);
     else
         hipLaunchKernelGGL(k_sweep_x, dim3(grid_for((int64_t)g.ny * g.nz, kBlock)), dim3(kBlock), 0,
                            s, F, O, g, W, changed, prev);

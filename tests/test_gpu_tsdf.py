@@ -495,3 +495,14 @@ def test_thin_grids_of_many_tiles(ctx, shape):
     surf = (rng.random(shape, dtype=np.float32) < 0.6).astype(np.uint8)
     log(f"{shape}")
     check_tsdf(ctx, surf, (0.0, 0.0, 0.0), 0.5, 0.35, 0.2, 1.0, tag=f"{shape}")
+
+
+@pytest.mark.parametrize("shape", [(1024, 20, 33), (1025, 20, 33), (1030, 255, 190), (1030, 256, 190),
+                                   (40, 768, 190), (40, 769, 190)])
+def test_sweeps_by_slices_and_by_rows(ctx, shape):
+    # the last grid of few slices and the next one, slices of 765 and 768 words
+    # among many, and slices of 2,304 and 2,307 (four blocks a CU or one)
+    rng = np.random.default_rng(sum(shape))
+    surf = (rng.random(shape, dtype=np.float32) < 0.3).astype(np.uint8)
+    log(f"{shape}")
+    check_tsdf(ctx, surf, (0.0, 0.0, 0.0), 0.5, 0.5, 0.3, 1.0, tag=f"{shape}")
