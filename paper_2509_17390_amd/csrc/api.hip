@@ -431,11 +431,11 @@ TraceConfig config_of(const rc_tuning &t, const DevJob *jobs, int n_jobs)
 {
     TraceConfig cfg;
     cfg.leaf_batch = t.leaf_batch;
-    cfg.pack_ok = true;
-    for (int k = 0; k < n_jobs; ++k) {
-        if ((int64_t)jobs[k].n_tris > kLeafBatchMaxTris) cfg.leaf_batch = 0;
-        if ((int64_t)jobs[k].n_tris > kPackMaxTris) cfg.pack_ok = false;
-    }
+    cfg.max_tris = 0;
+    for (int k = 0; k < n_jobs; ++k)
+        if ((int64_t)jobs[k].n_tris > cfg.max_tris) cfg.max_tris = jobs[k].n_tris;
+    if (cfg.max_tris > kLeafBatchMaxTris) cfg.leaf_batch = 0;
+    cfg.pack_ok = cfg.max_tris <= kPackMaxTris;
     cfg.persistent = t.persistent;
     cfg.stack_lds = t.stack_lds;
     cfg.refill_min = t.refill_min;

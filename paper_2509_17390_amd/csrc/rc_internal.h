@@ -116,6 +116,7 @@ struct TraceConfig {
     int group_waves;    // waves per workgroup of the one-ray-per-thread grid (1 or 4)
     int leaf_batch;     // Q8 grid: 0 tests leaves on the spot; 1..64 queues them per wave
                         // and tests them once this many are queued (scenes < 2^26 tris)
+    int64_t max_tris;   // triangles of the launch's largest scene
     bool pack_ok;       // every scene's nodes can be named by pack_children
 };
 

@@ -1482,28 +1482,47 @@ hipError_t launch_persistent(const TraceConfig &cfg, const DevJob *jobs, int n_j
 // them).  Four lanes win while the launch has fewer waves than the chip holds,
 // two a little longer on plain nodes, whose one-lane visit is dearer; beyond,
 // the extra instructions of shared rays cost more than the short waves save.
-// us per call for indoor 18k / indoor 1.03M / terrain 3M / terrain 52k
-// triangles, rays in rows:
-//                quantised: 1 lane       4 lanes            plain: 1 lane          2 lanes             4 lanes
-//      5,760    68 106  98  76     40  61  55  42      72 114 106  80     53  81  75  62     39  58  52  40
-//    131,072    96 163 213 105     68 101 125  78     109 192 247 119     78 120 165  95     66  97 121  76
-//    262,144    86 208 202  88     94 162 130  86     103 256 218 104     84 170 155  83     91 160 126  83
-//    393,216   119 213 257 146    133 202 207 138     137 225 297 156    114 190 212 122    127 192 196 136
-//    524,288   129 228 273 176    158 243 244 171     152 251 304 195    127 218 225 151    153 237 237 166
-//  1,048,576   182 307 344 217    270 404 466 319     204 344 390 248    198 323 373 244    261 389 454 313
-//  2,097,152   270 438 536 349    497 747 812 581     311 501 635 400    337 528 610 411    484 717 787 570
-// (262,144 is one dense frame, the others 1,024 azimuths an environment; some
-// 15 us of each are the call's host side.)
-constexpr int64_t kFourLaneRays = 3 << 17;
-constexpr int64_t kTwoLaneRays = 3 << 19;   // plain nodes
+// The longest rays, which the lanes shorten, grow with the scene, and the
+// limits with its triangles (the largest scene's).  us a launch replayed from
+// a graph, 64 x 1,024 beams an environment, one / four lanes on quantised and
+// one / two / four on plain nodes (one dense frame of 262,144 rays on quantised
+// nodes gains less: 104 / 96 on 12.6k triangles, 113 / 107 on 53.7k, 90 / 95 on
+// 18.4k):
+//                    indoor 12.6k          terrain 53.8k         indoor 152k
+//   rays            q8       plain        q8       plain        q8       plain
+//     131,072   103  75  108  92  72   116  84  125  97  81   144  96  150 106  90
+//     262,144   103  96  114  89  90   129 121  151 118 119   154 120  173 113 114
+//     327,680   103 111  118  94 106   133 139  150 121 131   168 141  191 138 138
+//     393,216   105 127  120 101 121   139 156  155 132 150   167 157  188 140 151
+//     786,432            171 170 218            214 206 267            266 247 280
+//   1,048,576            181 188 269            273 263 351            285 266 347
+//   1,572,864            252 271 385            335 347 488            312 343 477
+//                    indoor 1.03M          terrain 3.0M          terrain 202k
+//     262,144   210 153  240 160 144   255 202  291 222 191   168 139  187 142 135
+//     327,680   222 183  243 188 175   250 210  283 221 202   172 165  184 151 162
+//     393,216   226 195  260 191 187   267 252  291 245 241   173 180  197 158 176
+//     524,288   235 245  255 211 234   317 317  355 288 301   208 236  233 202 230
+//   1,048,576            338 337 418            464 400 485            324 313 399
+//   1,572,864            391 415 560            634 586 724            416 430 572
+struct GroupLimits {
+    int64_t four, two;   // rays (two: plain nodes)
+};
+
+GroupLimits group_limits(int64_t max_tris)
+{
+    if (max_tris < (1 << 16)) return {8 << 15, 24 << 15};
+    if (max_tris < (1 << 19)) return {10 << 15, 32 << 15};
+    return {12 << 15, 48 << 15};
+}
 
 int group_lanes(const TraceConfig &cfg, int fmt, int64_t total)
 {
     if (cfg.persistent || cfg.stack_lds != 0 || !cfg.waves_cap || cfg.group_waves != 1 ||
         cfg.leaf_batch != 0)
         return 1;
-    if (total <= kFourLaneRays) return 4;
-    return fmt == FMT_WIDE && total <= kTwoLaneRays ? 2 : 1;
+    const GroupLimits most = group_limits(cfg.max_tris);
+    if (total <= most.four) return 4;
+    return fmt == FMT_WIDE && total <= most.two ? 2 : 1;
 }
 
 template <int MODE, int FMT>

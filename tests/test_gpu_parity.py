@@ -954,3 +954,46 @@ def test_calls_beside_a_capture_leave_it_whole(mode):
     torch.cuda.synchronize()
     assert ctx.device_bytes() == base
     ctx.close()
+
+
+@pytest.mark.parametrize("tris,four,two", [((1 << 16) - 1, 8 << 15, 24 << 15),
+                                           (1 << 16, 10 << 15, 32 << 15),
+                                           ((1 << 19) - 1, 10 << 15, 32 << 15),
+                                           (1 << 19, 12 << 15, 48 << 15)])
+def test_lane_limits_by_scene_size(ctx, tris, four, two):
+    """The last launch that shares its rays between four and between two lanes
+    and the next one, for scenes on either side of the limits' steps (by the
+    launch's largest scene), against one lane a ray."""
+    import torch
+    rng = np.random.default_rng(tris)
+    v = (rng.uniform(-40, 40, (tris, 1, 3)) + rng.uniform(-0.8, 0.8, (tris, 3, 3))).reshape(-1, 3)
+    v, t = v.astype(np.float32), np.arange(3 * tris, dtype=np.int32).reshape(-1, 3)
+    small = synth.random_soup(rng, 500, 40.0)
+    pat = ctx.upload_pattern(rng.normal(size=(64, 3)).astype(np.float32), 64)
+    pat1 = ctx.upload_pattern(np.array([[0.6, 0.8, 0.1]], np.float32), 1)
+    poses = np.zeros((two // 64, 12), np.float32)
+    poses[:, [0, 5, 10]] = 1
+    poses[:, [3, 7, 11]] = rng.uniform(-30, 30, (len(poses), 3))
+    p = cuda(poses)
+    for fmt, limits in ((RC_NODE_FP32, (four, two)), (RC_NODE_Q8, (four,))):
+        ids = [ctx.upload_scene(v, t), ctx.upload_scene(*small)]
+        for s in ids:
+            ctx.build(s, node_format=fmt)
+        for n in limits:
+            for more in (0, 1):
+                jobs = [Job(ids[0], pat, p[:n // 64 - 1], 0.0, 90.0, 0),
+                        Job(ids[1], pat, p[:1], 0.0, 90.0, n - 64)]
+                if more:
+                    jobs.append(Job(ids[1], pat1, p[:1], 0.0, 90.0, n))
+                log(f"{tris} triangles, node format {fmt}, {n + more} rays")
+                r0, h0 = ctx.cast(jobs)
+                ctx.set_tuning(group_waves=4)
+                try:
+                    r1, h1 = ctx.cast(jobs)
+                finally:
+                    ctx.reset_tuning()
+                assert r0.numel() == n + more and int((h0 >= 0).sum()) > n // 100
+                assert torch.equal(h0, h1)
+                assert torch.equal(r0.view(torch.int32), r1.view(torch.int32))
+        for s in ids:
+            ctx.release_scene(s)
