@@ -118,13 +118,12 @@ __global__ __launch_bounds__(kBlock) void k_nearest(const NodeRec *__restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// Bounds of the shared search.  gap2 is the squared distance to a box in float32, off by less than
-// 2^-21 of itself (one rounding each in the differences, squares and sums)
-// or an underflow.  A box is dropped when it exceeds limit(best) =
+// Bounds of the shared search.  gap2 is the squared distance to a box in
+// float32, off by less than 2^-21 of itself (one rounding each in the
+// differences, squares and sums) or an underflow.  A box is dropped when it exceeds limit(best) =
 // best (1 + 2^-19) + 1e-37, which also covers the sort key's two low bits.
 // Where the best is beyond 1e38 float32 squares overflow (or nothing was
 // found: infinite or NaN coordinates), and the query goes to search_binary.
-//
 constexpr int kQuadLds = 24;                 // stack entries a query in LDS (G = 4)
 constexpr int kWideStack = 96;               // three pushes per two levels of 62
 constexpr uint32_t kNoKey = 0x7f800000u;     // keys from here on (+inf): no candidate
@@ -185,10 +184,10 @@ inline unsigned xcd_grid(int64_t n, int per_block) { return (grid_for(n, per_blo
 // four boxes; a child that is a point itself is measured at once.  A search is
 // a chain of dependent fetches (12 such visits on average, 77 the longest, on
 // scans of a room), so a launch that does not fill the chip ends with its
-// longest query: 5,000 / 50,000 / 131,072 / 262,144 queries on 250,001 points
-// take some 35 / 55 / 85 / 155 us where one thread a query takes 70 / 80 /
-// 104 / 160.  Beyond (400,000: 215 against 190) the shared queries' extra
-// instructions cost more.
+// longest query: 5,000 / 50,000 / 131,072 queries on 250,001 points take some
+// 35 / 55 / 85 us where one thread a query takes 70 / 80 / 104.  Beyond
+// quad_queries (400,000: 215 against 190) the shared queries' extra instructions
+// cost more.
 __global__ __launch_bounds__(64) void k_nearest_quad(const NodeRec *__restrict__ nodes,
                                                      const float4 *__restrict__ pts,
                                                      const float *__restrict__ q, int64_t n_q,
@@ -343,8 +342,24 @@ __global__ __launch_bounds__(kBlock) void k_metric_final(const double *__restric
 
 }  // namespace
 
-// Four lanes a query up to here: see k_nearest_quad.
-constexpr int64_t kQuadQueries = 1 << 18;
+// Queries up to which four lanes share one: more for larger clouds, whose
+// chains of fetches are longer.  us a call (build and search), four lanes / one,
+// queries ordered by azimuth (random order likewise):
+//     queries    1,000 points   5,000       50,000      250,001     1,000,000
+//      65,536     115 / 130
+//     100,000     124 / 135    146 / 159   172 / 201   224 / 282   315 / 386
+//     150,000                  165 / 165   198 / 209   252 / 288   337 / 422
+//     200,000                  177 / 173   214 / 218   268 / 314   359 / 425
+//     230,000                  190 / 174   225 / 226   283 / 328   391 / 442
+//     262,144                  198 / 177   236 / 231   297 / 346   402 / 457
+//     300,000                  211 / 188   251 / 244   312 / 352   432 / 478
+//     350,000                  225 / 202   267 / 253   333 / 357   449 / 484
+static int64_t quad_queries(int64_t n_ref)
+{
+    int bits = 0;
+    while (bits < 19 && (n_ref >> (bits + 1)) > 0) ++bits;
+    return (int64_t)(bits < 11 ? 3 : bits - 8) << 15;
+}
 
 size_t nn_scratch_bytes(int64_t n_ref)
 {
@@ -395,7 +410,7 @@ hipError_t nearest_launch(const float *ref, int64_t n_ref, const float *query, i
         hipError_t e = lbvh_build_points_launch(b, pts, s);
         if (e != hipSuccess) return e;
     }
-    if (n_q > 0 && n_q <= kQuadQueries && n_ref > 1 && n_ref <= kPackMaxTris) {
+    if (n_q > 0 && n_q <= quad_queries(n_ref) && n_ref > 1 && n_ref <= kPackMaxTris) {
         hipLaunchKernelGGL(k_nearest_quad, dim3(xcd_grid(n_q, 16)), dim3(64), 0, s, nodes, pts,
                            query, n_q, out_d, out_i);
     } else if (n_q > 0)

@@ -167,3 +167,22 @@ def test_metric_errors(ctx):
     with pytest.raises(rcast.RcastError) as e:
         ctx.chamfer_fscore(P, P, -1.0)
     assert e.value.status == rcast.RC_E_INVAL
+
+
+@pytest.mark.parametrize("n_ref,most", [(4095, 3 << 15), (4096, 4 << 15), (70_000, 8 << 15)])
+def test_nearest_by_four_lanes_and_by_one(ctx, n_ref, most):
+    """The last number of queries that four lanes share one each of and the
+    next: the same answers, and the tree search's of SciPy."""
+    from scipy.spatial import cKDTree
+    rng = np.random.default_rng(n_ref)
+    ref = rng.uniform(-1, 1, (n_ref, 3)).astype(np.float32)
+    q = rng.uniform(-1.2, 1.2, (most + 1, 3)).astype(np.float32)
+    log(f"{n_ref} points, {most} queries and one more")
+    d, i = gpu_nearest(ctx, ref, q[:most])
+    d1, i1 = gpu_nearest(ctx, ref, q)
+    assert np.array_equal(d, d1[:most]) and np.array_equal(i, i1[:most])
+    # distances of the same float32 points in FP64: a few roundings apart
+    want, _ = cKDTree(ref.astype(np.float64)).query(q.astype(np.float64))
+    np.testing.assert_allclose(d1, want, rtol=1e-14, atol=0)
+    g = ref[i1].astype(np.float64) - q.astype(np.float64)
+    assert np.array_equal(d1, np.sqrt((g[:, 0] ** 2 + g[:, 1] ** 2) + g[:, 2] ** 2))
