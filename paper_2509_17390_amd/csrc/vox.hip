@@ -377,7 +377,9 @@ struct Scratch {
     {
         want.push_back({(void **)p, (bytes + 255) & ~(size_t)255});
     }
-    rc_status commit()
+    // Where the scratch has to grow, it grows to `ahead` bytes (what the call
+    // that usually comes next will ask for) if there is room for them.
+    rc_status commit(size_t ahead = 0)
     {
         size_t need = 0;
         for (auto &w : want) need += w.second;
@@ -385,9 +387,15 @@ struct Scratch {
             if (c->mesh_ws) dev_free(c, c->mesh_ws, c->mesh_ws_bytes);
             c->mesh_ws = nullptr;
             c->mesh_ws_bytes = 0;
-            rc_status st = dev_alloc(c, &c->mesh_ws, need);
+            size_t size = need > ahead ? need : ahead;
+            rc_status st = dev_alloc(c, &c->mesh_ws, size);
+            if (st != RC_OK && size > need) {
+                (void)hipGetLastError();   // the refused allocation's
+                size = need;
+                st = dev_alloc(c, &c->mesh_ws, size);
+            }
             if (st != RC_OK) return st;
-            c->mesh_ws_bytes = need;
+            c->mesh_ws_bytes = size;
         }
         char *base = static_cast<char *>(c->mesh_ws);
         for (auto &w : want) {
@@ -397,6 +405,27 @@ struct Scratch {
         return RC_OK;
     }
 };
+
+// What marching cubes takes of a grid of n points.
+struct McScratch {
+    size_t inside, words, list, sums;
+    explicit McScratch(int64_t n)
+    {
+        const int64_t nw = mc_words(n), nb = mc_blocks(n);
+        inside = 2 * sizeof(uint64_t) * nw;
+        words = mc_word_bytes() * nw;
+        list = (size_t)512 * nb;
+        sums = sizeof(uint32_t) * (4 * nb + 3);
+    }
+    size_t bytes() const
+    {
+        size_t all = 0;
+        for (size_t part : {inside, words, list, sums}) all += (part + 255) & ~(size_t)255;
+        return all;
+    }
+};
+
+constexpr int64_t kMaxMcPoints = (int64_t)1 << 29;
 
 }  // namespace
 
@@ -484,7 +513,8 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
         ws.take(&sums, sizeof(uint64_t) * (size_t)g.n);
         ws.take(&sel, radix_select_state_bytes());
     }
-    st = ws.commit();
+    // the field's mesh is extracted next
+    st = ws.commit(g.n <= kMaxMcPoints ? McScratch(g.n).bytes() : 0);
     if (st != RC_OK) return st;
     if (quant) {
         HIP_TRY(tsdf_smooth_sums_launch(surf, a, b, sums, g, w, s));
@@ -550,7 +580,7 @@ rc_status rc_marching_cubes(rc_ctx *c, const rc_grid *grid, const float *phi, fl
     if (st != RC_OK) return st;
     // at most 3 vertices per lattice point and 5 triangles per cell: 32-bit
     // counts and int32 vertex ids hold grids up to 2^29 voxels
-    if (g.n > ((int64_t)1 << 29)) return fail(RC_E_INVAL, "grid too large for 32-bit counts");
+    if (g.n > kMaxMcPoints) return fail(RC_E_INVAL, "grid too large for 32-bit counts");
     if (c->mock) return fail(RC_E_STATE, "a mock context does not extract meshes");
     HIP_TRY(hipSetDevice(c->device));
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -570,10 +600,11 @@ rc_status rc_marching_cubes(rc_ctx *c, const rc_grid *grid, const float *phi, fl
     Scratch ws(c);
     McBuffers b;
     const int64_t nw = mc_words(g.n), nb = mc_blocks(g.n);
-    ws.take(&b.inside, 2 * sizeof(uint64_t) * nw);
-    ws.take(&b.words, mc_word_bytes() * nw);
-    ws.take(&b.list, (size_t)512 * nb);
-    ws.take(&b.nlist, sizeof(uint32_t) * (4 * nb + 3));
+    const McScratch size(g.n);
+    ws.take(&b.inside, size.inside);
+    ws.take(&b.words, size.words);
+    ws.take(&b.list, size.list);
+    ws.take(&b.nlist, size.sums);
     st = ws.commit();
     if (st != RC_OK) return st;
     b.cells = b.inside + nw;

@@ -506,3 +506,30 @@ def test_sweeps_by_slices_and_by_rows(ctx, shape):
     surf = (rng.random(shape, dtype=np.float32) < 0.3).astype(np.uint8)
     log(f"{shape}")
     check_tsdf(ctx, surf, (0.0, 0.0, 0.0), 0.5, 0.5, 0.3, 1.0, tag=f"{shape}")
+
+
+def test_scratch_holds_the_mesh_extraction(ctx):
+    # a new context's scratch is allocated once for a field and its mesh; a
+    # budget that has room for the field alone still gives the field
+    import torch
+    shape = (60, 70, 80)
+    surf = cuda((np.random.default_rng(3).random(shape) < 0.3).astype(np.uint8))
+    phi = torch.empty(shape, dtype=torch.float32, device="cuda")
+    tiny = torch.ones((2, 2, 2), dtype=torch.float32, device="cuda")
+    used = []
+    for budget in (0, 1):
+        c = rcast.Context(0, budget_bytes=used[0] - 1 if budget else 0)
+        c.marching_cubes(c.grid((0, 0, 0), 0.5, (2, 2, 2), 0.0), tiny, 0.0)    # the case table
+        g = c.grid((0, 0, 0), 0.5, shape[::-1], 0.0)
+        phi.fill_(9.0)
+        c.tsdf(g, surf, phi, 0.4, 0.3, 1.5)
+        torch.cuda.synchronize()
+        used.append(c.device_bytes())
+        assert bool((phi != 9.0).all())
+        if not budget:
+            first = phi.clone()
+            c.marching_cubes(g, phi, 0.0)
+            assert c.device_bytes() == used[0]
+        else:
+            assert torch.equal(phi, first) and used[1] < used[0]
+        c.close()
