@@ -161,6 +161,16 @@ __device__ __forceinline__ void test_children(const NodeRec *__restrict__ nodes,
     hr = meets(nr.q0.z, nr.q0.w, nr.q1.z, nr.q1.w, nr.q2.z, nr.q2.w, tb);
 }
 
+// v's integer part, 0 if v is no number (a Gaussian thinner than float32's
+// reciprocals go has terms inf - inf).  The instruction saturates; a cast of
+// such a value has no defined result.
+__device__ __forceinline__ uint32_t floor_or_0(float v)
+{
+    uint32_t r;
+    asm("v_cvt_u32_f32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
 // LDS written by this wave is read by it next
 __device__ __forceinline__ void wave_lds_fence()
 {
@@ -288,7 +298,7 @@ k_voxelize(const NodeRec *__restrict__ nodes,
                 if (WAVES > 1 || __ballot(least <= kQSkip)) {
 #pragma unroll
                     for (int k = 0; k < kSkipRun; ++k)
-                        acc[x0 + k] += (uint32_t)fmaf(__builtin_amdgcn_exp2f(-q[k]), A, 0.5f);
+                        acc[x0 + k] += floor_or_0(fmaf(__builtin_amdgcn_exp2f(-q[k]), A, 0.5f));
                 }
             }
         }

@@ -308,3 +308,28 @@ def test_many_tiles_equal_few(ctx):
     np.testing.assert_array_equal(b["surf"], og.surface(b["occ"]))
     for r in (a, b):
         ctx.release_gaussians(r["set"])
+
+
+@pytest.mark.parametrize("dims", [(16, 16, 16), (160, 144, 96)])
+def test_terms_that_are_no_numbers_add_nothing(ctx, dims):
+    # scales whose reciprocals overflow float32, on and off the voxel centres,
+    # among ordinary Gaussians; few tiles (four waves each) and many
+    rng = np.random.default_rng(8)
+    hi = tuple(0.1 * d for d in dims)
+    plain = synth.random_gaussians(rng, 200, (0, 0, 0), hi, 0.05, 0.2)
+    n = 40
+    means = rng.uniform((0, 0, 0), hi, (n, 3)).astype(np.float32)
+    means[::2] = (np.floor(means[::2] / np.float32(0.1)) + 0.5) * np.float32(0.1)
+    scales = np.full((n, 3), 1e-39, np.float32)
+    scales[::3, 1:] = 0.1
+    thin = (means, np.tile(np.float32([1, 0, 0, 0]), (n, 1)), scales, np.ones(n, np.float32))
+    grid = og.Grid((0, 0, 0), 0.1, dims, tile=8, theta=0.05)
+    a = run(ctx, plain, grid)
+    b = run(ctx, tuple(np.concatenate([x, y]) for x, y in zip(plain, thin)), grid)
+    log(f"{dims}: {int((b['D'] > 0).sum())} voxels with density")
+    assert b["counts"].sum() >= a["counts"].sum() + n
+    differ = a["D"].view(np.uint32) != b["D"].view(np.uint32)
+    # only a voxel at a disc's own coordinate may see it (its exponent is 0 * inf or 0)
+    assert np.isfinite(b["D"]).all() and differ.sum() == 0
+    for r in (a, b):
+        ctx.release_gaussians(r["set"])
