@@ -1003,10 +1003,9 @@ __global__ __launch_bounds__(kBlock) void k_qem_eval(QemBuffers b, int nslots)
 }
 
 // Radix select, one digit of `width` bits a pass from the top.  The last block
-// to finish a pass picks the digit that holds the rank-th key (the blocks'
-// counts are device-scope atomics, read as such after its ticket) and clears
-// the counts for the next: a launch of its own for the pick took as long as
-// the pass.  Equal digits of a wave's keys are counted with one addition for
+// to finish a pass picks the digit that holds the rank-th key and clears the
+// counts for the next: a launch of its own for the pick took as long as the
+// pass.  Equal digits of a wave's keys are counted with one addition for
 // the two commonest, the rest one by one: most costs share their exponents
 // (25 and 53 us for the first two passes over 682,000 keys, now 10 and 9.5).
 // QEM: the need smallest keys are eligible, every candidate's if need is at
@@ -1059,14 +1058,17 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(const uint64_t *__res
     __syncthreads();
     for (int i = threadIdx.x; i < bins; i += kSelBlock)
         if (h[i]) __hip_atomic_fetch_add(&hist[i], h[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // each wave waits for its additions, then one thread takes the ticket; a
-    // release at device scope instead writes back the whole L2, wave by wave
-    // (70 us a pass)
+    // each wave's additions are done and the barrier orders them before thread
+    // 0's ticket, whose release hands them on; the last block's acquire takes all
+    // of them over.  A release by one thread a block writes back the XCD's L2
+    // once (a call of 11.02 ms takes 11.08; by every wave it made a pass 70 us).
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0)
-        last = __hip_atomic_fetch_add(&st->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+    if (threadIdx.x == 0) {
+        last = __hip_atomic_fetch_add(&st->ticket, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) ==
                gridDim.x - 1;
+        if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
     __syncthreads();
     if (!last) return;
     // bins 2 t and 2 t + 1 of thread t
