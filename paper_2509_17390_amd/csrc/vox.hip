@@ -429,13 +429,16 @@ constexpr int64_t kMaxMcPoints = (int64_t)1 << 29;
 
 }  // namespace
 
-// Outside-labelling rounds enqueued per flag read, for grids beyond one block's.
-// The usual masks settle in 2 to 5 rounds on small grids and 5 to 8 on large
-// ones; a flag read costs the stream some 25 us, a round after the last one
-// 5 us.  4 first up to 2^22 voxels (8 there: +8 us of 370 at 350,200 voxels), 8
-// beyond (6 and a second read: +40 us of 480 at 34.2M), then 4 and 8 at a time.
+// Outside-labelling rounds enqueued per flag read, for grids beyond one block's:
+// 8, then 4, then 8 at a time.  Closed rooms settle in 3 or 4 rounds up to 2^22
+// voxels, open ones and larger grids in 5 to 8, some in 9 and more; a flag read
+// costs the stream some 25 us and the field's pass behind it, a round after the
+// last one 2 to 4.  us a TSDF call, 8 / 4 rounds first:
+//   voxels   0.67M       1.08M       1.62M       2.63M       6.5M        29.8M
+//   closed   140 / 121   131 / 117   132 / 119   137 / 126   178 / 216   248 / 291
+//   open     154 / 199   139 / 191   148 / 194   370 / 461   266 / 326   230 / 271
 constexpr int kFloodBatchMax = 8;
-inline int flood_batch(int64_t k, int64_t n) { return k == 1 || (k == 0 && n <= (1 << 22)) ? 4 : 8; }
+inline int flood_batch(int64_t k) { return k == 1 ? 4 : kFloodBatchMax; }
 
 rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_tsdf_opts *opts,
                   float *out_phi, uint8_t *out_vtilde, void *stream)
@@ -543,7 +546,7 @@ rc_status rc_tsdf(rc_ctx *c, const rc_grid *grid, const uint8_t *surf, const rc_
         }
     }
     for (int64_t it = 0, k = 0; !small; ++k) {
-        const int nb = flood_batch(k, g.n);
+        const int nb = flood_batch(k);
         int32_t changed[kFloodBatchMax];
         HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int32_t) * nb, s));
         for (int r = 0; r < nb; ++r)
