@@ -922,7 +922,6 @@ rc_status rc_decimate(rc_ctx *c, const float *verts, int64_t nv, const int32_t *
     uint8_t *bnd;
     double *Q, *lo;
     float *partial, *box;
-    char *sortws;
     const size_t nss = (size_t)mc_scan_sums_len(nv > nt ? nv : nt);
     ws.take(&slots, sizeof(int32_t) * kNbrCap * (size_t)nv);
     ws.take(&cnt, sizeof(uint32_t) * (size_t)nv);
@@ -949,13 +948,12 @@ rc_status rc_decimate(rc_ctx *c, const float *verts, int64_t nv, const int32_t *
     ws.take(&flags, sizeof(int32_t));
     rc_status st = ws.commit();
     if (st != RC_OK) return st;
-    // the sorts run when the incidence lists (and, of a few vertices, the box's
-    // parts) are done with
-    const size_t sort_bytes = radix_sort_ws_bytes(nv);
+    // the sorts run when the incidence lists and the box's parts are done with:
+    // the lists (512 bytes a vertex) hold a sort's counts (4 KB a tile of 2,048
+    // vertices or more, and 1 KB) from two tiles on, the parts hold one tile's
+    const bool few = sizeof(int32_t) * kNbrCap * (size_t)nv < radix_sort_ws_bytes(nv);
     static_assert(sizeof(float) * 6 * kMinmaxBlocks >= 6144, "holds the sort of one tile");
-    if (sizeof(int32_t) * kNbrCap * (size_t)nv >= sort_bytes) sortws = reinterpret_cast<char *>(slots);
-    else if (sizeof(float) * 6 * kMinmaxBlocks >= sort_bytes) sortws = reinterpret_cast<char *>(partial);
-    else return fail(RC_E_DEVICE, "sort workspace");
+    char *const sortws = few ? reinterpret_cast<char *>(partial) : reinterpret_cast<char *>(slots);
     int32_t hf = 0;
     HIP_TRY(hipMemsetAsync(flags, 0, sizeof(int32_t), s));
     HIP_TRY(validate_mesh_launch(verts, nv, tris, nt, flags, s));
