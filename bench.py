@@ -1355,12 +1355,12 @@ TSDF_PASS_BYTES = {
 }
 
 
-def tsdf_bytes_per_voxel(shells: int, steps: int, quantile: bool = False) -> float:
+def tsdf_bytes_per_voxel(shells: int, steps: int) -> float:
     """Bytes per voxel of TSDF_PASS_BYTES for a band of `shells` shells and a
-    smoothing kernel of `steps` steps."""
+    smoothing kernel of `steps` steps (fixed threshold)."""
     b = TSDF_PASS_BYTES
     total = b["flood_sweep"] + b["mc_inside"] + b["mc_count"] + b["mc_emit"]
-    if 1 <= steps <= 3 and not quantile:
+    if 1 <= steps <= 3:
         total += b["pack_mask"] + b["smooth_bits"]
     else:
         total += b["smooth_x"] + b["smooth_y"] + b["smooth_z"] + b["pack"]

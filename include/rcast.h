@@ -183,7 +183,11 @@ rc_status rc_raycast_bruteforce(rc_ctx *ctx, const rc_job *jobs, int32_t n_jobs,
 /* Instrumented traversal: like rc_raycast_batch, and additionally writes
  * per-ray counts of BVH node records fetched (out_nodes) and triangles
  * tested (out_tris), DEVICE int32 arrays laid out like out_range.  These
- * are N_nodes(r_j) and K_j of the per-ray cost model of Sec. IV-C. */
+ * are N_nodes(r_j) and K_j of the per-ray cost model of Sec. IV-C.  The
+ * walk is one lane per ray and one record per visit; of RC_NODE_Q8 scenes
+ * rc_raycast_batch's large launches walk the same way, of RC_NODE_FP32
+ * scenes they take two levels a visit (records fetched in pairs), and small
+ * launches share a ray between lanes: the counts are this walk's. */
 rc_status rc_raycast_stats(rc_ctx *ctx, const rc_job *jobs, int32_t n_jobs,
                            float *out_range, int32_t *out_hit, int32_t *out_nodes,
                            int32_t *out_tris, void *stream);
@@ -549,10 +553,15 @@ typedef struct {
  * float32 `out_phi` (same layout); `out_vtilde` (DEVICE uint8, or NULL)
  * receives V~.  Runs on `stream` and returns when phi is complete (the
  * outside labelling of grids beyond some 9,000 words of 64 voxels repeats
- * until it settles, reading a flag per 4 to 8 rounds).  Scratch device memory of about 0.5 bytes per voxel (14 with more
- * than 3 smoothing steps or 4 shells, 21 to 23 with the quantile re-threshold, which
- * keeps the smoothing's integer sums) is kept by the context
- * (grown on demand, reused by later calls, freed by rc_destroy).
+ * until it settles, reading a flag per 4 to 8 rounds).  Scratch device memory
+ * is kept by the context (grown on demand, reused by later calls, freed by
+ * rc_destroy).  Per voxel of the grid with nx rounded up to a multiple of 64:
+ *   up to 3 smoothing steps and 4 shells   0.42 bytes
+ *   more than 4 shells                     2.4 (1.4 with out_vtilde given)
+ *   more than 3 steps                      13 to 14
+ *   quantile re-threshold                  20 to 22 (the smoothing's sums)
+ * and where it has to grow, at least the 0.8 bytes that rc_marching_cubes
+ * takes of the same grid, if there is room.
  * Errors: RC_E_INVAL (grid, options), RC_E_NOMEM, RC_E_DEVICE. */
 rc_status rc_tsdf(rc_ctx *ctx, const rc_grid *grid, const uint8_t *surf,
                   const rc_tsdf_opts *opts, float *out_phi, uint8_t *out_vtilde, void *stream);

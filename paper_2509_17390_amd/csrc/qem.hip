@@ -1377,6 +1377,10 @@ hipError_t qem_round_launch(const QemBuffers &b, int64_t nv, int64_t nt, int64_t
     return hipGetLastError();
 }
 
+// A vertex with more faces or neighbours than its lists hold is reported by
+// k_qem_end: until then the step runs on lists cut to their length.  Every entry
+// is a face or vertex of the mesh and the edges are among the faces' (at most
+// 3 nt), so all indices stay in range, and the caller discards the result.
 hipError_t qem_step_launch(const QemBuffers &b, int64_t nv, int64_t nt, int64_t max_edges,
                            int round_start, hipStream_t s)
 {
