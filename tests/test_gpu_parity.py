@@ -878,10 +878,12 @@ def _pattern_and_memory(ctx, s):
     return pat, ctx.device_bytes()
 
 
-def test_a_busy_stream_does_not_hold_another_streams_casts(ctx):
-    """Casts return once enqueued, however long another stream's work takes: a
-    stream with some tenths of a second of casts, and more casts on a second
-    one than launches are kept track of; both give their scenes back."""
+@pytest.mark.parametrize("behind", [False, True])
+def test_a_busy_stream_does_not_hold_another_streams_casts(ctx, behind):
+    """Casts return once enqueued, however long the work before them takes: a
+    stream with some tenths of a second of casts, and more casts than launches
+    are kept track of on a second one, or behind the long ones, where none of
+    them can have finished; both give their scenes back."""
     import torch
     s = synth.indoor_scene(seed=8, h=0.1, n_envs=512, n_az=1024)
     pat, base = _pattern_and_memory(ctx, s)
@@ -897,12 +899,13 @@ def test_a_busy_stream_does_not_hold_another_streams_casts(ctx):
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     done = torch.cuda.Event()
     torch.cuda.synchronize()
-    log("300 long casts and 1400 short ones on another stream")
+    short = 1000 if behind else 1400     # (a stream's own queue has an end, too)
+    log(f"300 long casts and {short} short ones, on the same stream: {behind}")
     for _ in range(300):
         ctx.raycast(long_job, big[0], big[1], stream=streams[0])
     done.record(streams[0])
-    for _ in range(1400):
-        ctx.raycast(job, out[0], out[1], stream=streams[1])
+    for _ in range(short):
+        ctx.raycast(job, out[0], out[1], stream=streams[0 if behind else 1])
     assert not done.query()
     ctx.release_scene(a)
     ctx.release_scene(b)
