@@ -1012,7 +1012,7 @@ __global__ __launch_bounds__(kBlock) void k_qem_eval(QemBuffers b, int nslots)
 // least their number (decided in the first pass), and a digit all of whose
 // keys are among them ends the select: prefix, filled up with ones, separates
 // the same keys.
-constexpr int kSelBlock = 1024, kSelBlocks = 256, kSelBits = 11;
+constexpr int kSelBlock = 1024, kSelBits = 11;
 
 template <bool QEM>
 __global__ __launch_bounds__(kSelBlock) void k_select_pass(const uint64_t *__restrict__ key,
@@ -1061,7 +1061,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_pass(const uint64_t *__res
     // each wave's additions are done and the barrier orders them before thread
     // 0's ticket, whose release hands them on; the last block's acquire takes all
     // of them over.  A release by one thread a block writes back the XCD's L2
-    // once (a call of 11.02 ms takes 11.08; by every wave it made a pass 70 us).
+    // once (by every wave it made a pass 70 us; see sel_grid).
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1328,10 +1328,15 @@ int sel_bins(int64_t ne_cap) { return wide_select(ne_cap) ? 1 << kSelBits : 256;
 constexpr int kQemSlots = 64;
 int qem_slots(int64_t ne_cap) { return wide_select(ne_cap) ? kQemSlots : 1; }
 
+// Blocks of a pass.  Each pays for its release (see k_select_pass), which up to
+// 2^20 keys costs more than the keys: 256 / 128 / 64 blocks take 173 / 166 / 170
+// us a coarse quantile reconstruction (350,200 keys) and 11.18 / 11.05 / 11.04
+// ms a decimation (682,000 keys at first); beyond, the keys count: 566 / 613 /
+// 711 us a reconstruction of 17.6M voxels.
 unsigned sel_grid(int64_t n)
 {
-    const unsigned g = grid_for(n, kSelBlock);
-    return g < 1 ? 1 : (g > (unsigned)kSelBlocks ? (unsigned)kSelBlocks : g);
+    const unsigned g = grid_for(n, kSelBlock), most = n <= (1 << 20) ? 128 : 256;
+    return g < 1 ? 1 : (g > most ? most : g);
 }
 
 }  // namespace
